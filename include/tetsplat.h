@@ -317,6 +317,18 @@ int render_regularizers(const float* verts, const int32_t* tets, const float* sd
                         void* stream);
 
 /*
+ * render_regularizers_backward: the gradient of weights[0] * L_eik +
+ * weights[1] * L_nc alone, after render_regularizers on the same inputs
+ * (which left the vertex normals in the workspace; the inputs and the
+ * workspace unchanged since).  dverts and dsdf are OVERWRITTEN.  May be
+ * repeated on one workspace.  Otherwise as render_regularizers.
+ */
+int render_regularizers_backward(const float* verts, const int32_t* tets, const float* sdf, int32_t V, int32_t K,
+                                 const int32_t* edges, const int32_t* n_edges, int64_t edge_capacity,
+                                 const float* weights, float* dverts, float* dsdf, void* workspace,
+                                 size_t workspace_bytes, void* stream);
+
+/*
  * render_prefilter_bounds: coarse-to-fine pre-filtering (App. B).  The
  * bounding box of the vertices of the tets the pre-filter keeps (alpha_max of
  * Eq. 1 at the tet's largest and smallest SDF value >= params->prefilter_tf,

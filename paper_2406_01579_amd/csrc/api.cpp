@@ -472,6 +472,25 @@ int render_regularizers(const float* verts, const int32_t* tets, const float* sd
   return RENDER_OK;
 }
 
+int render_regularizers_backward(const float* verts, const int32_t* tets, const float* sdf, int32_t V, int32_t K,
+                                 const int32_t* edges, const int32_t* n_edges, int64_t edge_capacity,
+                                 const float* weights, float* dverts, float* dsdf, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
+  if (K < 0 || V < 0 || V > (1 << 30) || K > (1 << 30)) return fail(RENDER_EINVAL, "K or V out of range");
+  if (edge_capacity < 0 || edge_capacity > 0xffffffffll) return fail(RENDER_EINVAL, "edge_capacity out of range");
+  if (!workspace || !n_edges || !weights || (K > 0 && (!verts || !tets || !sdf)) || (edge_capacity > 0 && !edges) ||
+      (V > 0 && (!dverts || !dsdf)))
+    return fail(RENDER_EINVAL, "null pointer");
+  if (((uintptr_t)tets & 15u) != 0) return fail(RENDER_EINVAL, "tets must be 16-byte aligned");
+  if (((uintptr_t)edges & 7u) != 0) return fail(RENDER_EINVAL, "edges must be 8-byte aligned");
+  const ts::RegLayout R = ts::reg_layout(V);
+  if (workspace_bytes < R.bytes) return fail(RENDER_ENOSPC, "workspace %zu < %zu bytes", workspace_bytes, R.bytes);
+  hipError_t e = ts::launch_regularizers_backward(verts, tets, sdf, V, K, edges, n_edges, edge_capacity, weights,
+                                                  dverts, dsdf, workspace, R, (hipStream_t)stream);
+  if (e != hipSuccess) return fail(RENDER_EHIP, "regularizers backward: %s", hipGetErrorString(e));
+  return RENDER_OK;
+}
+
 int render_workspace_size(const render_scene* scenes, int n_scenes, const render_view* views, int n_views,
                           const render_params* params, int64_t kept_capacity, int64_t entry_capacity,
                           size_t* bytes) {

@@ -236,6 +236,10 @@ hipError_t launch_regularizers(const float* verts, const int32_t* tets, const fl
                                const int32_t* edges, const int32_t* n_edges, int64_t edge_cap, const float* weights,
                                double* losses, float* dverts, float* dsdf, void* ws, const RegLayout& R,
                                hipStream_t st);
+hipError_t launch_regularizers_backward(const float* verts, const int32_t* tets, const float* sdf, int32_t V,
+                                        int32_t K, const int32_t* edges, const int32_t* n_edges, int64_t edge_cap,
+                                        const float* weights, float* dverts, float* dsdf, void* ws,
+                                        const RegLayout& R, hipStream_t st);
 hipError_t launch_prefilter_bounds(const DevScene& S, float tf, float* bounds, int64_t* kept, hipStream_t st);
 hipError_t launch_refit_cube(const float* bounds, const float* cube_in, int R, float* cube_out, hipStream_t st);
 hipError_t launch_cube_grid(int R, const float* cube, float* verts, int32_t* tets, hipStream_t st);

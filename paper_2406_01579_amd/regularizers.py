@@ -3,8 +3,9 @@
 ``MeshEdges(tets, V)`` builds the unique-edge list of the tet mesh once per
 topology; ``regularizers(verts, sdf, tets, edges)`` returns (L_eik, L_nc) as
 float64 device scalars and is differentiable with respect to ``verts`` and
-``sdf`` (its backward runs the kernels again with the upstream gradients as
-the two weights, read on the device: no host synchronisation)."""
+``sdf`` (its backward starts from the vertex normals that the forward left in
+its workspace, with the upstream gradients as the two weights, read on the
+device: no host synchronisation)."""
 from __future__ import annotations
 
 import ctypes as C
@@ -47,17 +48,21 @@ class MeshEdges:
         return int(self.buffer.shape[0])
 
 
-def _run(verts, sdf, tets, edges: MeshEdges, weights=None, dverts=None, dsdf=None):
-    V, K = int(verts.shape[0]), int(tets.shape[0])
+def _workspace(verts, tets) -> torch.Tensor:
     n = C.c_size_t(0)
-    check(_lib.lib().render_regularizers_workspace_size(V, K, C.byref(n)))
-    ws = torch.empty(max(1, int(n.value)), dtype=torch.uint8, device=verts.device)
+    check(_lib.lib().render_regularizers_workspace_size(int(verts.shape[0]), int(tets.shape[0]), C.byref(n)))
+    return torch.empty(max(1, int(n.value)), dtype=torch.uint8, device=verts.device)
+
+
+def _run(verts, sdf, tets, edges: MeshEdges, weights=None, dverts=None, dsdf=None, ws=None):
+    V, K = int(verts.shape[0]), int(tets.shape[0])
+    ws = _workspace(verts, tets) if ws is None else ws
     losses = torch.empty(2, dtype=torch.float64, device=verts.device)
     ptr = (lambda t: None if t is None else t.data_ptr())
     check(_lib.lib().render_regularizers(verts.data_ptr(), tets.data_ptr(), sdf.data_ptr(), V, K,
                                          edges.buffer.data_ptr(), edges.count.data_ptr(), edges.capacity,
                                          ptr(weights), losses.data_ptr(), ptr(dverts), ptr(dsdf), ws.data_ptr(),
-                                         int(n.value), _stream(verts.device)))
+                                         ws.numel(), _stream(verts.device)))
     return losses
 
 
@@ -66,17 +71,24 @@ class RegularizerFunction(torch.autograd.Function):
     def forward(ctx, verts, sdf, tets, edges):
         v, f = verts.detach().contiguous(), sdf.detach().contiguous()
         t = tets.contiguous()
-        ctx.save_for_backward(v, f, t)
+        ws = _workspace(v, t)
+        losses = _run(v, f, t, edges, ws=ws)
+        # the workspace holds the vertex normals that the backward starts from
+        ctx.save_for_backward(v, f, t, ws)
         ctx.edges = edges
-        return _run(v, f, t, edges)
+        return losses
 
     @staticmethod
     def backward(ctx, g):
-        v, f, t = ctx.saved_tensors
+        v, f, t, ws = ctx.saved_tensors
+        edges = ctx.edges
         w = g.detach().float().contiguous()
-        dv = torch.zeros_like(v)
-        df = torch.zeros_like(f)
-        _run(v, f, t, ctx.edges, w, dv, df)
+        dv, df = torch.empty_like(v), torch.empty_like(f)
+        check(_lib.lib().render_regularizers_backward(v.data_ptr(), t.data_ptr(), f.data_ptr(), int(v.shape[0]),
+                                                      int(t.shape[0]), edges.buffer.data_ptr(),
+                                                      edges.count.data_ptr(), edges.capacity, w.data_ptr(),
+                                                      dv.data_ptr(), df.data_ptr(), ws.data_ptr(), ws.numel(),
+                                                      _stream(v.device)))
         return dv, df, None, None
 
 
