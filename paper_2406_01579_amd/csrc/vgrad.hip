@@ -58,7 +58,9 @@ static_assert(VB_HASH == 1 << 9, "the slot hash keeps 9 bits");
 template <int P, bool DET>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_vertex_bwd(void* ws, Layout L) {
   __shared__ uint32_t hkey[DET ? 1 : VB_HASH];   // vertex id + 1; 0: empty
-  __shared__ float hval[7][DET ? 1 : VB_HASH];   // dverts xyz, dsdf, dcolors xyz
+  // doubles: an LDS add of a double takes 9 cycles per wave and CU, one of a
+  // float 194 (the kernel: 46.5 to 43.2 us at the training shape)
+  __shared__ double hval[7][DET ? 1 : VB_HASH];  // dverts xyz, dsdf, dcolors xyz
   __shared__ int bscene;
   DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
   const DevView* vw = at<const DevView>(ws, L.o_view);
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       for (int h = threadIdx.x; h < VB_HASH; h += blockDim.x) {
         hkey[h] = 0u;
 #pragma unroll
-        for (int m = 0; m < 7; ++m) hval[m][h] = 0.0f;
+        for (int m = 0; m < 7; ++m) hval[m][h] = 0.0;
       }
       if (threadIdx.x == 0) bscene = tet_ok ? ks : -1;   // thread 0 holds the block's first tet
       __syncthreads();
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
           if (old == 0u || old == vv + 1u) {
 #pragma unroll
             for (int m = 0; m < 7; ++m)
-              if (val[m] != 0.0f) atomicAdd(&hval[m][h], val[m]);
+              if (val[m] != 0.0f) unsafeAtomicAdd(&hval[m][h], (double)val[m]);
             put = true;
             break;
           }
@@ -302,10 +304,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         if (key == 0u) continue;
         const size_t vv = (size_t)(key - 1u);
         for (int m = 0; m < 3; ++m) {
-          if (hval[m][h] != 0.0f) gatomic_add(&S.dverts[3 * vv + m], hval[m][h]);
-          if (hval[4 + m][h] != 0.0f) gatomic_add(&S.dcolors[3 * vv + m], hval[4 + m][h]);
+          const float x = (float)hval[m][h], c = (float)hval[4 + m][h];
+          if (x != 0.0f) gatomic_add(&S.dverts[3 * vv + m], x);
+          if (c != 0.0f) gatomic_add(&S.dcolors[3 * vv + m], c);
         }
-        if (hval[3][h] != 0.0f) gatomic_add(&S.dsdf[vv], hval[3][h]);
+        const float f = (float)hval[3][h];
+        if (f != 0.0f) gatomic_add(&S.dsdf[vv], f);
       }
     }
     __syncthreads();
