@@ -33,7 +33,8 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
                                               unsigned long long* done_mask,
                                               float& T, float& Tb, float& O, float (&acc)[7], int& last,
                                               bool want_acc, uint32_t& nblend,
-                                              unsigned long long* bmask = nullptr) {
+                                              unsigned long long* bmask = nullptr,
+                                              unsigned long long* bml = nullptr) {
   constexpr int NT = 64 * NWV;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool done = !c.inside;
@@ -49,21 +50,26 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, start + CHN, end - 1);
   }
+  // the last chunk's blend masks, still in LDS: the last wave writes them out
+  // after the next chunk's loads have been issued (loads and stores share one
+  // counter, so a store issued before the wait for a load is waited for too)
+  uint32_t mbase = start;
+  int mn = 0;
+  const auto write_masks = [&] {
+    if (wave == NWV - 1 && lane < mn) bmask[mbase + lane] = bml[lane];
+  };
   for (uint32_t base = start; base < end; base += CHN) {
     __syncthreads();
     if (*done_mask == ~0ull) break;
     const int n = (int)min((uint32_t)CHN, end - base);
-    rp.store(recs, n);
+    rp.store(recs, n, feat);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, base + 2 * CHN, end - 1);
+    if (bmask) write_masks();
     __syncthreads();
     // phase A: coverage and Eq. 1 of the live (entry, pixel) pairs, packed;
     // hm[pixel] collects the chunk entries the pixel may blend
-    if (threadIdx.x < 64) hm[threadIdx.x] = 0ull;
-    for (int q = threadIdx.x; q < n * 7; q += NT) {
-      const int e = q / 7, k = q - e * 7;
-      feat[k][e] = k < 3 ? recs[e].c[k] : k == 3 ? recs[e].zt : recs[e].n[k - 4];
-    }
+    if (wave == NWV - 1) hm[lane] = 0ull;
     if (wave == 0) chunk_pairs<CHN>(recs, n, c, ~*done_mask, pm);
     __syncthreads();
     for_each_pair<CHN>(pm, NT, [&](int e, int pix) {
@@ -110,15 +116,17 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
       nblend += (uint32_t)__popcll(blended);   // the chunk's blended pairs (per lane)
       if (bmask) {
         // per entry of the chunk, the pixels that blended it (what the
-        // backward's pairs are): lane e writes entry e's mask
-        const uint64_t mine = wave_transpose64(blended);
-        if (lane < n) bmask[base + lane] = mine;
+        // backward's pairs are): entry e's mask in lane e
+        bml[lane] = wave_transpose64(blended);
       }
       const unsigned long long m = __ballot(done);
       if (lane == 0) *done_mask = m;
     }
+    mbase = base;
+    mn = n;
   }
   __syncthreads();
+  if (bmask) write_masks();
 }
 
 // Background of `count` tiles with an empty list (the dispatch slots from
@@ -173,6 +181,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   __shared__ PairMap<CHN> pm;
   __shared__ uint64_t hm[64];
   __shared__ float feat[7][CHN];
+  __shared__ unsigned long long bml[64];
   __shared__ unsigned long long done_mask;
 
   // the tiles with an empty list take the last slots (length bucket 0):
@@ -199,7 +208,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   const bool count = L.o_pairs != 0;
   forward_sweep<NWV, CHN>(vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
                           feat, &done_mask, T, Tb, O, acc, last, true, nblend,
-                          L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr);
+                          L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr, bml);
   if ((threadIdx.x >> 6) == 0) {
     // end of the tile's blended prefix: where the backward starts its walk
     int wmax = last;
@@ -350,22 +359,17 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     // also wait for the record loads just issued
     bm_cur = bm_next;
     if (wave == 0 && cb - CHB >= (int64_t)start && lane < (unsigned)CHB) bm_next = bmask[base - CHB + lane];
-    rp.store(recs, n, ridx);
+    rp.store(recs, n, feat, ridx);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, below(cb - 2 * CHB), pend - 1u);
     __syncthreads();
     // phase A: coverage, faces and Eq. 1 of every (entry, pixel) pair the
     // forward blended, packed
-    if (threadIdx.x < 64) hmask[threadIdx.x] = 0ull;
-    for (int q = threadIdx.x; q < n * 7; q += NT) {
-      const int e = q / 7, k = q - e * 7;
-      feat[k][e] = k < 3 ? recs[e].c[k] : k == 3 ? recs[e].zt : recs[e].n[k - 4];
-    }
+    if (wave == NWV - 1) hmask[lane] = 0ull;
     if (wave == 0) {
       // lane e: the pixels that blended entry e (the forward's masks, loaded
       // a chunk ahead)
-      const uint64_t live_e = bm_cur;
-      chunk_pairs<CHB>(recs, n, c, live_e, pm);
+      pair_map<CHB>(n, bm_cur, pm);
     }
     __syncthreads();
     for_each_pair<CHB>(pm, NT, [&](int e, int pix) {

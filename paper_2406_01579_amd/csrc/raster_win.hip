@@ -107,18 +107,6 @@ __device__ __forceinline__ unsigned long long mask_load(const unsigned long long
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Per chunk: the entries' blended features as a conflict-free table
-// (feat[k][e]: c[3], zt, n[3]) and a cleared per-pixel candidate mask.
-template <int CH>
-__device__ __forceinline__ void load_chunk_tables(const ViewRec* recs, int n, float (*feat)[CH], uint32_t* hm,
-                                                  int nthreads) {
-  if (threadIdx.x < 64) hm[threadIdx.x] = 0u;
-  for (int q = threadIdx.x; q < n * 7; q += nthreads) {
-    const int e = q / 7, k = q - e * 7;
-    feat[k][e] = k < 3 ? recs[e].c[k] : k == 3 ? recs[e].zt : recs[e].n[k - 4];
-  }
-}
-
 }  // namespace
 
 template <int NWV, int WS>
@@ -196,11 +184,11 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
     if (done_mask == ~0ull) break;
     const int n = (int)min((uint32_t)CHW, end - base);
     walked = base + (uint32_t)n;
-    rp.store(recs, n);
+    rp.store(recs, n, feat);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, base + 2 * CHW, end - 1);
     __syncthreads();
-    load_chunk_tables(recs, n, feat, hm, NT);
+    if (wave == NWV - 1) hm[lane] = 0u;
     if (wave == 0) chunk_pairs<CHW>(recs, n, c, ~done_mask, pm);
     __syncthreads();
     for_each_pair<CHW>(pm, NT, [&](int e, int pix) {
@@ -396,11 +384,11 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
     __syncthreads();
     if (done_mask == ~0ull) break;
     const int n = (int)min((uint32_t)CHB, end - base);
-    rp.store(recs, n, erec);
+    rp.store(recs, n, feat, erec);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, base + 2 * CHB, end - 1);
     __syncthreads();
-    load_chunk_tables(recs, n, feat, hm, NT);
+    if (wave == NWV - 1) hm[lane] = 0u;
     if (threadIdx.x < (unsigned)n) {
       // the entry's gradient slot (its record came with the chunk's records);
       // its blend mask starts empty

@@ -133,12 +133,7 @@ template <int CH, int GROUP = 1>
 __device__ __forceinline__ void pair_offsets(int n, uint64_t m_e, uint64_t* pmask, uint32_t* poff) {
   const int lane = threadIdx.x & 63;
   const uint64_t m = lane < n ? m_e : 0ull;
-  uint32_t x = ((uint32_t)__popcll(m) + (GROUP - 1)) / GROUP;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    x += lane >= d ? y : 0u;
-  }
+  const uint32_t x = wave_scan_add(((uint32_t)__popcll(m) + (GROUP - 1)) / GROUP);
   if (lane < CH) {
     pmask[lane] = m;
     poff[lane + 1] = x;
@@ -170,12 +165,7 @@ __device__ __forceinline__ void pair_map(int n, uint64_t m_e, PairMap<CH>& M) {
   const int lane = threadIdx.x & 63;
   const uint64_t m = lane < n ? m_e : 0ull;
   const uint32_t cnt = (uint32_t)__popcll(m);
-  uint32_t x = cnt;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    x += lane >= d ? y : 0u;
-  }
+  const uint32_t x = wave_scan_add(cnt);
   const uint32_t first = x - cnt;
   const uint32_t k = (uint32_t)__popcll(__ballot(m != 0ull) & ((1ull << lane) - 1ull));
   // the pairs fill at most CH blocks; this wave's own LDS operations take
@@ -190,12 +180,7 @@ __device__ __forceinline__ void pair_map(int n, uint64_t m_e, PairMap<CH>& M) {
   __builtin_amdgcn_wave_barrier();
   const uint64_t bs = lane < CH ? M.bstart[lane] : 0ull;
   const uint32_t bc = (uint32_t)__popcll(bs);
-  uint32_t y = bc;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t z = __shfl_up(y, d, 64);
-    y += lane >= d ? z : 0u;
-  }
+  const uint32_t y = wave_scan_add(bc);
   if (lane < CH) M.bfirst[lane] = y - bc;
   if (lane == 63) M.total = x;
 }
@@ -262,15 +247,29 @@ struct RecPipe {
       if (E0 && (q & 7) == 7) vw[j] = __uint_as_float(rfirst[idx[j]]);   // entry0: the record's last word
     }
   }
-  // With ridx, also each record's index (what a chunk needs of srec later
-  // comes from LDS then, not from a global load on its critical path).
-  __device__ __forceinline__ void store(ViewRec* recs, int n, uint32_t* ridx = nullptr) const {
+  // The blended features (c, zt, n: parts 5 and 6) also go to a table of
+  // their own, whose per-lane gathers have no bank conflicts.  With ridx, so
+  // does each record's index (what a chunk needs of srec later comes from LDS
+  // then, not from a global load on its critical path).
+  __device__ __forceinline__ void store(ViewRec* recs, int n, float (*feat)[CH], uint32_t* ridx = nullptr) const {
 #pragma unroll
     for (int j = 0; j < PQ; ++j) {
       const int q = (int)threadIdx.x + j * NT;
       if (q < n * 8) {
         reinterpret_cast<float4*>(&recs[q >> 3])[q & 7] = make_float4(vx[j], vy[j], vz[j], vw[j]);
-        if (ridx && (q & 7) == 0) ridx[q >> 3] = cur[j];
+        const int e = q >> 3, part = q & 7;
+        if (part == 5) {
+          feat[0][e] = vx[j];
+          feat[1][e] = vy[j];
+          feat[2][e] = vz[j];
+          feat[3][e] = vw[j];
+        } else if (part == 6) {
+          feat[4][e] = vx[j];
+          feat[5][e] = vy[j];
+          feat[6][e] = vz[j];
+        } else if (ridx && part == 0) {
+          ridx[e] = cur[j];
+        }
       }
     }
   }

@@ -285,23 +285,57 @@ __device__ __forceinline__ void pair_grad_all(const ViewRec& R, float qx, float 
 }
 
 // ---------------------------------------------------------------------------
+// Wave-wide scans and exchanges on the data-parallel primitives (DPP) and the
+// lane swaps, not on LDS permutes: a step of a scan is one instruction of some
+// eight cycles against more than a hundred for a permute and its wait, and
+// the one-wave phases of the compositing kernels are chains of such steps.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+
+// inclusive sum over the lanes at or before this one (every lane active)
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
+  x += dpp_u32<0x111>(x);   // row_shr 1, 2, 4, 8 (0 past the row's start)
+  x += dpp_u32<0x112>(x);
+  x += dpp_u32<0x114>(x);
+  x += dpp_u32<0x118>(x);
+  // a row's last lane to the next row (rows 1 and 3), then lane 31 to rows 2 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
+// ---------------------------------------------------------------------------
 // Transpose of the 64 x 64 bit matrix whose row r is lane r's word: bit c of
 // lane r becomes bit r of lane c.  Six butterfly steps; at step j, lanes r
 // and r ^ j exchange the j-wide column blocks that the transpose swaps.
 // ---------------------------------------------------------------------------
+// a step below a byte: w's partner word y, K the columns that stay in the
+// lane whose bit j is clear
+template <int J, uint32_t K>
+__device__ __forceinline__ uint32_t transpose_step(uint32_t w, uint32_t y, bool upper) {
+  return upper ? (w & ~K) | ((y & ~K) >> J) : (w & K) | ((y & K) << J);
+}
 __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
-  constexpr uint64_t M[6] = {0x00000000ffffffffull, 0x0000ffff0000ffffull, 0x00ff00ff00ff00ffull,
-                             0x0f0f0f0f0f0f0f0full, 0x3333333333333333ull, 0x5555555555555555ull};
   const unsigned lane = __lane_id();
+  // 32: the lower lanes' high words against the upper lanes' low words
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)(x >> 32), false, false);
+  uint32_t w[2] = {h[0], h[1]};
+  const bool b4 = lane & 16u, b3 = lane & 8u, b2 = lane & 4u, b1 = lane & 2u, b0 = lane & 1u;
+  // byte selectors of (partner, own): own bytes are 0-3, the partner's 4-7
+  const uint32_t s16 = b4 ? 0x03020706u : 0x05040100u, s8 = b3 ? 0x03070105u : 0x06020400u;
 #pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    const int j = 32 >> s;
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, j, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), j, 64);
-    const uint64_t y = ((uint64_t)hi << 32) | lo;
-    x = (lane & (unsigned)j) ? (x & ~M[s]) | ((y & ~M[s]) >> j) : (x & M[s]) | ((y & M[s]) << j);
+  for (int i = 0; i < 2; ++i) {
+    const auto p = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false);
+    w[i] = __builtin_amdgcn_perm(b4 ? p[0] : p[1], w[i], s16);
+    w[i] = __builtin_amdgcn_perm(dpp_u32<0x128>(w[i]), w[i], s8);                                   // lane ^ 8
+    w[i] = transpose_step<4, 0x0f0f0f0fu>(w[i], dpp_u32<0x1B>(dpp_u32<0x141>(w[i])), b2);           // lane ^ 4
+    w[i] = transpose_step<2, 0x33333333u>(w[i], dpp_u32<0x4E>(w[i]), b1);                           // lane ^ 2
+    w[i] = transpose_step<1, 0x55555555u>(w[i], dpp_u32<0xB1>(w[i]), b0);                           // lane ^ 1
   }
-  return x;
+  return ((uint64_t)w[1] << 32) | w[0];
 }
 
 // ---------------------------------------------------------------------------

@@ -100,6 +100,7 @@ struct ViewRec {
   uint32_t entry0;  // first tile-duplicated entry: filled into LDS copies from the records' first entries
 };
 static_assert(sizeof(ViewRec) == 128, "view record is 128 bytes");
+static_assert(offsetof(ViewRec, c) == 5 * 16 && offsetof(ViewRec, n) == 6 * 16, "features in the 16-byte parts 5 and 6");
 
 constexpr int TGRAD_STRIDE = 24;  // floats per per-entry gradient
 // A blended (entry, pixel) pair of the 8x8 multi-wave and resort-window
