@@ -431,18 +431,18 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
             R.iz[a] = 1.0f / Z[a];
             R.f[a] = T.f[a];
           }
+          float D[4];
           for (int F = 0; F < 4; ++F) {
             const int A = face_vertex(F, 0), B = face_vertex(F, 1), C = face_vertex(F, 2);
-            const float D = (px[B] - px[A]) * (py[C] - py[A]) - (py[B] - py[A]) * (px[C] - px[A]);
-            R.rD[F] = D != 0.0f ? rcp(D) : 0.0f;   // once per record, not per pixel
+            D[F] = (px[B] - px[A]) * (py[C] - py[A]) - (py[B] - py[A]) * (px[C] - px[A]);
+            R.rD[F] = D[F] != 0.0f ? rcp(D[F]) : 0.0f;   // once per record, not per pixel
           }
           R.c[0] = T.c[0]; R.c[1] = T.c[1]; R.c[2] = T.c[2];
           R.zt = zt;
           R.n[0] = T.n[0]; R.n[1] = T.n[1]; R.n[2] = T.n[2];
           R.rx = (uint32_t)i0 | ((uint32_t)i1 << 16);
           R.ry = (uint32_t)j0 | ((uint32_t)j1 << 16);
-          R.kept = kb + k;
-          R.view = v;
+          hull_spans(px, py, D, fmaxf(xmax - xmin, ymax - ymin), i0, i1, j0, j1, R.span);
           R.entry0 = 0;
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];

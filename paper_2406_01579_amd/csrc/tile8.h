@@ -107,6 +107,24 @@ __device__ __forceinline__ uint64_t rect_mask(const ViewRec& R, const Tile8& c) 
   return (row * 0x0101010101010101ull) & rows;
 }
 
+// Of those, the pixels that R's hull may cover (its spans).
+__device__ __forceinline__ uint64_t hull_mask(const ViewRec& R, const Tile8& c) {
+  int i0, i1, j0, j1;
+  unpack_rect(R, i0, i1, j0, j1);
+  const int sx = span_shift(i1 - i0 + 1, 4), sy = span_shift(j1 - j0 + 1, 3);
+  const int dx = i0 - c.tx * 8, dy = c.ty * 8 - j0;
+  uint32_t m[2] = {0u, 0u};
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    const int k = max(dy + y, 0) >> sy;   // (rows outside the rectangle are masked below)
+    const uint32_t b = (k < 4 ? R.span[0] : R.span[1]) >> (8 * (k & 3));
+    const int xa = max(dx + (int)((b & 15u) << sx), 0), xb = min(dx + (int)((((b >> 4) & 15u) + 1u) << sx), 8);
+    const uint32_t row = xa < xb ? (1u << xb) - (1u << xa) : 0u;
+    m[y >> 2] |= row << (8 * (y & 3));
+  }
+  return rect_mask(R, c) & (((uint64_t)m[1] << 32) | m[0]);
+}
+
 // Position of the k-th (from 0) set bit of m; m has more than k set bits.
 __device__ __forceinline__ int select_bit(uint64_t m, uint32_t k) {
   int pos = 0;
@@ -185,13 +203,13 @@ __device__ __forceinline__ void pair_map(int n, uint64_t m_e, PairMap<CH>& M) {
   if (lane == 63) M.total = x;
 }
 
-// Wave 0, lane e < n: entry e's pairs are the pixels of its rectangle in
+// Wave 0, lane e < n: entry e's pairs are the pixels its hull may cover, in
 // live_e (the pixels that still take part for that entry).
 template <int CH>
 __device__ __forceinline__ void chunk_pairs(const ViewRec* recs, int n, const Tile8& c, uint64_t live_e,
                                             PairMap<CH>& M) {
   const int lane = threadIdx.x & 63;
-  pair_map<CH>(n, lane < n ? rect_mask(recs[lane], c) & live_e : 0ull, M);
+  pair_map<CH>(n, lane < n ? hull_mask(recs[lane], c) & live_e : 0ull, M);
 }
 
 // All threads: f(e, pix) for every listed pair (entry e, local pixel pix),

@@ -95,8 +95,7 @@ struct ViewRec {
   float n[3];
   uint32_t rx;      // i0 | i1 << 16 (inclusive pixel columns)
   uint32_t ry;      // j0 | j1 << 16
-  int32_t kept;     // global kept slot
-  int32_t view;
+  uint32_t span[2]; // per strip of rows, the columns the hull may cover (see hull_spans)
   uint32_t entry0;  // first tile-duplicated entry: filled into LDS copies from the records' first entries
 };
 static_assert(sizeof(ViewRec) == 128, "view record is 128 bytes");
