@@ -443,22 +443,30 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
 // through App. A.1-A.2) and leaves them in an LDS row; everything it needs
 // comes with the pair (one load) and then the record and the view's
 // upstream gradient (a second).  The segments whose first pair lies in the
-// window are then summed there in a fixed order, one (segment, parameter)
-// per thread, into the segment's gradient slot (flagged as reached) or, with
-// per-record gradients, added to the record's accumulator.  Only the
-// window's last segment runs past it, by at most 63 pairs: the first wave
-// also takes the pairs after the window up to the next segment's first pair
-// (their loads in flight beside its own pair's), and skips the pairs before
-// the window's first segment, which the previous window takes.  Fixed order
-// throughout: reproducible bitwise.  (Earlier layouts: a 4-lane group per
-// segment left most lanes idle behind a wave's longest segment, 47 us at the
-// training shape; one workgroup per tile summing its segments through LDS in
-// rounds, 68 us; pairs that reached their record and tile through a segment
-// table, 55 us.)
-constexpr int PG_W = 256;          // pairs per window (one per thread)
-constexpr int PG_TAIL = 64;        // rows for the last segment's pairs past the window
+// window are then summed there in a fixed order, a segment per half wave and
+// a parameter per lane, into the segment's gradient slot (flagged as reached)
+// or, with per-record gradients, added to the record's accumulator.  Only the
+// window's last segment runs past it, by at most 63 pairs: the workgroup's
+// last wave takes the pairs after the window up to the next segment's first
+// pair, and the first wave skips the pairs before the window's first segment,
+// which the previous window takes.  Fixed order throughout: reproducible
+// bitwise.
+//   Bound by VALU issue (61% of its cycles; a pair is some 280 instructions)
+// and the pairs' own 32 bytes.  Eight waves of which one takes the tail: with
+// four, of which the first took the tail after its own pairs, a fifth of the
+// instructions worked for a few lanes and the rest waited for it.  With the
+// four faces' products shared (pair_grad_all) and the sums per half wave: 55
+// to 38 us for 1.8 M pairs, 818 to 571 us for 27 M (1.5 TB/s of pairs alone).
+// (Earlier layouts: a 4-lane group per segment left most lanes idle behind a
+// wave's longest segment, 47 us at the training shape against 48 then; one
+// workgroup per tile summing its segments through LDS in rounds, 68 us; pairs
+// that reached their record and tile through a segment table, 55 us.)
+constexpr int PG_T = 512;          // threads: one pair each
+constexpr int PG_TAIL = 64;        // the last wave: the last segment's pairs past the window
+constexpr int PG_W = PG_T - PG_TAIL;      // pairs per window
 constexpr int PG_G = TGRAD_STRIDE - 1;    // the 23 parameters (the slot's last float is padding)
 constexpr int PG_LD = PG_G;               // LDS row stride (floats), odd: conflict-free column writes
+constexpr int PG_STEP = 8;                // rows a sum reads at a time
 
 struct PairIn {
   uint4 a, b;   // the pair's two halves
@@ -494,14 +502,14 @@ __device__ __forceinline__ void pair_row(const PairIn& q, const DevView* __restr
   float gr[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) gr[k] = dout[k * plane + p];
-  float g[32];
+  float g[PG_G];
   pair_grad_all(R, (float)i + 0.5f, (float)j + 0.5f, gr, __uint_as_float(q.a.x), __uint_as_float(q.a.y),
                 __uint_as_float(q.a.z), (int)((q.a.w >> 6) & 15u), g);
 #pragma unroll
   for (int k = 0; k < PG_G; ++k) row[k] = g[k];
 }
 
-__global__ __launch_bounds__(256) void k_pair_grads(void* ws, Layout L) {
+__global__ __launch_bounds__(PG_T) void k_pair_grads(void* ws, Layout L) {
   const DevHeader* hdr = at<const DevHeader>(ws, L.o_hdr);
   const DevView* vw = at<const DevView>(ws, L.o_view);
   const float4* vrec4 = at<const float4>(ws, L.o_vrec);
@@ -512,66 +520,77 @@ __global__ __launch_bounds__(256) void k_pair_grads(void* ws, Layout L) {
   const uint32_t npair = (uint32_t)min((uint64_t)hdr->pairs_total, cap);
   const bool per_record = record_grads(L);
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-  // (32 KB of LDS in all: five workgroups per CU)
-  __shared__ float gs[PG_W + PG_TAIL][PG_LD];
-  __shared__ uint32_t hrow[PG_W];   // the window's segments: their first row | pair count << 16
-  __shared__ uint2 hseg[PG_W];      // ... record, gradient slot
-  __shared__ uint32_t wheads[PG_W / 64];
+  constexpr uint32_t NW = PG_W / 64;   // waves with window pairs; the last one takes the tail
+  // one array: the rows, then the window's segments (a sum's last step may
+  // read past its segment's rows, up to the last row and STEP - 1 more, and
+  // drops what it read there)
+  __shared__ float lds[PG_T * PG_LD + 3 * PG_W];
+  static_assert((PG_STEP - 1) * PG_LD <= 3 * PG_W, "a sum's last step stays inside the array");
+  uint32_t* hrow = reinterpret_cast<uint32_t*>(lds + PG_T * PG_LD);   // first row | pair count << 16
+  uint32_t* hrec = hrow + PG_W;                                       // record
+  uint32_t* hslot = hrec + PG_W;                                      // gradient slot
+  __shared__ uint32_t wheads[NW];
 
   for (uint32_t w0 = blockIdx.x * PG_W; w0 < npair; w0 += gridDim.x * PG_W) {
     const uint32_t pidx = w0 + threadIdx.x;
-    const bool have = pidx < npair;
     PairIn q;
     q.ok = false;
-    if (have) q = pair_load(pairs, pidx, L);
+    q.a.w = 0u;
+    if (pidx < npair) q = pair_load(pairs, pidx, L);
     const bool head = q.ok && (q.a.w & PAIR_HEAD) != 0u;
     const uint64_t hb = __ballot(head);
-    // the first wave: the pairs after the window up to the next first pair
-    // (or the end) belong to the window's last segment
-    PairIn t;
-    t.ok = false;
-    bool skip = false;
+    bool take = q.ok;
     if (wave == 0u) {
-      const uint32_t tp = pidx + PG_W;
-      if (tp < npair) t = pair_load(pairs, tp, L);
-      const uint64_t tb = __ballot(tp >= npair || (t.a.w & PAIR_HEAD) != 0u);
-      const uint32_t tn = tb ? (uint32_t)__ffsll((unsigned long long)tb) - 1u : 64u;
-      t.ok = t.ok && lane < tn;
       // pairs before the window's first segment start belong to the previous window
       const uint32_t h0 = hb ? (uint32_t)__ffsll((unsigned long long)hb) - 1u : 64u;
-      skip = lane < h0 && w0 > 0u;
+      take = take && !(lane < h0 && w0 > 0u);
+    } else if (wave == NW) {
+      // the pairs after the window up to the next first pair (or the end)
+      // belong to the window's last segment
+      const uint64_t tb = __ballot(pidx >= npair || (q.a.w & PAIR_HEAD) != 0u);
+      const uint32_t tn = tb ? (uint32_t)__ffsll((unsigned long long)tb) - 1u : 64u;
+      take = take && lane < tn;
     }
-    if (q.ok && !skip) pair_row(q, vw, vrec4, gs[threadIdx.x]);
-    if (t.ok) pair_row(t, vw, vrec4, gs[PG_W + threadIdx.x]);
-    if (lane == 0u) wheads[wave] = (uint32_t)__popcll(hb);
+    if (take) pair_row(q, vw, vrec4, lds + threadIdx.x * PG_LD);
+    if (lane == 0u && wave < NW) wheads[wave] = (uint32_t)__popcll(hb);
     __syncthreads();
-    if (head) {
-      uint32_t h = (uint32_t)__popcll(hb & ((1ull << lane) - 1ull));
-      for (uint32_t w = 0; w < wave; ++w) h += wheads[w];
-      hrow[h] = threadIdx.x | (min((q.a.w >> 11) & 127u, 64u) << 16);
-      hseg[h] = make_uint2(q.b.x, q.b.w);
-    }
-    uint32_t nh = 0u;
+    uint32_t nh = 0u, hbase = 0u;
 #pragma unroll
-    for (int w = 0; w < PG_W / 64; ++w) nh += wheads[w];
+    for (uint32_t w = 0; w < NW; ++w) {
+      hbase += w < wave ? wheads[w] : 0u;
+      nh += wheads[w];
+    }
+    if (head && wave < NW) {
+      const uint32_t h = hbase + (uint32_t)__popcll(hb & ((1ull << lane) - 1ull));
+      hrow[h] = threadIdx.x | (min((q.a.w >> 11) & 127u, 64u) << 16);
+      hrec[h] = q.b.x;
+      hslot[h] = q.b.w;
+    }
     __syncthreads();
-    for (uint32_t it = threadIdx.x; it < nh * TGRAD_STRIDE; it += PG_W) {
-      const uint32_t h = it / TGRAD_STRIDE, k = it - h * TGRAD_STRIDE;
-      const uint32_t r0 = hrow[h] & 0xffffu, cnt = k < (uint32_t)PG_G ? hrow[h] >> 16 : 0u;
-      const uint2 hs = hseg[h];
+    // a segment per half wave, a parameter per lane (24 of 32)
+    const uint32_t k = lane & 31u;
+    for (uint32_t h = 2u * wave + (lane >> 5); h < nh; h += 2u * (PG_T / 64)) {
+      if (k >= (uint32_t)TGRAD_STRIDE) continue;
+      const uint32_t rc = hrow[h], cnt = k < (uint32_t)PG_G ? rc >> 16 : 0u;
+      const float* row = lds + (rc & 0xffffu) * PG_LD + k;
       // eight rows per step, their reads in flight together (a fixed order)
       float sum = 0.0f;
-      for (uint32_t m0 = 0; m0 < cnt; m0 += 8u) {
-        float v[8];
+      for (uint32_t m0 = 0; m0 < cnt; m0 += PG_STEP) {
+        float v[PG_STEP];
 #pragma unroll
-        for (uint32_t u = 0; u < 8u; ++u) v[u] = m0 + u < cnt ? gs[r0 + m0 + u][k] : 0.0f;
+        for (uint32_t u = 0; u < PG_STEP; ++u) v[u] = row[(m0 + u) * PG_LD];
+#pragma unroll
+        for (uint32_t u = 0; u < PG_STEP; ++u) v[u] = m0 + u < cnt ? v[u] : 0.0f;
         sum += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
       }
       if (per_record) {
-        if (k < TGRAD_STRIDE - 1 && sum != 0.0f) unsafeAtomicAdd(&tgrad[(size_t)hs.x * TGRAD_STRIDE + k], sum);
-      } else if ((uint64_t)hs.y < cap) {
-        tgrad[(size_t)hs.y * TGRAD_STRIDE + k] = sum;
-        if (k == 0u) eflag[hs.y] = 1;
+        if (k < (uint32_t)PG_G && sum != 0.0f) unsafeAtomicAdd(&tgrad[(size_t)hrec[h] * TGRAD_STRIDE + k], sum);
+      } else {
+        const uint32_t d = hslot[h];
+        if ((uint64_t)d < cap) {
+          tgrad[(size_t)d * TGRAD_STRIDE + k] = sum;
+          if (k == 0u) eflag[d] = 1;
+        }
       }
     }
     __syncthreads();
@@ -582,7 +601,7 @@ hipError_t launch_pair_grads(void* ws, const Layout& L, hipStream_t st) {
   if (L.o_pairs == 0) return hipErrorInvalidValue;
   const int64_t b = (L.entry_cap + PG_W - 1) / PG_W;   // one window of pairs per block and pass
   const unsigned blocks = (unsigned)(b < 4096 ? (b > 0 ? b : 1) : 4096);
-  k_pair_grads<<<blocks, 256, 0, st>>>(ws, L);
+  k_pair_grads<<<blocks, PG_T, 0, st>>>(ws, L);
   return hipGetLastError();
 }
 

@@ -257,40 +257,6 @@ __device__ __forceinline__ int len_bucket(uint32_t len) {
 // Reverse mode of one (pixel, record) pair: the pixel's blend weight w and
 // dL/dalpha are chained to the record's 23 screen-space parameters.
 // ---------------------------------------------------------------------------
-// d f(face F) / d(record parameters) times df, added to g.  F is a
-// compile-time constant, so every index is static; the face's values (S, f)
-// are recomputed from its cross products N.
-// f = sum N_k w_k f_k / S, S = sum N_k w_k.
-template <int F, bool ZERO_SAFE = false>
-__device__ __forceinline__ void face_geom_grad(const ViewRec& R, const float (&ax)[4], const float (&ay)[4],
-                                               float N0, float N1, float N2, float df, float (&g)[32]) {
-  constexpr int A = face_vertex(F, 0), B = face_vertex(F, 1), C = face_vertex(F, 2);
-  constexpr int I[3] = {A, B, C};
-  const float N[3] = {N0, N1, N2};
-  const float qa = N0 * R.iz[A], qb = N1 * R.iz[B], qc = N2 * R.iz[C];
-  const float S = (qa + qb) + qc;
-  const float invS = ZERO_SAFE ? (df != 0.0f ? rcp(S) : 0.0f) : rcp(S);
-  const float fF = fmaf(qa, R.f[A], fmaf(qb, R.f[B], qc * R.f[C])) * invS;
-  float a[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int v = I[k];
-    const float wk = R.iz[v];
-    const float diff = (R.f[v] - fF) * invS * df;
-    g[G_F + v] = fmaf(N[k] * wk * invS, df, g[G_F + v]);   // d/df_k
-    g[G_IZ + v] = fmaf(N[k], diff, g[G_IZ + v]);            // d/dw_k
-    a[k] = wk * diff;                                       // d/dN_k
-  }
-  const float Ax = ax[A], Ay = ay[A], Bx = ax[B], By = ay[B], Cx = ax[C], Cy = ay[C];
-  // N0 = cross(B', C'), N1 = cross(C', A'), N2 = cross(A', B')
-  g[G_PX + A] += a[2] * By - a[1] * Cy;
-  g[G_PY + A] += a[1] * Cx - a[2] * Bx;
-  g[G_PX + B] += a[0] * Cy - a[2] * Ay;
-  g[G_PY + B] += a[2] * Ax - a[0] * Cx;
-  g[G_PX + C] += a[1] * Ay - a[0] * By;
-  g[G_PY + C] += a[0] * Bx - a[1] * Ax;
-}
-
 // dL/dalpha of a pair chained through Eq. 1 (stable form) to its entry and
 // exit SDF values: alpha = A / B, A = -expm1(-s d), B = 1 + exp(s f_next),
 // d = f_prev - f_next; e2 = exp(s f_next).  Zero when alpha is zero (the
@@ -312,22 +278,22 @@ __device__ __forceinline__ void eq1_chain(float da, float alpha, float e2, float
 // enter linearly), dL/df_prev = dd and dL/df_next = dfn, and the entry/exit
 // faces fs = fe | fx << 2.  Without branches: all four faces are chained, a
 // face whose weight is zero contributes exactly zero (its 1/S is taken as 0),
-// so g is updated in place and a lane with w = dd = dfn = 0 returns zeros.
-// With ACC the pair's gradient is added to g instead.
-template <bool ACC = false>
+// so a lane with w = dd = dfn = 0 returns zeros.
+//   Face F: f = sum N_k w_k f_k / S, S = sum N_k w_k, N_k = +- e_ij of its
+// other two vertices.  With U_F = dL/df / S and d_kF = (f_k - f) U_F:
+//   dL/df_k = w_k sum_F N_kF U_F, dL/dw_k = sum_F N_kF d_kF,
+//   dL/de_ij = sum over the two faces with edge ij of +- w_k d_kF,
+// and the six edge cross products e_ij = cross(P_i - p, P_j - p) carry on to
+// the vertices together (24 products for the four faces, not 24 for each).
 __device__ __forceinline__ void pair_grad_all(const ViewRec& R, float qx, float qy, const float (&gr)[8], float dd,
-                                              float dfn, float w, int fs, float (&g)[32]) {
-  if (!ACC) {
-#pragma unroll
-    for (int q = 0; q < 32; ++q) g[q] = 0.0f;
-  }
-  g[G_C + 0] = fmaf(w, gr[0], g[G_C + 0]);
-  g[G_C + 1] = fmaf(w, gr[1], g[G_C + 1]);
-  g[G_C + 2] = fmaf(w, gr[2], g[G_C + 2]);
-  g[G_ZT] = fmaf(w, gr[4], g[G_ZT]);
-  g[G_N + 0] = fmaf(w, gr[5], g[G_N + 0]);
-  g[G_N + 1] = fmaf(w, gr[6], g[G_N + 1]);
-  g[G_N + 2] = fmaf(w, gr[7], g[G_N + 2]);
+                                              float dfn, float w, int fs, float (&g)[TGRAD_STRIDE - 1]) {
+  g[G_C + 0] = w * gr[0];
+  g[G_C + 1] = w * gr[1];
+  g[G_C + 2] = w * gr[2];
+  g[G_ZT] = w * gr[4];
+  g[G_N + 0] = w * gr[5];
+  g[G_N + 1] = w * gr[6];
+  g[G_N + 2] = w * gr[7];
   const int fe = fs & 3, fx = fs >> 2;
   float ax[4], ay[4];
 #pragma unroll
@@ -335,20 +301,53 @@ __device__ __forceinline__ void pair_grad_all(const ViewRec& R, float qx, float 
     ax[k] = R.px[k] - qx;
     ay[k] = R.py[k] - qy;
   }
-  const float e01 = ax[0] * ay[1] - ay[0] * ax[1];
-  const float e02 = ax[0] * ay[2] - ay[0] * ax[2];
-  const float e03 = ax[0] * ay[3] - ay[0] * ax[3];
-  const float e12 = ax[1] * ay[2] - ay[1] * ax[2];
-  const float e13 = ax[1] * ay[3] - ay[1] * ax[3];
-  const float e23 = ax[2] * ay[3] - ay[2] * ax[3];
-  const float w0 = (fe == 0 ? dd : 0.0f) + (fx == 0 ? dfn : 0.0f);
-  const float w1 = (fe == 1 ? dd : 0.0f) + (fx == 1 ? dfn : 0.0f);
-  const float w2 = (fe == 2 ? dd : 0.0f) + (fx == 2 ? dfn : 0.0f);
-  const float w3 = (fe == 3 ? dd : 0.0f) + (fx == 3 ? dfn : 0.0f);
-  face_geom_grad<0, true>(R, ax, ay, e12, -e02, e01, w0, g);
-  face_geom_grad<1, true>(R, ax, ay, e13, -e03, e01, w1, g);
-  face_geom_grad<2, true>(R, ax, ay, e23, -e03, e02, w2, g);
-  face_geom_grad<3, true>(R, ax, ay, e23, -e13, e12, w3, g);
+  constexpr int EI[6] = {0, 0, 0, 1, 1, 2}, EJ[6] = {1, 2, 3, 2, 3, 3};
+  float e[6], de[6];
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    e[q] = ax[EI[q]] * ay[EJ[q]] - ay[EI[q]] * ax[EJ[q]];
+    de[q] = 0.0f;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g[G_F + k] = g[G_IZ + k] = 0.0f;
+#pragma unroll
+  for (int F = 0; F < 4; ++F) {
+    const int v[3] = {face_vertex(F, 0), face_vertex(F, 1), face_vertex(F, 2)};
+    // N_0 = e_12, N_1 = -e_02, N_2 = e_01 of the face's vertices in order
+    // (their indices ascend, so each is one of the six e)
+    const int q12 = v[1] == 1 ? (v[2] == 2 ? 3 : 4) : 5, q02 = v[0] == 0 ? (v[2] == 2 ? 1 : 2) : 4,
+              q01 = v[0] == 0 ? (v[1] == 1 ? 0 : 1) : 3;
+    const int q[3] = {q12, q02, q01};
+    const float N[3] = {e[q12], -e[q02], e[q01]};
+    const float wF = (fe == F ? dd : 0.0f) + (fx == F ? dfn : 0.0f);
+    const float qa = N[0] * R.iz[v[0]], qb = N[1] * R.iz[v[1]], qc = N[2] * R.iz[v[2]];
+    const float S = (qa + qb) + qc;
+    const float invS = wF != 0.0f ? rcp(S) : 0.0f;
+    const float f = fmaf(qa, R.f[v[0]], fmaf(qb, R.f[v[1]], qc * R.f[v[2]])) * invS;
+    const float U = wF * invS;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float dk = (R.f[v[k]] - f) * U;
+      g[G_F + v[k]] = fmaf(N[k], U, g[G_F + v[k]]);
+      g[G_IZ + v[k]] = fmaf(N[k], dk, g[G_IZ + v[k]]);
+      de[q[k]] = fmaf(k == 1 ? -R.iz[v[k]] : R.iz[v[k]], dk, de[q[k]]);
+    }
+  }
+  float gx[4] = {0.0f, 0.0f, 0.0f, 0.0f}, gy[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const int i = EI[q], j = EJ[q];
+    gx[i] = fmaf(de[q], ay[j], gx[i]);
+    gy[i] = fmaf(-de[q], ax[j], gy[i]);
+    gx[j] = fmaf(-de[q], ay[i], gx[j]);
+    gy[j] = fmaf(de[q], ax[i], gy[j]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    g[G_F + k] *= R.iz[k];
+    g[G_PX + k] = gx[k];
+    g[G_PY + k] = gy[k];
+  }
 }
 
 // ---------------------------------------------------------------------------
