@@ -918,25 +918,32 @@ hipError_t launch_bwd_order(void* ws, const Layout& L, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// a5b: depth order inside each tile.  The tile sort leaves every tile's
-// entries in record order (per view ascending kept slot, i.e. ascending tet
-// id); each tile is then sorted by the key (depth float bits, record), which
-// is unique and gives the (tile, depth, tet id) order of Sec. 3.3 with the
-// tie broken by tet id.  One workgroup per tile with entries, longest lists
-// first (the forward dispatch order).  The sort is a bottom-up merge sort in
-// which every element goes straight to its place in the merged pair of runs:
-// its index in its own run plus the number of keys below it in the other
-// run (a binary search; the keys are distinct), one barrier per doubling of
-// the run length.  A list of at most DS_CAP entries is sorted in LDS; a
-// longer one sorts runs of DS_CAP in LDS and merges them the same way in
-// HBM, ping-ponging between the other tile-sort buffer pair and the tile's
-// own range of the result pair (whose tile keys are rewritten at the end).
-// DS_CAP = 1024 keeps the workgroup at 16 KB of LDS (eight per CU): at the
-// training shape the lists average about 400 entries and reach about 1,100,
-// and the sort took 37 us against 43 us with 2048 (five per CU) and 45 us
-// with 512 (more lists take the HBM merge).
+// a5b: depth order inside each tile.  The tile lists hold every tile's entries
+// in no particular order; each is sorted by the key (depth float bits,
+// record), which is unique and gives the (tile, depth, tet id) order of Sec.
+// 3.3 with the tie broken by tet id (records of a view ascend with the tet
+// id).  One workgroup per tile with entries, longest lists first (the forward
+// dispatch order).
+//   A list is sorted by counting: its keys go to DS_BUCKETS buckets of equal
+// width over the list's own depth range (monotone in the depth bits), the
+// buckets are scanned, and a key's place inside its bucket is the number of
+// smaller keys there, mostly none or a few.  That is some ten LDS operations
+// per key and five barriers; the merge sort below, a binary search per key and
+// doubling, is bound by the latency of its dependent LDS reads (775 lists of
+// 295 entries on average: 17 to 7 us; 27k of 446: 218 to 121 us).
+// Lists past DS_LIST (the keys a workgroup keeps in LDS: at 20 KB eight fit a
+// CU) take the buckets in groups of at most that many keys; the merge sort's
+// runs merged in HBM made the few lists past 1,024 a tail (3.5k lists of 499, up
+// to 1,129: 37 us with the merge sort, 35 with counting up to 1,024, 19 so).
+//   Depths that agree in almost all their bits share a bucket: past DS_CROWD
+// keys in one, the list is merge sorted instead, in runs of DS_RUN keys in LDS
+// merged pairwise in HBM.
 // ---------------------------------------------------------------------------
-constexpr int DS_CAP = 1024;
+constexpr int DS_RUN = 1024;
+constexpr int DS_LIST = 2 * DS_RUN;
+constexpr int DS_BUCKETS = 1024;
+constexpr int DS_PER = DS_LIST / 256;   // keys per thread
+constexpr uint32_t DS_CROWD = 48;
 
 // Where element i (key `key`) of a run of length w goes when runs are merged
 // pairwise: `get(j)` reads the key at index j of the current array of length n.
@@ -956,13 +963,8 @@ __device__ __forceinline__ uint32_t merge_position(uint32_t i, unsigned long lon
   return (left ? lo : lo - w) + (i - lo) + (a - a0);
 }
 
-// Sort k[0, m) (m <= DS_CAP) in LDS, t as the second buffer; returns the
-// buffer that holds the result.  (Measured at the training shape: this plain
-// form, 42 us for the 3,450 lists, beat a bitonic network in LDS, 77 us, and
-// one that first sorts runs of 64 per wave in registers and then searches
-// several keys per thread together, 53 us: the sort is bound by the latency
-// of its dependent LDS reads, and the wave-level network adds a chain of
-// lane exchanges of its own.)
+// Sort k[0, m) (m <= DS_RUN) in LDS, t as the second buffer; returns the
+// buffer that holds the result.
 __device__ __forceinline__ unsigned long long* lds_merge_sort(unsigned long long* k, unsigned long long* t,
                                                               uint32_t m) {
   for (uint32_t w = 1; w < m; w <<= 1) {
@@ -976,62 +978,230 @@ __device__ __forceinline__ unsigned long long* lds_merge_sort(unsigned long long
   return k;
 }
 
-__global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L) {
-  __shared__ unsigned long long kbuf[2][DS_CAP];
-  const uint32_t n_empty = at<const uint32_t>(ws, L.o_tile_hist)[0];
-  if (blockIdx.x >= (uint32_t)L.total_tiles - n_empty) return;
-  const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
-  const uint32_t s0 = sl.start, n = sl.end - sl.start;
-  uint32_t* rk = at<uint32_t>(ws, sorted_tile_keys(L));       // result pair: tile keys, records
-  uint32_t* rv = at<uint32_t>(ws, sorted_entry_records(L));
-  // the list's tile keys (a list past DS_CAP uses them as merge scratch first
-  // and writes them at the end)
-  if (n <= (uint32_t)DS_CAP)
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) rk[s0 + i] = sl.tile;
-  if (n < 2) return;
-  const uint32_t* zkey = at<const uint32_t>(ws, L.o_key1a);   // depth bits per record
-  const bool res_a = sorted_entry_records(L) == L.o_val2a;    // scratch pair: the other buffers
-  uint32_t* xk = at<uint32_t>(ws, res_a ? L.o_key2b : L.o_key2a);
-  uint32_t* xv = at<uint32_t>(ws, res_a ? L.o_val2b : L.o_val2a);
-  // runs of DS_CAP (the whole list if it fits) sorted in LDS
-  for (uint32_t r0 = 0; r0 < n; r0 += DS_CAP) {
-    const uint32_t m = min((uint32_t)DS_CAP, n - r0);
+// The merge sort of a tile's list: records rv[0, n) by (zkey[record], record),
+// through the scratch pair xk, xv, with the tile keys rk as scratch too
+// (rewritten by the caller).
+__device__ __forceinline__ void merge_sort_list(uint32_t* rk, uint32_t* rv, uint32_t* xk, uint32_t* xv,
+                                                const uint32_t* zkey, uint32_t n, unsigned long long* lds) {
+  for (uint32_t r0 = 0; r0 < n; r0 += DS_RUN) {
+    const uint32_t m = min((uint32_t)DS_RUN, n - r0);
     for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) {
-      const uint32_t r = rv[s0 + r0 + i];
-      kbuf[0][i] = ((unsigned long long)zkey[r] << 32) | r;
+      const uint32_t r = rv[r0 + i];
+      lds[i] = ((unsigned long long)zkey[r] << 32) | r;
     }
     __syncthreads();
-    const unsigned long long* srt = lds_merge_sort(kbuf[0], kbuf[1], m);
-    if (n <= (uint32_t)DS_CAP) {
-      for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) rv[s0 + i] = (uint32_t)srt[i];
-      return;
-    }
+    const unsigned long long* srt = lds_merge_sort(lds, lds + DS_RUN, m);
     for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) {
-      xk[s0 + r0 + i] = (uint32_t)(srt[i] >> 32);
-      xv[s0 + r0 + i] = (uint32_t)srt[i];
+      xk[r0 + i] = (uint32_t)(srt[i] >> 32);
+      xv[r0 + i] = (uint32_t)srt[i];
     }
     __syncthreads();
   }
   // pairwise merges of the runs in HBM: scratch -> result pair -> scratch ...
   uint32_t *ak = xk, *av = xv, *bk = rk, *bv = rv;
-  for (uint32_t w = DS_CAP; w < n; w <<= 1) {
+  for (uint32_t w = DS_RUN; w < n; w <<= 1) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-      const unsigned long long key = ((unsigned long long)ak[s0 + i] << 32) | av[s0 + i];
+      const unsigned long long key = ((unsigned long long)ak[i] << 32) | av[i];
       const uint32_t pos = merge_position(i, key, w, n, [&](uint32_t j) {
-        return ((unsigned long long)ak[s0 + j] << 32) | av[s0 + j];
+        return ((unsigned long long)ak[j] << 32) | av[j];
       });
-      bk[s0 + pos] = (uint32_t)(key >> 32);
-      bv[s0 + pos] = (uint32_t)key;
+      bk[pos] = (uint32_t)(key >> 32);
+      bv[pos] = (uint32_t)key;
     }
     __syncthreads();
     uint32_t* t = ak; ak = bk; bk = t;
     t = av; av = bv; bv = t;
   }
-  // the sorted records into the result pair, whose tile keys are restored
-  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    if (av != rv) rv[s0 + i] = av[s0 + i];
-    rk[s0 + i] = sl.tile;
+  if (av != rv)
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) rv[i] = av[i];
+  __syncthreads();
+}
+
+struct DepthSort {
+  unsigned long long key[DS_LIST];   // the keys of the list, or of a group of its buckets
+  uint32_t cnt[DS_BUCKETS];          // per bucket its count, then its first place, then its end
+  uint32_t red[8];
+};
+
+__device__ __forceinline__ void block_min_max(uint32_t& lo, uint32_t& hi, uint32_t* red) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
   }
+  if ((threadIdx.x & 63u) == 0u) {
+    red[threadIdx.x >> 6] = lo;
+    red[4 + (threadIdx.x >> 6)] = hi;
+  }
+  __syncthreads();
+  lo = min(min(red[0], red[1]), min(red[2], red[3]));
+  hi = max(max(red[4], red[5]), max(red[6], red[7]));
+}
+
+// exclusive scan of the bucket counts in place (every thread; ends with a barrier)
+__device__ __forceinline__ void scan_buckets(DepthSort& S) {
+  constexpr int PER = DS_BUCKETS / 256;
+  const uint32_t t = threadIdx.x, wave = t >> 6;
+  uint32_t c[PER], sum = 0u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    c[i] = sum;
+    sum += S.cnt[t * PER + i];
+  }
+  const uint32_t x = wave_scan_add(sum);
+  __syncthreads();   // (red is also block_min_max's)
+  if ((t & 63u) == 63u) S.red[wave] = x;
+  __syncthreads();
+  uint32_t base = x - sum;
+  for (uint32_t w = 0; w < wave; ++w) base += S.red[w];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) S.cnt[t * PER + i] = base + c[i];
+  __syncthreads();
+}
+
+struct BucketOf {
+  uint32_t lo;
+  float scale;
+  __device__ __forceinline__ uint32_t operator()(uint32_t z) const {
+    return min((uint32_t)((float)(z - lo) * scale), (uint32_t)DS_BUCKETS - 1u);
+  }
+};
+
+// The place of a key among the list's (or group's) keys in bucket order:
+// [p0, p1) are its bucket's.
+__device__ __forceinline__ uint32_t bucket_place(const unsigned long long* k, uint32_t p0, uint32_t p1,
+                                                 unsigned long long key) {
+  uint32_t p = p0;
+  for (uint32_t j = p0; j < p1; ++j) p += k[j] < key ? 1u : 0u;
+  return p;
+}
+
+// n <= DS_LIST; false, with rv unchanged, if a bucket is crowded
+__device__ __forceinline__ bool bucket_sort_list(uint32_t* rv, const uint32_t* zkey, uint32_t n, DepthSort& S) {
+  const uint32_t t = threadIdx.x;
+  uint32_t z[DS_PER], r[DS_PER], lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    r[i] = t + 256u * i < n ? rv[t + 256u * i] : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    const bool in = t + 256u * i < n;
+    z[i] = in ? zkey[r[i]] : 0u;
+    lo = min(lo, in ? z[i] : 0xffffffffu);
+    hi = max(hi, in ? z[i] : 0u);
+  }
+  for (uint32_t i = t; i < (uint32_t)DS_BUCKETS; i += 256u) S.cnt[i] = 0u;
+  block_min_max(lo, hi, S.red);
+  const BucketOf bucket{lo, (float)DS_BUCKETS / ((float)(hi - lo) + 1.0f)};
+  uint32_t rank[DS_PER], crowd = 0u;
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    rank[i] = t + 256u * i < n ? atomicAdd(&S.cnt[bucket(z[i])], 1u) : 0u;
+    crowd = max(crowd, rank[i]);
+  }
+  if (__syncthreads_or((int)(crowd >= DS_CROWD))) return false;
+  scan_buckets(S);
+  // into bucket order (inside a bucket: whatever the atomics gave)
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    if (t + 256u * i < n) S.key[S.cnt[bucket(z[i])] + rank[i]] = ((unsigned long long)z[i] << 32) | r[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    if (t + 256u * i >= n) continue;
+    const uint32_t b = bucket(z[i]);
+    rank[i] = bucket_place(S.key, S.cnt[b], b + 1u < (uint32_t)DS_BUCKETS ? S.cnt[b + 1u] : n,
+                           ((unsigned long long)z[i] << 32) | r[i]);
+  }
+  __syncthreads();
+  // the records in order, staged in LDS and written out contiguously
+  uint32_t* out = reinterpret_cast<uint32_t*>(S.key);
+#pragma unroll
+  for (int i = 0; i < DS_PER; ++i) {
+    if (256u * i >= n) break;
+    if (t + 256u * i < n) out[rank[i]] = r[i];
+  }
+  __syncthreads();
+  for (uint32_t i = t; i < n; i += 256u) rv[i] = out[i];
+  return true;
+}
+
+// any n: the depths go to xk once, then each group of consecutive buckets
+// with at most DS_LIST keys is picked out of the list and sorted into xv
+__device__ __forceinline__ bool bucket_sort_long(uint32_t* rv, uint32_t* xk, uint32_t* xv, const uint32_t* zkey,
+                                                 uint32_t n, DepthSort& S) {
+  const uint32_t t = threadIdx.x;
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  for (uint32_t i = t; i < n; i += 256u) {
+    const uint32_t z = zkey[rv[i]];
+    xk[i] = z;
+    lo = min(lo, z);
+    hi = max(hi, z);
+  }
+  for (uint32_t i = t; i < (uint32_t)DS_BUCKETS; i += 256u) S.cnt[i] = 0u;
+  block_min_max(lo, hi, S.red);
+  const BucketOf bucket{lo, (float)DS_BUCKETS / ((float)(hi - lo) + 1.0f)};
+  uint32_t crowd = 0u;
+  for (uint32_t i = t; i < n; i += 256u) crowd = max(crowd, atomicAdd(&S.cnt[bucket(xk[i])], 1u));
+  if (__syncthreads_or((int)(crowd >= DS_CROWD))) return false;
+  scan_buckets(S);
+  for (uint32_t g0 = 0; g0 < (uint32_t)DS_BUCKETS;) {
+    // cnt still holds first places from g0 on: the group ends before the
+    // first bucket whose end is past the group's room
+    const uint32_t p0 = S.cnt[g0];
+    uint32_t a = g0 + 1u, b = (uint32_t)DS_BUCKETS;
+    while (a < b) {
+      const uint32_t mid = (a + b + 1u) >> 1;
+      if ((mid < (uint32_t)DS_BUCKETS ? S.cnt[mid] : n) - p0 <= (uint32_t)DS_LIST) a = mid;
+      else b = mid - 1u;
+    }
+    const uint32_t g1 = a;
+    __syncthreads();
+    for (uint32_t i = t; i < n; i += 256u) {
+      const uint32_t z = xk[i], q = bucket(z);
+      // (after its additions a bucket's cnt is its end, the next one's start)
+      if (q >= g0 && q < g1) S.key[atomicAdd(&S.cnt[q], 1u) - p0] = ((unsigned long long)z << 32) | rv[i];
+    }
+    __syncthreads();
+    const uint32_t m = S.cnt[g1 - 1u] - p0;
+    for (uint32_t i = t; i < m; i += 256u) {
+      const unsigned long long key = S.key[i];
+      const uint32_t q = bucket((uint32_t)(key >> 32));
+      xv[p0 + bucket_place(S.key, (q > g0 ? S.cnt[q - 1u] : p0) - p0, S.cnt[q] - p0, key)] = (uint32_t)key;
+    }
+    __syncthreads();
+    g0 = g1;
+  }
+  for (uint32_t i = t; i < n; i += 256u) rv[i] = xv[i];
+  return true;
+}
+
+__global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L) {
+  __shared__ DepthSort S;
+  static_assert(DS_LIST >= 2 * DS_RUN, "the merge sort's two LDS buffers");
+  const uint32_t n_empty = at<const uint32_t>(ws, L.o_tile_hist)[0];
+  if (blockIdx.x >= (uint32_t)L.total_tiles - n_empty) return;
+  const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
+  const uint32_t s0 = sl.start, n = sl.end - sl.start;
+  uint32_t* rk = at<uint32_t>(ws, sorted_tile_keys(L)) + s0;       // result pair: tile keys, records
+  uint32_t* rv = at<uint32_t>(ws, sorted_entry_records(L)) + s0;
+  const uint32_t* zkey = at<const uint32_t>(ws, L.o_key1a);        // depth bits per record
+  const bool res_a = sorted_entry_records(L) == L.o_val2a;         // scratch pair: the other buffers
+  uint32_t* xk = at<uint32_t>(ws, res_a ? L.o_key2b : L.o_key2a) + s0;
+  uint32_t* xv = at<uint32_t>(ws, res_a ? L.o_val2b : L.o_val2a) + s0;
+  if (n > 1u) {
+    const bool done = n <= (uint32_t)DS_LIST ? bucket_sort_list(rv, zkey, n, S)
+                                             : bucket_sort_long(rv, xk, xv, zkey, n, S);
+    if (!done) merge_sort_list(rk, rv, xk, xv, zkey, n, S.key);
+  }
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) rk[i] = sl.tile;   // the list's tile keys
 }
 
 hipError_t launch_tile_depth_sort(void* ws, const Layout& L, hipStream_t st) {
