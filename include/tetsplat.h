@@ -262,10 +262,10 @@ int render_debug_pointers(const render_scene* scenes, int n_scenes, const render
 enum {
   RENDER_STAGE_UPLOAD = 0,      /* descriptor upload (and header reset) */
   RENDER_STAGE_PREFILTER = 1,   /* alpha_max pre-filter, compaction, normals */
-  RENDER_STAGE_PROJECT = 2,     /* per-view projection and tile counts */
+  RENDER_STAGE_PROJECT = 2,     /* per-view projection and binning (entries per tile and their ranks) */
   RENDER_STAGE_DEPTH_SORT = 3,  /* depth order inside every tile's list */
-  RENDER_STAGE_SCAN = 4,        /* entry counts per record and per tile, their scans, tile lists */
-  RENDER_STAGE_EMIT = 5,        /* entries placed into the tile lists */
+  RENDER_STAGE_SCAN = 4,        /* the scan of the tiles' entry counts: tile lists */
+  RENDER_STAGE_EMIT = 5,        /* entries placed into the tile lists; the forward's dispatch order */
   RENDER_STAGE_PAIR_GRADS = 6,  /* backward: per-(entry, pixel) gradients summed per (tile, entry) */
   RENDER_STAGE_RANGES = 7,      /* dispatch orders (forward and backward) */
   RENDER_STAGE_COMPOSITE = 8,   /* forward compositing */

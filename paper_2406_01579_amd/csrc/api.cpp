@@ -191,7 +191,6 @@ bool plan_layout(const render_scene* scenes, int ns, const render_view* views, i
   L.rec_cap = rec_cap;
   L.entry_cap = entry_cap;
   L.pf_blocks = pf_blocks;
-  L.scan_blocks_rec = (rec_cap + SCAN_TILE - 1) / SCAN_TILE;
   // the radix sort is left for the deterministic backward's corner sort
   const int64_t smax = det ? 4 * kept_cap : 1;
   L.sort_blocks_max = (smax + SORT_TILE - 1) / SORT_TILE;
@@ -222,21 +221,20 @@ bool plan_layout(const render_scene* scenes, int ns, const render_view* views, i
   L.o_kept_tet = take(4 * (size_t)kept_cap);
   L.o_trec = take(sizeof(TetRec) * (size_t)kept_cap);
   L.o_vrec = take(sizeof(ViewRec) * (size_t)rec_cap);
-  L.o_rbox = take(16 * (size_t)rec_cap);
+  L.o_rbox = p->window > 0 ? take(16 * (size_t)rec_cap) : 0;
   L.o_rfirst = take(4 * (size_t)rec_cap);
   L.o_count1 = take(4 * (size_t)rec_cap);
   L.o_key1a = take(4 * (size_t)rec_cap);
-  L.o_scan_part = take(4 * (size_t)(L.scan_blocks_rec + 1));
   L.o_hist = take(4 * (size_t)(256 * L.sort_blocks_max + 256));
   L.o_key2a = take(4 * (size_t)entry_cap);
   L.o_key2b = take(4 * (size_t)entry_cap);
   L.o_val2a = take(4 * (size_t)entry_cap);
   L.o_val2b = take(4 * (size_t)entry_cap);
   L.o_eflag = take((size_t)entry_cap + 16);  // padded: the vertex backward reads aligned 8-byte words
-  L.o_tile_cnt = take(4 * (size_t)tiles);
-  L.o_tile_bsum = take(4 * (size_t)(L.tile_blocks + 1));   // right after the counts: cleared together
+  L.o_tile_cnt = take(4 * 32 * (size_t)tile_counter_row(L));
+  L.o_tile_bsum = take(4 * (size_t)(L.tile_blocks + 1));
   L.o_ranges = take(8 * (size_t)tiles);
-  L.o_tile_hist = take(4 * 2 * (size_t)TILE_BUCKETS);  // right after the ranges: cleared together
+  L.o_tile_hist = take(4 * 2 * (size_t)TILE_BUCKETS);
   L.o_tile_order = take(sizeof(TileSlot) * (size_t)tiles);
   L.o_tile_pend = take(4 * (size_t)tiles);
   L.o_bwd_hist = take(4 * (size_t)BWD_HIST_WORDS);
@@ -521,10 +519,9 @@ int render_forward(const render_scene* scenes, int n_scenes, const render_view* 
   TS_STAGE(RENDER_STAGE_PREFILTER,
            launch_desc_prefilter(hs.data(), n_scenes, hv.data(), n_views, sv.data(), workspace, L, *params, st),
            "descriptor upload and pre-filter");
-  TS_STAGE(RENDER_STAGE_PROJECT, launch_project(workspace, L, *params, st), "project");
-  TS_STAGE(RENDER_STAGE_SCAN, launch_count_scan(workspace, L, *params, st), "count scan and tile lists");
-  TS_STAGE(RENDER_STAGE_EMIT, launch_emit(workspace, L, *params, st), "emit");
-  TS_STAGE(RENDER_STAGE_RANGES, launch_tile_order(workspace, L, st), "tile order");
+  TS_STAGE(RENDER_STAGE_PROJECT, launch_project(workspace, L, *params, st), "project and bin");
+  TS_STAGE(RENDER_STAGE_SCAN, launch_tile_lists(workspace, L, st), "tile lists");
+  TS_STAGE(RENDER_STAGE_EMIT, launch_emit(workspace, L, st), "emit and tile order");
   TS_STAGE(RENDER_STAGE_DEPTH_SORT, launch_tile_depth_sort(workspace, L, st), "depth order in tiles");
   TS_STAGE(RENDER_STAGE_COMPOSITE,
            params->window > 0 ? launch_composite_win(workspace, L, with_waves(*params), st)

@@ -235,6 +235,20 @@ __global__ __launch_bounds__(PF_THREADS) void k_pf_scatter(void* ws, Layout L, f
   int32_t* kept_tet = at<int32_t>(ws, L.o_kept_tet);
   __shared__ uint32_t lds[8];
   const int b = blockIdx.x;
+  {
+    // the per-tile entry counters and the dispatch-order histograms and
+    // cursors (forward and backward) start cleared for the kernels that follow
+    uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
+    for (uint64_t i = (uint64_t)b * PF_THREADS + threadIdx.x; i < 32u * tile_counter_row(L);
+         i += (uint64_t)gridDim.x * PF_THREADS)
+      tcnt[i] = 0u;
+    if (b == 0) {
+      uint32_t* th = at<uint32_t>(ws, L.o_tile_hist);
+      for (int i = threadIdx.x; i < 2 * TILE_BUCKETS; i += PF_THREADS) th[i] = 0u;
+      uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
+      for (int i = threadIdx.x; i < BWD_HIST_WORDS; i += PF_THREADS) bh[i] = 0u;
+    }
+  }
   if (b == 0) prefilter_totals(ws, L, lds);
   if (b >= (int)L.pf_blocks) return;   // (no blocks of tets: block 0 only writes the totals)
   uint32_t part = 0;
@@ -330,9 +344,10 @@ hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, 
 }
 
 // ---------------------------------------------------------------------------
-// a2: per (view, kept tet) record: camera transform, near-plane cull,
+// a2, a3: per (view, kept tet) record: camera transform, near-plane cull,
 // projection, pixel rectangle, tile count, depth key (float32, fixed op
-// sequence), 2D face determinants, shading features.
+// sequence), 2D face determinants, shading features; then the binning of its
+// entries, one per tile that its rectangle touches.
 // ---------------------------------------------------------------------------
 // One block projects 256 consecutive kept tets of one view per step.  The
 // 96-byte tet records come in and the 128-byte view records go out through
@@ -340,11 +355,36 @@ hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, 
 // block.  A record takes 9 x 16 bytes in LDS: when each thread reads or
 // writes its own record 16 bytes at a time, sixteen neighbouring threads
 // touch 64 distinct banks.
+//   The step's entries are binned while its rectangles are in LDS.  The block
+// takes its entries' places (the records' gradient slots, contiguous per
+// record) from one global counter, and every entry its rank inside its tile's
+// list from the tile's counter; neighbouring records touch neighbouring tiles,
+// so the block's entries are counted per tile in an LDS hash first (integer
+// LDS adds are fast on this chip) and each tile costs one global atomic.  (tile, rank, record) go out per entry; once the tiles' counts are
+// scanned, an entry's place in the lists is its tile's start plus its rank.
+// The order inside a list is left to the atomics: the per-tile depth sort
+// imposes the final one.
+//   At the training shape (496k records, 1.75 M entries) this took the place of
+// a projection (27 us), a count of every tile's entries (25), the scan of the
+// counts (11), and a second pass that found every entry's tile again to place
+// it (29): now 49 us here and 10 us in k_emit; 8 x 1024^2: 142 + 91 + 114 to
+// 225 + 80 us.  Bound by the latency of a step's phases (two rounds of four
+// workgroups per CU there; LDS, 40 KB, sets the four).  Grouping a wave's
+// entries by ballots instead of the hash: 56 us, and 111 against 68 us for six
+// mixed scenes.
 constexpr int PROJ_STRIDE = 9;   // uint4 per record in LDS
+constexpr int BIN_PER = 4;       // entries per thread and binning round
+constexpr uint32_t BIN_SLOTS = 1024, BIN_PROBES = 16;
+struct BinHash {
+  uint32_t key[BIN_SLOTS];       // tile + 1; 0: free
+  uint32_t cnt[BIN_SLOTS];       // the round's entries of the tile, then the first one's rank
+};
+static_assert(sizeof(BinHash) <= 256 * PROJ_STRIDE * 16, "the hash takes the records' place in LDS");
 static_assert(sizeof(TetRec) == 6 * 16 && sizeof(ViewRec) == 8 * 16, "record sizes in 16-byte units");
+static_assert(BIN_SLOTS == 1u << 10, "the tile hash keeps 10 bits");
 
 __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2, int th_log2) {
-  const DevHeader* hdr = at<const DevHeader>(ws, L.o_hdr);
+  DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
   const DevView* vw = at<const DevView>(ws, L.o_view);
   const int32_t* kbase = at<const int32_t>(ws, L.o_scene_kept_base);
   const int32_t* kcount = at<const int32_t>(ws, L.o_scene_kept_count);
@@ -353,24 +393,20 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
   uint4* vrec4 = at<uint4>(ws, L.o_vrec);
   uint32_t* count1 = at<uint32_t>(ws, L.o_count1);
   uint32_t* key1 = at<uint32_t>(ws, L.o_key1a);
-  uint4* rbox = at<uint4>(ws, L.o_rbox);
+  uint4* rbox = L.o_rbox ? at<uint4>(ws, L.o_rbox) : nullptr;
+  uint32_t* rfirst = at<uint32_t>(ws, L.o_rfirst);
+  uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
+  uint32_t* etile = at<uint32_t>(ws, L.o_key2a);
+  uint32_t* erank = at<uint32_t>(ws, L.o_key2b);
+  uint32_t* erec = at<uint32_t>(ws, L.o_val2b);
+  const uint64_t cap = (uint64_t)L.entry_cap;
   __shared__ uint4 sbuf[256 * PROJ_STRIDE];
-  __shared__ uint32_t svalid[256];
-  {
-    // the per-tile entry counters and tile-block sums, the dispatch-order
-    // histograms and cursors (forward and backward) start cleared for the
-    // binning kernels that follow
-    const uint64_t nb = (uint64_t)gridDim.x * gridDim.y, b = (uint64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
-    const uint64_t ncnt = (L.o_tile_bsum - L.o_tile_cnt) / 4 + (uint64_t)L.tile_blocks;
-    for (uint64_t i = b * 256 + threadIdx.x; i < ncnt; i += nb * 256) tcnt[i] = 0u;
-    if (b == 0) {
-      uint32_t* th = at<uint32_t>(ws, L.o_tile_hist);
-      for (int i = threadIdx.x; i < 2 * TILE_BUCKETS; i += 256) th[i] = 0u;
-      uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
-      for (int i = threadIdx.x; i < BWD_HIST_WORDS; i += 256) bh[i] = 0u;
-    }
-  }
+  __shared__ unsigned long long svalid[4];   // bit: the record covers a pixel
+  __shared__ uint32_t loff[256];
+  __shared__ uint2 lrect[256];
+  __shared__ uint32_t lds[8];
+  __shared__ unsigned long long sbase;
+  BinHash& H = *reinterpret_cast<BinHash*>(sbuf);
   const int v = blockIdx.y;
   const DevView V = vw[v];
   const int n = kcount[V.scene];
@@ -390,7 +426,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
       for (int q = 0; q < 6; ++q) reinterpret_cast<uint4*>(&T)[q] = sbuf[t * PROJ_STRIDE + q];
     }
     __syncthreads();
-    uint32_t valid = 0;
+    uint32_t valid = 0, cnt = 0;
     if (t < nloc) {
       const int k = k0 + t;
       const int r = r0 + k;
@@ -404,7 +440,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
         Z[a] = fmaf(V.R[6], x, fmaf(V.R[7], y, fmaf(V.R[8], z, V.t[2])));
         culled |= (Z[a] < V.znear);
       }
-      uint32_t cnt = 0, key = 0xffffffffu;
+      uint32_t key = 0xffffffffu;
       if (!culled) {
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -447,19 +483,91 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];
           valid = 1;
-          // the fields the emit and vertex-backward kernels need, compact
-          rbox[r] = make_uint4(R.rx, R.ry, (uint32_t)v, 0u);
+          if (rbox) rbox[r] = make_uint4(R.rx, R.ry, 0u, 0u);   // (the window's backward)
         }
       }
       count1[r] = cnt;
       key1[r] = key;
     }
-    svalid[t] = valid;
+    uint32_t tot;
+    const uint32_t off = block_exclusive_scan_256(cnt, lds, &tot);
+    loff[t] = off;
+    if (valid) lrect[t] = make_uint2(sbuf[t * PROJ_STRIDE + 6].w, sbuf[t * PROJ_STRIDE + 7].x);
+    const uint64_t vb = __ballot(valid != 0u);
+    if ((t & 63) == 0) svalid[t >> 6] = vb;
+    // (the places' counter is not waited for before the records have gone out)
+    unsigned long long place = 0ull;
+    if (t == 0 && tot > 0u) place = atomicAdd((unsigned long long*)&hdr->entries_needed, (unsigned long long)tot);
     __syncthreads();
     // view records out, contiguous (records that cover no pixel are skipped)
     uint4* dst = vrec4 + (size_t)(r0 + k0) * 8;
     for (int q = t; q < nloc * 8; q += 256)
-      if (svalid[q >> 3]) dst[q] = sbuf[(q >> 3) * PROJ_STRIDE + (q & 7)];
+      if ((svalid[q >> 9] >> ((q >> 3) & 63)) & 1ull) dst[q] = sbuf[(q >> 3) * PROJ_STRIDE + (q & 7)];
+    if (t == 0) sbase = place;
+    __syncthreads();
+    const uint64_t base = sbase;
+    if (cnt) rfirst[r0 + k0 + t] = (uint32_t)min(base + off, (uint64_t)0xffffffffu);
+    // the binning, BIN_PER x 256 entries a round
+    for (uint32_t e0 = 0; e0 < tot; e0 += 256u * BIN_PER) {
+      __syncthreads();   // the records, or the last round's hash, are done with
+      for (uint32_t i = t; i < BIN_SLOTS; i += 256u) H.key[i] = H.cnt[i] = 0u;
+      __syncthreads();
+      uint32_t q[BIN_PER], tile[BIN_PER], rank[BIN_PER], slot[BIN_PER];
+#pragma unroll
+      for (int i = 0; i < BIN_PER; ++i) {
+        const uint32_t e = e0 + 256u * i + (uint32_t)t;
+        q[i] = tile[i] = rank[i] = 0u;
+        slot[i] = BIN_SLOTS;
+        if (e >= tot) continue;
+        // the entry's record: the last one whose first entry is at or before it
+#pragma unroll
+        for (uint32_t step = 128u; step > 0u; step >>= 1) q[i] = loff[q[i] + step] <= e ? q[i] + step : q[i];
+        const uint2 rc = lrect[q[i]];
+        const int tx0 = (int)(rc.x & 0xffffu) >> tw_log2, tx1 = (int)(rc.x >> 16) >> tw_log2;
+        const int ty0 = (int)(rc.y & 0xffffu) >> th_log2;
+        const uint32_t nx = (uint32_t)(tx1 - tx0 + 1), j = e - loff[q[i]], jy = j / nx;
+        tile[i] = (uint32_t)(V.tile_base + (ty0 + (int)jy) * V.tiles_x + tx0 + (int)(j - jy * nx));
+        uint32_t h = (tile[i] * 2654435761u) >> 22;   // 10 bits: BIN_SLOTS
+#pragma unroll 1
+        for (uint32_t p = 0; p < BIN_PROBES; ++p) {
+          uint32_t key = H.key[h];
+          if (key == 0u) {
+            key = atomicCAS(&H.key[h], 0u, tile[i] + 1u);
+            if (key == 0u) key = tile[i] + 1u;
+          }
+          if (key == tile[i] + 1u) {
+            slot[i] = h;
+            rank[i] = atomicAdd(&H.cnt[h], 1u);
+            break;
+          }
+          h = (h + 1u) & (BIN_SLOTS - 1u);
+        }
+        if (slot[i] == BIN_SLOTS) rank[i] = atomicAdd(&tcnt[tile_counter(L, tile[i])], 1u);   // no place: on its own
+      }
+      __syncthreads();
+      {
+        // the tiles' counters, a thread's atomics in flight together
+        constexpr int NS = BIN_SLOTS / 256;
+        uint32_t c[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) c[i] = H.cnt[t + 256 * i];
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          if (c[i] != 0u) c[i] = atomicAdd(&tcnt[tile_counter(L, H.key[t + 256 * i] - 1u)], c[i]);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) H.cnt[t + 256 * i] = c[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < BIN_PER; ++i) {
+        const uint32_t e = e0 + 256u * i + (uint32_t)t;
+        const uint64_t d = base + e;
+        if (e >= tot || d >= cap) continue;
+        etile[d] = tile[i];
+        erank[d] = rank[i] + (slot[i] < BIN_SLOTS ? H.cnt[slot[i]] : 0u);
+        erec[d] = (uint32_t)(r0 + k0) + q[i];
+      }
+    }
     __syncthreads();
   }
 }
@@ -472,194 +580,31 @@ hipError_t launch_project(void* ws, const Layout& L, const render_params& p, hip
 }
 
 // ---------------------------------------------------------------------------
-// a3-a5a: binning.  Records are taken in record order (per view ascending
-// kept slot, i.e. ascending tet id), SCAN_TILE at a time.  Two counts come
-// out of one pass over every record's (record, tile) entries: the entries
-// per record (their exclusive scan is each record's first entry: the slot of
-// its per-(record, tile) gradient) and the entries per tile.  The tiles'
-// exclusive scan is where each tile's list starts; the emit kernel then
-// places every entry in its tile's list through a per-tile cursor.  The
-// order inside a list is left to the atomics: the per-tile depth sort that
-// follows imposes the final order.  Entries of one wave that share a tile
-// (neighbouring records touch neighbouring tiles) are combined first, so
-// each wave issues one global atomic per distinct tile, all at once.
+// a3: the tile lists.  Each tile's list [start, end) from the exclusive scan of
+// the tiles' entry counts, and the dispatch-order histogram of their lengths.
+// Up to LISTS_DIRECT blocks of 1024 tiles every block sums the counts of the
+// tiles before its own itself (at most 256 KB from L2, some 3 us; a launch
+// costs 4.6 us); past that the blocks' sums come from a launch of their own.
+// More entries than the capacity: every list is left empty (the forward's
+// outputs are invalid then), since entries past it were not kept.
 // ---------------------------------------------------------------------------
-// The wave's lanes with `active` set, grouped by tile: returns the lane's
-// place in its group; *lead is the group's first lane and *cnt (in that lane
-// only, else 0) the group's size.  Every lane of the wave must call it.
-__device__ __forceinline__ uint32_t wave_group_by_tile(uint32_t tile, bool active, int* lead, uint32_t* cnt) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  uint64_t pending = __ballot(active);
-  uint32_t off = 0;
-  *lead = lane;
-  *cnt = 0u;
-  while (pending != 0ull) {
-    const int l0 = __ffsll((unsigned long long)pending) - 1;
-    const uint32_t t0 = (uint32_t)__shfl((int)tile, l0, 64);
-    const uint64_t m = __ballot(active && tile == t0) & pending;
-    if ((m >> lane) & 1ull) {
-      *lead = l0;
-      off = (uint32_t)__popcll(m & lt);
-    }
-    if (lane == l0) *cnt = (uint32_t)__popcll(m);
-    pending &= ~m;
-  }
-  return off;
-}
+constexpr int64_t LISTS_DIRECT = 64;
 
-// Round k of a block's entries: entry e = e0 + 256 k + threadIdx.x for every
-// thread (active if e < ne) -- its record (binary search over the block's
-// record offsets loff) and tile.
-__device__ __forceinline__ void block_entry(const uint32_t* loff, uint32_t m, uint32_t q0, uint32_t e,
-                                            const uint4* __restrict__ rbox, const DevView* __restrict__ vw,
-                                            int tw_log2, int th_log2, uint32_t& r, uint32_t& tile) {
-  int k = 0;
-#pragma unroll
-  for (int step = SCAN_TILE / 2; step > 0; step >>= 1) {
-    const int k2 = k + step;
-    k = (k2 < (int)m && loff[k2] <= e) ? k2 : k;
-  }
-  r = q0 + (uint32_t)k;
-  const uint4 bx = rbox[r];   // rectangle and view
-  const int i0 = (int)(bx.x & 0xffffu), i1 = (int)(bx.x >> 16), j0 = (int)(bx.y & 0xffffu);
-  const DevView& V = vw[bx.z];
-  const int tx0 = i0 >> tw_log2, tx1 = i1 >> tw_log2, ty0 = j0 >> th_log2;
-  const int nx = tx1 - tx0 + 1;
-  const uint32_t j = e - loff[k];
-  const int ty = ty0 + (int)(j / (uint32_t)nx), tx = tx0 + (int)(j % (uint32_t)nx);
-  tile = (uint32_t)(V.tile_base + ty * V.tiles_x + tx);
-}
-
-// records per thread of a 256-thread scan block (one, or none past the block's
-// records, when a block holds fewer than 256)
-constexpr int SCAN_PER = SCAN_TILE >= 256 ? SCAN_TILE / 256 : 1;
-static_assert(SCAN_TILE % 256 == 0 || 256 % SCAN_TILE == 0, "scan blocks of whole thread rounds");
-
-// The block's records: counts, their exclusive scan (loff) and the total.
-__device__ __forceinline__ uint32_t block_record_offsets(const uint32_t* __restrict__ count1, uint32_t q0, uint32_t m,
-                                                         uint32_t* loff, uint32_t* lds, uint32_t (&c)[SCAN_PER]) {
-  constexpr int PER = SCAN_PER;
-  const int t = threadIdx.x;
-  uint32_t sum = 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const uint32_t k = (uint32_t)(t * PER + i);
-    c[i] = k < m ? count1[q0 + k] : 0u;
-    sum += c[i];
-  }
-  uint32_t tot;
-  uint32_t run = block_exclusive_scan_256(sum, lds, &tot);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    if (t * PER + i < SCAN_TILE) loff[t * PER + i] = run;
-    run += c[i];
-  }
-  __syncthreads();
-  return tot;
-}
-
-// per SCAN_TILE records: the block's entry total, and its entries counted per
-// tile
-__global__ __launch_bounds__(256) void k_scan_reduce(void* ws, Layout L, int tw_log2, int th_log2) {
-  const DevHeader* hdr = at<const DevHeader>(ws, L.o_hdr);
-  const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* count1 = at<const uint32_t>(ws, L.o_count1);
-  const uint4* rbox = at<const uint4>(ws, L.o_rbox);
-  uint32_t* part = at<uint32_t>(ws, L.o_scan_part);
-  uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
-  __shared__ uint32_t loff[SCAN_TILE];
-  __shared__ uint32_t lds[8];
-  const uint32_t n = hdr->records_total;
-  const uint32_t q0 = blockIdx.x * SCAN_TILE;
-  if (q0 >= n) return;
-  const uint32_t m = min((uint32_t)SCAN_TILE, n - q0);
-  uint32_t c[SCAN_PER];
-  const uint32_t tot = block_record_offsets(count1, q0, m, loff, lds, c);
-  if (threadIdx.x == 0) part[blockIdx.x] = tot;
-  for (uint32_t e0 = 0; e0 < tot; e0 += 256u) {
-    const uint32_t e = e0 + threadIdx.x;
-    const bool active = e < tot;
-    uint32_t r = 0, tile = 0;
-    if (active) block_entry(loff, m, q0, e, rbox, vw, tw_log2, th_log2, r, tile);
-    int lead;
-    uint32_t cnt;
-    wave_group_by_tile(tile, active, &lead, &cnt);
-    if (cnt) atomicAdd(&tcnt[tile], cnt);
-  }
-}
-
-// per 1024 tiles: the entry total of the block's tiles (for the spine)
-__global__ __launch_bounds__(1024) void k_tile_block_sum(void* ws, Layout L) {
-  const uint32_t* tcnt = at<const uint32_t>(ws, L.o_tile_cnt);
-  uint32_t* tbsum = at<uint32_t>(ws, L.o_tile_bsum);
-  __shared__ uint32_t lds[16];
-  const uint32_t t = blockIdx.x * 1024u + threadIdx.x;
-  uint32_t x = t < (uint32_t)L.total_tiles ? tcnt[t] : 0u;
+__device__ __forceinline__ uint32_t block_sum_1024(uint32_t x, uint32_t* lds /*[16]*/) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
   if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t sum = 0;
-    for (int w = 0; w < 16; ++w) sum += lds[w];
-    tbsum[blockIdx.x] = sum;
-  }
-}
-
-// one block: exclusive scans of the record-block entry totals (the blocks'
-// first entries) and of the tile-block entry totals (the tile blocks' first
-// list places), the entry total and the capacity check
-__device__ __forceinline__ void spine_scan_1024(uint32_t* part, int nb, unsigned long long* lp,
-                                                unsigned long long* total) {
-  const int per = (nb + 1023) / 1024;
-  const int t = threadIdx.x;
-  unsigned long long sum = 0;
-  for (int i = t * per; i < min(nb, (t + 1) * per); ++i) sum += part[i];
-  lp[t] = sum;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) sum += lds[w];
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    unsigned long long v = (t >= o) ? lp[t - o] : 0ull;
-    __syncthreads();
-    lp[t] += v;
-    __syncthreads();
-  }
-  unsigned long long run = lp[t] - sum;
-  for (int i = t * per; i < min(nb, (t + 1) * per); ++i) {
-    uint32_t c = part[i];
-    part[i] = (uint32_t)run;
-    run += c;
-  }
-  *total = lp[1023];
-  __syncthreads();
+  return sum;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_spine(void* ws, Layout L) {
-  DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
-  __shared__ unsigned long long lp[1024];
-  const uint32_t n = hdr->records_total;
-  unsigned long long total, ttotal;
-  spine_scan_1024(at<uint32_t>(ws, L.o_scan_part), (int)((n + SCAN_TILE - 1) / SCAN_TILE), lp, &total);
-  spine_scan_1024(at<uint32_t>(ws, L.o_tile_bsum), (int)L.tile_blocks, lp, &ttotal);
-  if (threadIdx.x == 0) {
-    uint32_t E = total > (unsigned long long)L.entry_cap ? (uint32_t)L.entry_cap : (uint32_t)total;
-    if (total > (unsigned long long)L.entry_cap) hdr->overflow |= 2u;
-    hdr->entries_total = E;
-    hdr->entries_needed = total;
-  }
-}
-
-// per 1024 tiles: each tile's list [start, end) (clamped to the entry
-// capacity; (0, 0) when empty), its cursor (the list start, for the emit
-// kernel), and the dispatch-order histogram of the list lengths
 __device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t* lds /*[16]*/) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  const uint32_t x = wave_scan_add(v);
   if (lane == 63) lds[wave] = x;
   __syncthreads();
   uint32_t wbase = 0;
@@ -668,97 +613,61 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32
   return wbase + x - v;
 }
 
-__global__ __launch_bounds__(1024) void k_tile_lists(void* ws, Layout L) {
-  uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
-  const uint32_t* tbpre = at<const uint32_t>(ws, L.o_tile_bsum);
-  uint32_t* ranges = at<uint32_t>(ws, L.o_ranges);
+// per 1024 tiles: the entry total of the block's tiles
+__global__ __launch_bounds__(1024) void k_tile_block_sum(void* ws, Layout L) {
+  __shared__ uint32_t lds[16];
+  const uint32_t t = blockIdx.x * 1024u + threadIdx.x;
+  const uint32_t sum = block_sum_1024(
+      t < (uint32_t)L.total_tiles ? at<const uint32_t>(ws, L.o_tile_cnt)[tile_counter(L, t)] : 0u, lds);
+  if (threadIdx.x == 0) at<uint32_t>(ws, L.o_tile_bsum)[blockIdx.x] = sum;
+}
+
+__global__ __launch_bounds__(1024) void k_tile_lists(void* ws, Layout L, int direct) {
+  DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
+  const uint32_t* tcnt = at<const uint32_t>(ws, L.o_tile_cnt);
+  uint2* ranges = at<uint2>(ws, L.o_ranges);
   uint32_t* hist = at<uint32_t>(ws, L.o_tile_hist);
   __shared__ uint32_t lds[16];
   __shared__ uint32_t hb[TILE_BUCKETS];
   if (threadIdx.x < TILE_BUCKETS) hb[threadIdx.x] = 0u;
-  const uint64_t cap = (uint64_t)L.entry_cap;
+  const uint64_t total = hdr->entries_needed;
+  const bool over = total > (uint64_t)L.entry_cap;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    hdr->entries_total = over ? (uint32_t)L.entry_cap : (uint32_t)total;
+    if (over) hdr->overflow |= 2u;
+  }
+  // (without an overflow every sum below is under 2^31)
+  uint32_t before = 0u;
+  if (direct) {
+    // the tiles before 1024 b: the first 32 b counters of each of the 32 rows
+    const uint4* t4 = at<const uint4>(ws, L.o_tile_cnt);
+    const uint32_t row4 = (uint32_t)(tile_counter_row(L) / 4), n4 = blockIdx.x * 8u;
+    for (uint32_t i = threadIdx.x & 31u; i < n4; i += 32u) {
+      const uint4 c = t4[(threadIdx.x >> 5) * row4 + i];
+      before += (c.x + c.y) + (c.z + c.w);
+    }
+  } else {
+    const uint32_t* bsum = at<const uint32_t>(ws, L.o_tile_bsum);
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 1024u) before += bsum[i];
+  }
+  before = block_sum_1024(before, lds);
   const uint32_t t = blockIdx.x * 1024u + threadIdx.x;
   const bool in = t < (uint32_t)L.total_tiles;
-  const uint32_t c = in ? tcnt[t] : 0u;
-  const uint64_t start = (uint64_t)tbpre[blockIdx.x] + block_exclusive_scan_1024(c, lds);
+  const uint32_t c = in && !over ? tcnt[tile_counter(L, t)] : 0u;
+  const uint32_t start = before + block_exclusive_scan_1024(c, lds);
   if (in) {
-    uint32_t s0 = (uint32_t)min(start, cap), s1 = (uint32_t)min(start + c, cap);
-    if (s0 == s1) s0 = s1 = 0u;   // an empty list is (0, 0)
-    ranges[2 * (size_t)t] = s0;
-    ranges[2 * (size_t)t + 1] = s1;
-    tcnt[t] = (uint32_t)min(start, (uint64_t)0xffffffffu);   // the emit kernel's cursor
-    atomicAdd(&hb[len_bucket(s1 - s0)], 1u);
+    ranges[t] = c ? make_uint2(start, start + c) : make_uint2(0u, 0u);   // an empty list is (0, 0)
+    atomicAdd(&hb[len_bucket(c)], 1u);
   }
   __syncthreads();
   if (threadIdx.x < TILE_BUCKETS && hb[threadIdx.x]) atomicAdd(&hist[threadIdx.x], hb[threadIdx.x]);
 }
 
-hipError_t launch_count_scan(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
-  int twl = __builtin_ctz((unsigned)p.tile_w), thl = __builtin_ctz((unsigned)p.tile_h);
-  unsigned nb = (unsigned)L.scan_blocks_rec;
-  // per-record offsets are finished inside the emit kernel
-  k_scan_reduce<<<nb, 256, 0, st>>>(ws, L, twl, thl);
-  if (L.total_tiles > 0) k_tile_block_sum<<<(unsigned)L.tile_blocks, 1024, 0, st>>>(ws, L);
-  k_scan_spine<<<1, 1024, 0, st>>>(ws, L);
-  if (L.total_tiles > 0) k_tile_lists<<<(unsigned)L.tile_blocks, 1024, 0, st>>>(ws, L);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// a4: duplicate each record once per overlapped tile into the tile's list:
-// per SCAN_TILE records, each record's first entry into its box, then the
-// block's entries (records) placed through the per-tile cursors; places past
-// the entry capacity are dropped (the overflow is flagged).  The lists' tile
-// keys are written by the depth sort, contiguously per tile, not here, where
-// every 4-byte place is a scattered write.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_emit(void* ws, Layout L, int tw_log2, int th_log2) {
-  const DevHeader* hdr = at<const DevHeader>(ws, L.o_hdr);
-  const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* count1 = at<const uint32_t>(ws, L.o_count1);
-  const uint4* rbox = at<const uint4>(ws, L.o_rbox);
-  uint32_t* rfirst = at<uint32_t>(ws, L.o_rfirst);
-  uint32_t* cursor = at<uint32_t>(ws, L.o_tile_cnt);
-  uint32_t* val2 = at<uint32_t>(ws, sorted_entry_records(L));
-  constexpr int PER = SCAN_PER;
-  __shared__ uint32_t loff[SCAN_TILE];
-  __shared__ uint32_t lds[8];
-  const uint32_t* part = at<const uint32_t>(ws, L.o_scan_part);
-  const uint32_t n = hdr->records_total;
-  const uint64_t cap = (uint64_t)L.entry_cap;
-  const uint32_t nblk = (n + SCAN_TILE - 1) / SCAN_TILE;
-  const int t = threadIdx.x;
-  for (uint32_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const uint32_t q0 = blk * SCAN_TILE;
-    const uint32_t m = min((uint32_t)SCAN_TILE, n - q0);
-    uint32_t c[PER];
-    const uint32_t tot = block_record_offsets(count1, q0, m, loff, lds, c);
-    const uint32_t base = part[blk];
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-      if (c[i] != 0u) rfirst[q0 + (uint32_t)(t * PER + i)] = base + loff[t * PER + i];
-    for (uint32_t e0 = 0; e0 < tot; e0 += 256u) {
-      const uint32_t e = e0 + (uint32_t)t;
-      const bool active = e < tot;
-      uint32_t r = 0, tile = 0;
-      if (active) block_entry(loff, m, q0, e, rbox, vw, tw_log2, th_log2, r, tile);
-      int lead;
-      uint32_t cnt;
-      const uint32_t off = wave_group_by_tile(tile, active, &lead, &cnt);
-      uint32_t gb = cnt ? atomicAdd(&cursor[tile], cnt) : 0u;
-      gb = (uint32_t)__shfl((int)gb, lead, 64);
-      const uint64_t pos = (uint64_t)gb + off;
-      if (active && pos < cap) val2[pos] = r;
-    }
-    __syncthreads();
-  }
-}
-
-hipError_t launch_emit(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
-  int twl = __builtin_ctz((unsigned)p.tile_w), thl = __builtin_ctz((unsigned)p.tile_h);
-  // one block per SCAN_TILE records, up to 4096 (then several each)
-  const int64_t nb = L.scan_blocks_rec;
-  k_emit<<<(unsigned)(nb < 4096 ? (nb > 0 ? nb : 1) : 4096), 256, 0, st>>>(ws, L, twl, thl);
+hipError_t launch_tile_lists(void* ws, const Layout& L, hipStream_t st) {
+  if (L.total_tiles == 0) return hipSuccess;
+  const int direct = L.tile_blocks <= LISTS_DIRECT ? 1 : 0;
+  if (!direct) k_tile_block_sum<<<(unsigned)L.tile_blocks, 1024, 0, st>>>(ws, L);
+  k_tile_lists<<<(unsigned)L.tile_blocks, 1024, 0, st>>>(ws, L, direct);
   return hipGetLastError();
 }
 
@@ -787,7 +696,8 @@ __device__ __forceinline__ void bucket_first(const uint32_t* hist, uint32_t* fir
   if (t < TILE_BUCKETS) first[TILE_BUCKETS - 1 - t] = ex;
 }
 
-__global__ __launch_bounds__(256) void k_tile_scatter(void* ws, Layout L) {
+// block `blk` of the forward's dispatch order (256 tiles)
+__device__ __forceinline__ void tile_scatter_block(void* ws, const Layout& L, uint32_t blk) {
   const uint32_t* ranges = at<const uint32_t>(ws, L.o_ranges);
   const uint32_t* hist = at<const uint32_t>(ws, L.o_tile_hist);
   uint32_t* cursor = at<uint32_t>(ws, L.o_tile_hist) + TILE_BUCKETS;
@@ -801,7 +711,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(void* ws, Layout L) {
   uint32_t rank[SC_PER];
 #pragma unroll
   for (int i = 0; i < SC_PER; ++i) {
-    const uint32_t t = (blockIdx.x * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
+    const uint32_t t = (blk * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
     b[i] = 0;
     rank[i] = 0u;
     if (t < (uint32_t)L.total_tiles) {
@@ -815,7 +725,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(void* ws, Layout L) {
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < SC_PER; ++i) {
-    const uint32_t t = (blockIdx.x * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
+    const uint32_t t = (blk * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
     if (t < (uint32_t)L.total_tiles) {
       TileSlot sl;
       sl.tile = t;
@@ -827,11 +737,50 @@ __global__ __launch_bounds__(256) void k_tile_scatter(void* ws, Layout L) {
   }
 }
 
-hipError_t launch_tile_order(void* ws, const Layout& L, hipStream_t st) {
+// ---------------------------------------------------------------------------
+// a4: every entry's record into its tile's list, at the list's start plus the
+// entry's rank (a4), and the forward's dispatch order (its first blocks): two
+// independent steps after the tile lists, in one launch.
+// ---------------------------------------------------------------------------
+constexpr int EMIT_PER = 4;   // entries per thread and step
+__global__ __launch_bounds__(256) void k_emit(void* ws, Layout L, uint32_t scatter_blocks) {
+  if (blockIdx.x < scatter_blocks) {
+    tile_scatter_block(ws, L, blockIdx.x);
+    return;
+  }
+  const uint64_t total = at<const DevHeader>(ws, L.o_hdr)->entries_needed;
+  if (total > (uint64_t)L.entry_cap) return;   // the lists are empty
+  const uint32_t n = (uint32_t)total;
+  const uint2* ranges = at<const uint2>(ws, L.o_ranges);
+  const uint32_t* etile = at<const uint32_t>(ws, L.o_key2a);
+  const uint32_t* erank = at<const uint32_t>(ws, L.o_key2b);
+  const uint32_t* erec = at<const uint32_t>(ws, L.o_val2b);
+  uint32_t* list = at<uint32_t>(ws, sorted_entry_records(L));
+  const uint32_t step = 256u * EMIT_PER, blk = blockIdx.x - scatter_blocks, nblk = gridDim.x - scatter_blocks;
+  for (uint64_t d0 = (uint64_t)blk * step; d0 < n; d0 += (uint64_t)nblk * step) {
+    uint32_t tile[EMIT_PER], rank[EMIT_PER], rec[EMIT_PER], start[EMIT_PER];
+#pragma unroll
+    for (int i = 0; i < EMIT_PER; ++i) {
+      const uint64_t d = d0 + 256u * i + threadIdx.x;
+      const bool in = d < n;
+      tile[i] = in ? etile[d] : 0u;
+      rank[i] = in ? erank[d] : 0u;
+      rec[i] = in ? erec[d] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < EMIT_PER; ++i) start[i] = ranges[tile[i]].x;
+#pragma unroll
+    for (int i = 0; i < EMIT_PER; ++i)
+      if (d0 + 256u * i + threadIdx.x < n) list[start[i] + rank[i]] = rec[i];
+  }
+}
+
+hipError_t launch_emit(void* ws, const Layout& L, hipStream_t st) {
   if (L.total_tiles == 0) return hipSuccess;
-  const unsigned nb = (unsigned)((L.total_tiles + 256 * SC_PER - 1) / (256 * SC_PER));
-  // the length histogram was counted by k_tile_lists
-  k_tile_scatter<<<nb, 256, 0, st>>>(ws, L);
+  const unsigned ns = (unsigned)((L.total_tiles + 256 * SC_PER - 1) / (256 * SC_PER));
+  const int64_t nb = (L.entry_cap + 256 * EMIT_PER - 1) / (256 * EMIT_PER);
+  // (the length histogram was counted by k_tile_lists)
+  k_emit<<<ns + (unsigned)(nb < 4096 ? nb : 4096), 256, 0, st>>>(ws, L, ns);
   return hipGetLastError();
 }
 
