@@ -2,6 +2,7 @@
 // workspace layout, and the forward/backward launch sequences.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -528,8 +529,6 @@ int render_forward(const render_scene* scenes, int n_scenes, const render_view* 
            : multiwave(*params) ? launch_composite_mw(workspace, L, with_waves(*params), st)
                                 : launch_composite(workspace, L, *params, st),
            "composite");
-  // the backward's dispatch order, and the places of its per-pair terms
-  if (L.o_pairs != 0) TS_STAGE(RENDER_STAGE_RANGES, launch_bwd_order(workspace, L, st), "backward tile order");
   return RENDER_OK;
 }
 
@@ -604,11 +603,14 @@ int render_decode_status(const void* header_copy, render_status* status) {
   status->entries = h.entries_total;
   status->kept = h.kept_total;
   status->records = h.records_total;
-  status->overflow = (int32_t)h.overflow;
+  // the blended pairs go to a buffer of the entry capacity: past it the
+  // forward's outputs stand, its backward would not
+  const bool pairs_over = h.pairs_needed > (uint64_t)(h.entry_capacity > 0 ? h.entry_capacity : 0);
+  status->overflow = (int32_t)(h.overflow | (pairs_over ? 4u : 0u));
   status->invalid_index = (int32_t)h.invalid_index;
   status->entry_capacity = h.entry_capacity;
   status->kept_capacity = h.kept_capacity;
-  status->entries_needed = (int64_t)h.entries_needed;
+  status->entries_needed = (int64_t)std::max(h.entries_needed, h.pairs_needed);
   return RENDER_OK;
 }
 
@@ -620,15 +622,7 @@ int render_read_status(const void* workspace, render_status* status, void* strea
   if (e != hipSuccess) return hip_fail(e, "read status");
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "stream synchronize");
-  status->entries = h.entries_total;
-  status->kept = h.kept_total;
-  status->records = h.records_total;
-  status->overflow = (int32_t)h.overflow;
-  status->invalid_index = (int32_t)h.invalid_index;
-  status->entry_capacity = h.entry_capacity;
-  status->kept_capacity = h.kept_capacity;
-  status->entries_needed = (int64_t)h.entries_needed;
-  return RENDER_OK;
+  return render_decode_status(&h, status);
 }
 
 int render_debug_pointers(const render_scene* scenes, int n_scenes, const render_view* views, int n_views,

@@ -787,83 +787,56 @@ hipError_t launch_emit(void* ws, const Layout& L, hipStream_t st) {
 // backward order: forward slots re-bucketed by the walked length pend - start
 // (the forward compositing kernel counted every slot with pend > start; the
 // tiles with nothing walked form bucket 0, placed last, whose own count the
-// offsets never need).  On the multi-wave 8x8 path every slot also gets the
-// base of its blended pairs in the backward's pair buffer, by the same
-// bucket scheme (the forward counted them per slot and per bucket), and the
-// total is checked against the entry capacity, which bounds the pairs.
-__global__ __launch_bounds__(256) void k_bwd_scatter(void* ws, Layout L) {
+// offsets never need).  Every slot also gets the base of its blended pairs in
+// the backward's pair buffer, by the same bucket scheme (the forward counted
+// them per slot and per bucket).  256 tiles per block and step.
+__device__ __forceinline__ void bwd_scatter(void* ws, const Layout& L, uint32_t blk, uint32_t nblk) {
   const TileSlot* slots = at<const TileSlot>(ws, L.o_tile_order);
   const uint32_t* pend = at<const uint32_t>(ws, L.o_tile_pend);
+  const uint32_t* slot_pairs = at<const uint32_t>(ws, L.o_slot_pairs);
   const uint32_t* hist = at<const uint32_t>(ws, L.o_bwd_hist);
   uint32_t* cursor = at<uint32_t>(ws, L.o_bwd_hist) + TILE_BUCKETS;
+  uint32_t* pcursor = at<uint32_t>(ws, L.o_bwd_hist) + 3 * TILE_BUCKETS;
   TileSlot* bslots = at<TileSlot>(ws, L.o_bwd_order);
   uint32_t* bpend = at<uint32_t>(ws, L.o_bwd_pend);
-  const bool pairs = L.o_pairs != 0;
+  uint32_t* bbase = at<uint32_t>(ws, L.o_bwd_base);
   __shared__ uint32_t cnt[TILE_BUCKETS], base[TILE_BUCKETS], first[TILE_BUCKETS], lds[8];
   __shared__ uint32_t pcnt[TILE_BUCKETS], pbase[TILE_BUCKETS], pfirst[TILE_BUCKETS];
-  if (threadIdx.x < TILE_BUCKETS) cnt[threadIdx.x] = pcnt[threadIdx.x] = 0;
   bucket_first(hist, first, lds);
   __syncthreads();
-  if (pairs) {
-    bucket_first(hist + 2 * TILE_BUCKETS, pfirst, lds);
+  bucket_first(hist + 2 * TILE_BUCKETS, pfirst, lds);
+  __syncthreads();
+  // the slots before bucket 0 are the tiles with something walked
+  if (blk == 0 && threadIdx.x == 0) at<DevHeader>(ws, L.o_hdr)->bwd_work = first[0];
+  for (uint32_t t0 = blk * 256u; t0 < (uint32_t)L.total_tiles; t0 += nblk * 256u) {
+    if (threadIdx.x < TILE_BUCKETS) cnt[threadIdx.x] = pcnt[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t t = t0 + threadIdx.x;
+    const bool in = t < (uint32_t)L.total_tiles;
+    TileSlot sl{};
+    uint32_t pe = 0u, rank = 0u, prank = 0u;
+    int b = 0;
+    if (in) {
+      sl = slots[t];
+      pe = pend[t];
+      b = len_bucket(pe - sl.start);
+      rank = atomicAdd(&cnt[b], 1u);
+      if (pe > sl.start) prank = atomicAdd(&pcnt[b], slot_pairs[t]);
+    }
+    __syncthreads();
+    if (threadIdx.x < TILE_BUCKETS && cnt[threadIdx.x]) {
+      base[threadIdx.x] = first[threadIdx.x] + atomicAdd(&cursor[threadIdx.x], cnt[threadIdx.x]);
+      pbase[threadIdx.x] = pfirst[threadIdx.x] + atomicAdd(&pcursor[threadIdx.x], pcnt[threadIdx.x]);
+    }
+    __syncthreads();
+    if (in) {
+      const uint32_t q = base[b] + rank;
+      bslots[q] = sl;
+      bpend[q] = pe;
+      bbase[q] = pbase[b] + prank;
+    }
     __syncthreads();
   }
-  // the slots before bucket 0 are the tiles with something walked
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
-    hdr->bwd_work = first[0];
-    if (pairs) {
-      uint64_t np = 0;
-      for (int b = 0; b < TILE_BUCKETS; ++b) np += hist[2 * TILE_BUCKETS + b];
-      hdr->pairs_total = (uint32_t)min(np, (uint64_t)0xffffffffu);
-      // the capacity a backward needs covers the pairs too
-      if (np > hdr->entries_needed) hdr->entries_needed = np;
-      if (np > (uint64_t)L.entry_cap) hdr->overflow |= 4u;   // the forward's outputs stand; its backward would not
-    }
-  }
-  int b[SC_PER];
-  uint32_t rank[SC_PER], prank[SC_PER], pe[SC_PER];
-  TileSlot sl[SC_PER];
-#pragma unroll
-  for (int i = 0; i < SC_PER; ++i) {
-    const uint32_t t = (blockIdx.x * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
-    b[i] = 0;
-    rank[i] = prank[i] = pe[i] = 0u;
-    if (t < (uint32_t)L.total_tiles) {
-      sl[i] = slots[t];
-      pe[i] = pend[t];
-      b[i] = len_bucket(pe[i] - sl[i].start);
-      rank[i] = atomicAdd(&cnt[b[i]], 1u);
-      if (pairs && pe[i] > sl[i].start) prank[i] = atomicAdd(&pcnt[b[i]], at<const uint32_t>(ws, L.o_slot_pairs)[t]);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < TILE_BUCKETS && cnt[threadIdx.x]) {
-    base[threadIdx.x] = first[threadIdx.x] + atomicAdd(&cursor[threadIdx.x], cnt[threadIdx.x]);
-    if (pairs)
-      pbase[threadIdx.x] = pfirst[threadIdx.x] +
-                           atomicAdd(at<uint32_t>(ws, L.o_bwd_hist) + 3 * TILE_BUCKETS + threadIdx.x, pcnt[threadIdx.x]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < SC_PER; ++i) {
-    const uint32_t t = (blockIdx.x * SC_PER + (uint32_t)i) * 256u + threadIdx.x;
-    if (t < (uint32_t)L.total_tiles) {
-      const uint32_t q = base[b[i]] + rank[i];
-      bslots[q] = sl[i];
-      bpend[q] = pe[i];
-      if (pairs) at<uint32_t>(ws, L.o_bwd_base)[q] = pbase[b[i]] + prank[i];
-    }
-  }
-}
-
-hipError_t launch_bwd_order(void* ws, const Layout& L, hipStream_t st) {
-  if (L.total_tiles == 0) return hipSuccess;
-  const unsigned nb = (unsigned)((L.total_tiles + 256 * SC_PER - 1) / (256 * SC_PER));
-  // histograms: counted by the forward compositing kernel; cursors: cleared
-  // by the project kernel
-  k_bwd_scatter<<<nb, 256, 0, st>>>(ws, L);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1164,8 +1137,7 @@ hipError_t launch_tile_depth_sort(void* ws, const Layout& L, hipStream_t st) {
 // gradient buffers are overwritten: clear them first
 // ---------------------------------------------------------------------------
 // The scenes' gradients (row y: scene y); row 0 also clears the entry flags
-// of the last forward's entries (the backward sets the ones it reaches) and
-// the cursors of the backward dispatch order.
+// of the last forward's entries (the backward sets the ones it reaches).
 __device__ __forceinline__ void zero_grads_body(const DevScene& S, void* ws, const Layout& L) {
   const size_t n3 = 3 * (size_t)S.V;
   const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
@@ -1187,14 +1159,22 @@ __device__ __forceinline__ void zero_grads_body(const DevScene& S, void* ws, con
   }
 }
 
-__global__ void k_zero_grads(void* ws, Layout L) {
-  zero_grads_body(at<const DevScene>(ws, L.o_scene)[blockIdx.y], ws, L);
+// Row ns of the grid (where the backward goes through pairs) writes the
+// backward's dispatch order, which only needs the forward.  (In a launch of
+// its own at the end of the forward it cost 8 us at the training shape.)
+__global__ __launch_bounds__(256) void k_zero_grads(void* ws, Layout L) {
+  if (blockIdx.y == (unsigned)L.ns) bwd_scatter(ws, L, blockIdx.x, gridDim.x);
+  else zero_grads_body(at<const DevScene>(ws, L.o_scene)[blockIdx.y], ws, L);
 }
 
 // The same, taking the backward's descriptor image (scenes first) as the
 // kernel argument: row 0 also writes it to the workspace for the kernels
 // after this one, and every block reads its scene from the argument.
-__global__ void k_zero_grads_desc(Blob b, int nwords, void* ws, Layout L) {
+__global__ __launch_bounds__(256) void k_zero_grads_desc(Blob b, int nwords, void* ws, Layout L) {
+  if (blockIdx.y == (unsigned)L.ns) {
+    bwd_scatter(ws, L, blockIdx.x, gridDim.x);
+    return;
+  }
   if (blockIdx.y == 0) {
     uint32_t* dst = at<uint32_t>(ws, L.o_scene);
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += gridDim.x * blockDim.x) dst[i] = b.w[i];
@@ -1211,7 +1191,7 @@ hipError_t launch_desc_zero_grads(const DevScene* hs, int ns, const DevView* hv,
   size_t first;
   hipError_t e = desc_image(hs, ns, hv, nv, scene_views, L, false, img, first);
   if (e != hipSuccess) return e;
-  dim3 grid(256, (unsigned)L.ns);
+  dim3 grid(256, (unsigned)L.ns + (L.o_pairs != 0 && L.total_tiles > 0 ? 1u : 0u));
   const size_t words = img.size() / 4;
   if (words <= (size_t)BLOB_WORDS) {
     static_assert(alignof(DevScene) <= 16, "scenes start the image, which starts the argument");

@@ -227,7 +227,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
         uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
         const int b = len_bucket(pend - start);
         atomicAdd(bh + b, 1u);
-        if (count) atomicAdd(bh + 2 * TILE_BUCKETS + b, nblend);
+        if (count) {
+          atomicAdd(bh + 2 * TILE_BUCKETS + b, nblend);
+          atomicAdd((unsigned long long*)&at<DevHeader>(ws, L.o_hdr)->pairs_needed, (unsigned long long)nblend);
+        }
       }
     }
   }
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(PG_T) void k_pair_grads(void* ws, Layout L) {
   float* tgrad = at<float>(ws, L.o_tgrad);
   uint8_t* eflag = at<uint8_t>(ws, L.o_eflag);
   const uint64_t cap = (uint64_t)L.entry_cap;
-  const uint32_t npair = (uint32_t)min((uint64_t)hdr->pairs_total, cap);
+  const uint32_t npair = (uint32_t)min(hdr->pairs_needed, cap);
   const bool per_record = record_grads(L);
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   constexpr uint32_t NW = PG_W / 64;   // waves with window pairs; the last one takes the tail

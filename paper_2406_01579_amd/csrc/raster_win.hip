@@ -248,6 +248,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
         const int b = len_bucket(pend - start);
         atomicAdd(bh + b, 1u);
         atomicAdd(bh + 2 * TILE_BUCKETS + b, nb);
+        atomicAdd((unsigned long long*)&at<DevHeader>(ws, L.o_hdr)->pairs_needed, (unsigned long long)nb);
       }
     }
     if (c.inside) {

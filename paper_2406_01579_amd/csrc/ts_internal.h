@@ -65,8 +65,8 @@ struct DevHeader {
   int64_t entry_capacity, kept_capacity;
   uint64_t entries_needed;  // entries the last forward wanted (exact, also on overflow): the counter that
                             // the projection takes the entries' places from
-  uint32_t pairs_total;     // (entry, pixel) pairs the forward blended (multi-wave 8x8 path)
-  uint32_t pad1[49];
+  uint64_t pairs_needed;    // (entry, pixel) pairs the forward blended (multi-wave 8x8 and window paths)
+  uint32_t pad1[48];
 };
 static_assert(sizeof(DevHeader) == 256, "header is 256 bytes");
 
@@ -199,7 +199,6 @@ constexpr int TILE_BUCKETS = 129;  // tiles bucketed by list length, four bucket
 // the backward-order histogram region: slot counts, slot cursors, pair totals
 // and pair cursors (TILE_BUCKETS each)
 constexpr int BWD_HIST_WORDS = 4 * TILE_BUCKETS;
-hipError_t launch_bwd_order(void* ws, const Layout& L, hipStream_t st);
 hipError_t launch_composite(void* ws, const Layout& L, const render_params& p, hipStream_t st);
 hipError_t launch_composite_backward(void* ws, const Layout& L, const render_params& p, hipStream_t st);
 hipError_t launch_composite_mw(void* ws, const Layout& L, const render_params& p, hipStream_t st);
@@ -217,6 +216,7 @@ inline __host__ __device__ bool keeps_pixel_state(const Layout& L) { return L.o_
 // one gradient accumulator per record instead of one gradient per entry
 inline __host__ __device__ bool record_grads(const Layout& L) { return (L.flags & RENDER_RECORD_GRADS) != 0; }
 inline __host__ __device__ bool deterministic(const Layout& L) { return (L.flags & RENDER_DETERMINISTIC) != 0; }
+// descriptor upload, gradient clearing and the backward's dispatch order
 hipError_t launch_desc_zero_grads(const DevScene* hs, int ns, const DevView* hv, int nv, const int32_t* scene_views,
                                   void* ws, const Layout& L, hipStream_t st);
 

@@ -77,6 +77,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   const uint32_t nrec = hdr->records_total;
   const bool per_record = record_grads(L);
   if (DET && blockIdx.x == 0 && threadIdx.x == 0) hdr->corners_total = 4u * nk;
+  // the cursors of the backward's dispatch order, for another backward of
+  // this forward
+  if (L.o_pairs != 0 && blockIdx.x == 0 && threadIdx.x < TILE_BUCKETS) {
+    uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
+    bh[TILE_BUCKETS + threadIdx.x] = 0u;
+    bh[3 * TILE_BUCKETS + threadIdx.x] = 0u;
+  }
   const uint64_t cap = (uint64_t)L.entry_cap;
   const int q0 = (int)(threadIdx.x % P);
   const uint32_t stride = gridDim.x * (blockDim.x / P);
