@@ -222,7 +222,6 @@ bool plan_layout(const render_scene* scenes, int ns, const render_view* views, i
   L.o_kept_tet = take(4 * (size_t)kept_cap);
   L.o_trec = take(sizeof(TetRec) * (size_t)kept_cap);
   L.o_vrec = take(sizeof(ViewRec) * (size_t)rec_cap);
-  L.o_rbox = p->window > 0 ? take(16 * (size_t)rec_cap) : 0;
   L.o_rfirst = take(4 * (size_t)rec_cap);
   L.o_count1 = take(4 * (size_t)rec_cap);
   L.o_key1a = take(4 * (size_t)rec_cap);

@@ -393,7 +393,6 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
   uint4* vrec4 = at<uint4>(ws, L.o_vrec);
   uint32_t* count1 = at<uint32_t>(ws, L.o_count1);
   uint32_t* key1 = at<uint32_t>(ws, L.o_key1a);
-  uint4* rbox = L.o_rbox ? at<uint4>(ws, L.o_rbox) : nullptr;
   uint32_t* rfirst = at<uint32_t>(ws, L.o_rfirst);
   uint32_t* tcnt = at<uint32_t>(ws, L.o_tile_cnt);
   uint32_t* etile = at<uint32_t>(ws, L.o_key2a);
@@ -483,7 +482,6 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];
           valid = 1;
-          if (rbox) rbox[r] = make_uint4(R.rx, R.ry, 0u, 0u);   // (the window's backward)
         }
       }
       count1[r] = cnt;

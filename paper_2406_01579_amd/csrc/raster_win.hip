@@ -296,7 +296,6 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   const DevView* vw = at<const DevView>(ws, L.o_view);
   const uint32_t* srec = at<const uint32_t>(ws, sorted_entry_records(L));
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
-  const uint4* rbox = at<const uint4>(ws, L.o_rbox);
   const uint32_t* rfirst = at<const uint32_t>(ws, L.o_rfirst);
   uint4* blends = at<uint4>(ws, L.o_wblend);
   unsigned long long* emask = at<unsigned long long>(ws, L.o_wmask);
@@ -469,12 +468,10 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
     uint32_t d = 0u, cnt = 0u;
     if (idx < end) {
       const uint32_t r = srec[idx];
-      const uint4 bx = rbox[r];   // pixel rectangle, view
-      const int i0 = (int)(bx.x & 0xffffu), i1 = (int)(bx.x >> 16), j0 = (int)(bx.y & 0xffffu),
-                j1 = (int)(bx.y >> 16);
+      int i0, i1, j0, j1;
+      unpack_rect(vrec[r], i0, i1, j0, j1);
       const int tx0 = i0 >> 3, ty0 = j0 >> 3, nx = (i1 >> 3) - tx0 + 1;
       d = rfirst[r] + (uint32_t)((c.ty - ty0) * nx + (c.tx - tx0));
-      (void)j1;
       cnt = (uint64_t)d < cap ? (uint32_t)__popcll(mask_load(emask + d)) : 0u;
     }
     uint32_t x = cnt;

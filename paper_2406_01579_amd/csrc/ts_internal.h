@@ -134,7 +134,6 @@ struct Layout {
   size_t o_pf_cnt, o_kept_tet, o_trec;
   size_t o_pf_keep;   // pre-filter decisions, one bit per tet (PF_TILE / 32 words per block)
   size_t o_vrec, o_count1, o_key1a;   // key1a: depth float bits per record
-  size_t o_rbox;   // resort window only: per record its pixel rectangle (rx, ry; 16 B)
   size_t o_rfirst; // per record: its first entry (4 B, dense)
   size_t o_hist;
   size_t o_key2a, o_key2b, o_val2a, o_val2b, o_eflag;
