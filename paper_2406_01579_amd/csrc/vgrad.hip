@@ -9,10 +9,10 @@
 // n = g/|g| (App. A.3, as the equivalent 3x3 edge system g = E^-1 (f_k - f_0))
 // and the mean colour -- and adds the result to the per-vertex gradients
 // (combined per block in LDS, then float atomics).  A record's loads form
-// short dependent rounds (its compact box with the first entry, then its
-// entry flags, then the flagged entries; 1/Z is recomputed from the tet's
-// vertices with the projection's operations), and the views of a tet are in
-// flight together.
+// short dependent rounds (its first entry and their number, then its entry
+// flags, then the flagged entries; 1/Z is recomputed from the tet's vertices
+// with the projection's operations), and the views of a tet are in flight
+// together.
 #include "ts_device.h"
 
 namespace ts {
@@ -31,35 +31,54 @@ __device__ __forceinline__ int scene_of_kept(const int32_t* kbase, int ns, uint3
   return lo;
 }
 
-// sum over aligned groups of P lanes (P a power of two <= 64)
+// sum over aligned groups of P lanes (P a power of two <= 8; DPP: lane ^ 1,
+// lane ^ 2, and the half-row mirror, which pairs a quad's equal sums with the
+// other quad's)
 template <int P>
 __device__ __forceinline__ float group_sum(float x) {
-#pragma unroll
-  for (int o = 1; o < P; o <<= 1) x += __shfl_xor(x, o, 64);
+  static_assert(P <= 8, "within half a DPP row");
+  if (P > 1) x += __uint_as_float(dpp_u32<0xB1>(__float_as_uint(x)));
+  if (P > 2) x += __uint_as_float(dpp_u32<0x4E>(__float_as_uint(x)));
+  if (P > 4) x += __uint_as_float(dpp_u32<0x141>(__float_as_uint(x)));
   return x;
 }
 
-// Per-block combine of the vertex gradients: tets that share a vertex
-// (every vertex of a tetrahedral grid belongs to many tets, and neighbouring
-// kept slots are neighbouring tets) add into one LDS slot, keyed by vertex
-// id, and each slot is added to HBM once per block.  Open addressing with a
-// bounded probe; a vertex that finds no slot, or a tet of another scene than
-// the block's first, adds to HBM directly.
-constexpr int VB_HASH = 512;
-constexpr int VB_PROBES = 16;
-static_assert(VB_HASH == 1 << 9, "the slot hash keeps 9 bits");
+// Per-block combine of the vertex gradients: tets that share a vertex (every
+// vertex of a tetrahedral grid belongs to many tets, and neighbouring kept
+// slots are neighbouring tets) add into one LDS slot, and each slot is added
+// to HBM once per block.  Slots are runs of VB_RUN consecutive vertices, found
+// by hashing the run's number (open addressing, bounded probe), so that a
+// run's sums go out at consecutive addresses; a vertex that finds no slot, or
+// a tet of another scene than the block's first, adds to HBM directly.
+//   A block takes several rounds of tets before it adds its sums, while the
+// blocks still fill the chip: scattered atomics run at some 21 G/s, and with
+// one round of 256 threads per flush they were a third of the kernel.  Now
+// the flush is 3 of 36 us at the training shape (4 x 512^2), 13 of 214 at
+// 8 x 1024^2 and 9 of 121 for six mixed scenes (before: 43, 292 and 136); what
+// is left waits for the records' three dependent rounds of loads, at four waves
+// per SIMD.  Larger tables and blocks lose more waves to LDS than they save
+// atomics: 128 runs 38 / 219 / 165 us, 512 tets a block 36 / 219 / 168.
+constexpr int VB_T = 512;        // threads (the deterministic form, which sums nothing in LDS: 256)
+constexpr int VB_RUN = 8;
+constexpr int VB_GROUPS = 64;
+constexpr int VB_HASH = VB_GROUPS * VB_RUN;
+constexpr int VB_PROBES = 8;
+constexpr uint32_t VB_FILL = 1024;   // blocks that fill the chip
+constexpr uint32_t VB_TETS = 256;    // tets per block at most, where it takes several rounds of them
+static_assert(VB_GROUPS == 1 << 6, "the run hash keeps 6 bits");
 
 // With DET the per-vertex terms of every kept tet's four corners are written
 // out (with the corner's global vertex id as a sort key) instead of being
 // combined, and k_vertex_gather adds them in a fixed order.
 // A 4-waves-per-SIMD target (at most 128 VGPRs): at 5 the kernel fits 96
 // VGPRs only by spilling a dozen values to scratch inside its loops, and
-// took 61 us against 52 us at the training shape.
+// was slower at the training shape.
 template <int P, bool DET>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_vertex_bwd(void* ws, Layout L) {
-  __shared__ uint32_t hkey[DET ? 1 : VB_HASH];   // vertex id + 1; 0: empty
+__global__ __launch_bounds__(DET ? 256 : VB_T) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_vertex_bwd(void* ws, Layout L) {
+  constexpr int NT = DET ? 256 : VB_T;
+  __shared__ uint32_t hkey[DET ? 1 : VB_GROUPS];   // run number + 1; 0: free
   // doubles: an LDS add of a double takes 9 cycles per wave and CU, one of a
-  // float 194 (the kernel: 46.5 to 43.2 us at the training shape)
+  // float 194
   __shared__ double hval[7][DET ? 1 : VB_HASH];  // dverts xyz, dsdf, dcolors xyz
   __shared__ int bscene;
   DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
@@ -86,22 +105,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   }
   const uint64_t cap = (uint64_t)L.entry_cap;
   const int q0 = (int)(threadIdx.x % P);
-  const uint32_t stride = gridDim.x * (blockDim.x / P);
-  // the loop runs the same number of times in every lane of a group
-  for (uint32_t k = (blockIdx.x * blockDim.x + threadIdx.x) / P; k < nk + (stride - nk % stride) % stride;
-       k += stride) {
+  constexpr uint32_t TPR = NT / P;   // tets per round
+  // rounds per block: while the blocks fill the chip
+  const uint32_t rounds = DET ? 1u : min(max(VB_TETS / TPR, 1u), max(nk / (TPR * VB_FILL), 1u));
+  const uint32_t per = rounds * TPR;
+  for (uint32_t kb = blockIdx.x * per; kb < nk; kb += gridDim.x * per) {
+    if constexpr (!DET) {
+      for (int h = threadIdx.x; h < VB_GROUPS; h += NT) hkey[h] = 0u;
+      for (int h = threadIdx.x; h < 7 * VB_HASH; h += NT) (&hval[0][0])[h] = 0.0;
+      if (threadIdx.x == 0) bscene = scene_of_kept(kbase, L.ns, kb);
+      __syncthreads();
+    }
+    for (uint32_t rd = 0; rd < rounds; ++rd) {
+    const uint32_t k = kb + rd * TPR + threadIdx.x / P;
     const bool tet_ok = k < nk;
     const TetRec& T = trec[tet_ok ? k : 0u];
     const int ks = tet_ok ? scene_of_kept(kbase, L.ns, k) : 0;
-    if constexpr (!DET) {
-      for (int h = threadIdx.x; h < VB_HASH; h += blockDim.x) {
-        hkey[h] = 0u;
-#pragma unroll
-        for (int m = 0; m < 7; ++m) hval[m][h] = 0.0;
-      }
-      if (threadIdx.x == 0) bscene = tet_ok ? ks : -1;   // thread 0 holds the block's first tet
-      __syncthreads();
-    }
     float dv[4][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
     float dfv[4] = {0, 0, 0, 0}, dn[3] = {0, 0, 0}, dc[3] = {0, 0, 0};
     bool any = false;
@@ -280,17 +299,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       const float val[7] = {dv[a][0], dv[a][1], dv[a][2], dfv[a], 0.25f * dc[0], 0.25f * dc[1], 0.25f * dc[2]};
       bool put = false;
       if (ks == bscene) {
-        uint32_t h = (vv * 2654435761u) >> 23;   // 9 bits: VB_HASH slots
+        const uint32_t run = vv / VB_RUN + 1u;
+        uint32_t h = (run * 2654435761u) >> 26;   // 6 bits: VB_GROUPS
+#pragma unroll 1
         for (int probe = 0; probe < VB_PROBES; ++probe) {
-          const uint32_t old = atomicCAS(&hkey[h], 0u, vv + 1u);
-          if (old == 0u || old == vv + 1u) {
+          uint32_t old = hkey[h];
+          if (old == 0u) {
+            old = atomicCAS(&hkey[h], 0u, run);
+            if (old == 0u) old = run;
+          }
+          if (old == run) {
+            const uint32_t sl = h * VB_RUN + vv % VB_RUN;
 #pragma unroll
             for (int m = 0; m < 7; ++m)
-              if (val[m] != 0.0f) unsafeAtomicAdd(&hval[m][h], (double)val[m]);
+              if (val[m] != 0.0f) unsafeAtomicAdd(&hval[m][sl], (double)val[m]);
             put = true;
             break;
           }
-          h = (h + 1u) & (VB_HASH - 1u);
+          h = (h + 1u) & (VB_GROUPS - 1u);
         }
       }
       if (!put) {
@@ -302,21 +328,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       }
     }
     }
+    }
     if constexpr (DET) continue;
     __syncthreads();
-    if (bscene >= 0) {
+    {
       const DevScene& S = sc[bscene];
-      for (int h = threadIdx.x; h < VB_HASH; h += blockDim.x) {
-        const uint32_t key = hkey[h];
-        if (key == 0u) continue;
-        const size_t vv = (size_t)(key - 1u);
-        for (int m = 0; m < 3; ++m) {
-          const float x = (float)hval[m][h], c = (float)hval[4 + m][h];
-          if (x != 0.0f) gatomic_add(&S.dverts[3 * vv + m], x);
-          if (c != 0.0f) gatomic_add(&S.dcolors[3 * vv + m], c);
-        }
-        const float f = (float)hval[3][h];
-        if (f != 0.0f) gatomic_add(&S.dsdf[vv], f);
+      // a run's sums at consecutive addresses: positions, colours, SDF
+      for (int q = threadIdx.x; q < 3 * VB_HASH; q += NT) {
+        const int h = q / (3 * VB_RUN), r = q - h * (3 * VB_RUN);
+        const uint32_t run = hkey[h];
+        if (run == 0u) continue;
+        const size_t o = (size_t)(run - 1u) * (3 * VB_RUN) + r;
+        const float x = (float)hval[r % 3][h * VB_RUN + r / 3], c = (float)hval[4 + r % 3][h * VB_RUN + r / 3];
+        if (x != 0.0f) gatomic_add(&S.dverts[o], x);
+        if (c != 0.0f) gatomic_add(&S.dcolors[o], c);
+      }
+      for (int q = threadIdx.x; q < VB_HASH; q += NT) {
+        const uint32_t run = hkey[q / VB_RUN];
+        const float f = run != 0u ? (float)hval[3][q] : 0.0f;
+        if (f != 0.0f) gatomic_add(&S.dsdf[(size_t)(run - 1u) * VB_RUN + q % VB_RUN], f);
       }
     }
     __syncthreads();
@@ -325,10 +355,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 
 template <bool DET>
 static void launch_vbwd(void* ws, const Layout& L, unsigned blocks, int nvs, hipStream_t st) {
-  if (nvs <= 1) k_vertex_bwd<1, DET><<<blocks, 256, 0, st>>>(ws, L);
-  else if (nvs <= 2) k_vertex_bwd<2, DET><<<blocks, 256, 0, st>>>(ws, L);
-  else if (nvs <= 4) k_vertex_bwd<4, DET><<<blocks, 256, 0, st>>>(ws, L);
-  else k_vertex_bwd<8, DET><<<blocks, 256, 0, st>>>(ws, L);
+  if (nvs <= 1) k_vertex_bwd<1, DET><<<blocks, DET ? 256 : VB_T, 0, st>>>(ws, L);
+  else if (nvs <= 2) k_vertex_bwd<2, DET><<<blocks, DET ? 256 : VB_T, 0, st>>>(ws, L);
+  else if (nvs <= 4) k_vertex_bwd<4, DET><<<blocks, DET ? 256 : VB_T, 0, st>>>(ws, L);
+  else k_vertex_bwd<8, DET><<<blocks, DET ? 256 : VB_T, 0, st>>>(ws, L);
 }
 
 hipError_t launch_vertex_backward(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
@@ -336,7 +366,8 @@ hipError_t launch_vertex_backward(void* ws, const Layout& L, const render_params
   // lanes per tet: the largest view count of a scene, rounded up to a power of two (at most 8)
   const int nvs = L.max_scene_views;
   const int64_t threads = L.kept_cap * (nvs <= 1 ? 1 : nvs <= 2 ? 2 : nvs <= 4 ? 4 : 8);
-  const int64_t b = (threads + 255) / 256;
+  const int nt = deterministic(L) ? 256 : VB_T;
+  const int64_t b = (threads + nt - 1) / nt;
   const unsigned blocks = (unsigned)(b < 8192 ? (b > 0 ? b : 1) : 8192);
   if (deterministic(L)) launch_vbwd<true>(ws, L, blocks, nvs, st);
   else launch_vbwd<false>(ws, L, blocks, nvs, st);
