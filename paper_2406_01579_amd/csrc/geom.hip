@@ -15,17 +15,17 @@
 // block, so the losses do not depend on scheduling except through the float
 // atomics that build m.
 //
-// The unique-edge list is built once per topology: the six (a < b) pairs of
-// every tet are sorted by b and then stably by a with the LSD radix sort, and
-// a flag/scan/scatter pass keeps the first of each run.
+// The unique-edge list is built once per topology: the (a < b) pairs of every
+// tet, freed of most repeats in LDS, are binned by a, and each vertex's bucket
+// is sorted and freed of the rest.
 //
-// Marching Tetrahedra (the mesh extraction of Sec. 4.1): a flag/scan/scatter
-// pass over the edges places one surface vertex on every edge whose ends
-// differ in the inside test (f < 0), numbered in edge order; a second one
-// over the tets writes one triangle (one or three inside vertices) or two
-// (two inside) in tet order, looking the crossed edges up in the sorted edge
-// list by binary search.  The winding is fixed by a 16-entry case table built
-// at compile time (outward normals, flipped for negatively oriented tets).
+// Marching Tetrahedra (the mesh extraction of Sec. 4.1): a mark/scan/write
+// sequence over the edges places one surface vertex on every edge whose ends
+// differ in the inside test (f < 0), numbered in edge order; one over the tets
+// writes one triangle (one or three inside vertices) or two (two inside) in
+// tet order, looking the crossed edges up in the sorted edge list.  The
+// winding is fixed by a 16-entry case table built at compile time (outward
+// normals, flipped for negatively oriented tets).
 #include <algorithm>
 
 #include "ts_device.h"
@@ -184,7 +184,8 @@ __global__ __launch_bounds__(RT) void k_edge_count(const int32_t* tets, uint32_t
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void k_edge_spine(uint32_t* bsum, uint32_t nb, int32_t* n_edges) {
+// one block of 1024: exclusive scan of nb block sums in place, and their total
+__device__ __forceinline__ void spine_1024(uint32_t* bsum, uint32_t nb, int32_t* n_edges) {
   __shared__ uint32_t part[16];
   const uint32_t t = threadIdx.x;
   const uint32_t per = (nb + 1023) / 1024;
@@ -214,6 +215,10 @@ __global__ __launch_bounds__(1024) void k_edge_spine(uint32_t* bsum, uint32_t nb
   if (t == 0) n_edges[0] = (int32_t)tot;
 }
 
+__global__ __launch_bounds__(1024) void k_edge_spine(uint32_t* bsum, uint32_t nb, int32_t* n_edges) {
+  spine_1024(bsum, nb, n_edges);
+}
+
 __global__ __launch_bounds__(RT) void k_edge_write(const int32_t* tets, uint32_t n, int32_t V, const uint32_t* idx,
                                                    const uint32_t* bsum, int32_t* edges) {
   __shared__ uint32_t lds[RT / 64];
@@ -228,22 +233,6 @@ __global__ __launch_bounds__(RT) void k_edge_write(const int32_t* tets, uint32_t
       reinterpret_cast<int2*>(edges)[o] = make_int2((int32_t)ab[t][0], (int32_t)ab[t][1]);
       ++o;
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// regularisers
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(RT) void k_fill_f32(float* p, size_t n, float v) {
-  for (size_t i = blockIdx.x * (size_t)RT + threadIdx.x; i < n; i += (size_t)gridDim.x * RT) p[i] = v;
-}
-
-// the three accumulators of the gradient pass, cleared in one launch
-__global__ __launch_bounds__(RT) void k_reg_clear(float* dm, float* dverts, float* dsdf, size_t V) {
-  for (size_t i = blockIdx.x * (size_t)RT + threadIdx.x; i < 3 * V; i += (size_t)gridDim.x * RT) {
-    dm[i] = 0.0f;
-    dverts[i] = 0.0f;
-    if (i < V) dsdf[i] = 0.0f;
   }
 }
 
@@ -280,22 +269,26 @@ __device__ __forceinline__ void vs_clear(VertexSums<C>& S) {
   for (int i = threadIdx.x; i < C * VS_GROUPS * VS_RUN; i += VS_T) (&S.val[0][0])[i] = 0.0;
 }
 
-// the place of vertex v's sums, -1 if its group finds none
-template <int C>
-__device__ __forceinline__ int vs_place(VertexSums<C>& S, uint32_t v) {
+// the place of vertex v's sums under the group keys, -1 if its group finds none
+__device__ __forceinline__ int group_place(uint32_t* key, uint32_t v) {
   const uint32_t g = v / VS_RUN + 1u;
   uint32_t h = (g * 2654435761u) >> 25;
 #pragma unroll 1
   for (int p = 0; p < VS_PROBES; ++p) {
-    uint32_t k = S.key[h];
+    uint32_t k = key[h];
     if (k == 0u) {
-      k = atomicCAS(&S.key[h], 0u, g);
+      k = atomicCAS(&key[h], 0u, g);
       if (k == 0u) k = g;
     }
     if (k == g) return (int)(h * VS_RUN + v % VS_RUN);
     h = (h + 1u) & (VS_GROUPS - 1u);
   }
   return -1;
+}
+
+template <int C>
+__device__ __forceinline__ int vs_place(VertexSums<C>& S, uint32_t v) {
+  return group_place(S.key, v);
 }
 
 // component c of vertex v's sum, N components per vertex in out
@@ -331,6 +324,320 @@ __device__ __forceinline__ uint32_t xcd_chunk(uint32_t j, uint32_t nchunks) {
 // one cell all share two; LDS adds to one address wait for each other).
 __device__ __forceinline__ uint32_t vs_item() {
   return (threadIdx.x & 63u) * (VS_T / 64) + (threadIdx.x >> 6);
+}
+
+// ---------------------------------------------------------------------------
+// unique edges, binned by their lower vertex.  A chunk of tets puts its pairs
+// into an LDS set first (neighbouring tets share most of their edges: the
+// 3072 pairs of 512 tets of a cube grid are some 1,400 different ones), and
+// each different pair takes a rank among its lower vertex's pairs, from LDS
+// counters whose totals go to the vertices' counters in runs of 16.  The
+// counts' scan gives every vertex a bucket, the pairs' upper vertices are
+// placed there, and each bucket is sorted and freed of the repeats that other
+// chunks brought (ranks by comparison; some 13 entries a bucket).  The sort of
+// all 6 K pairs by both vertices, which this replaces where the vertex arrays
+// fit the workspace (V <= 4 K, as when every vertex belongs to a tet), read and
+// wrote them six times: 870 us at 1.57 M tets, 230 us so.
+// ---------------------------------------------------------------------------
+constexpr int EB_T = 512;             // threads
+constexpr uint32_t EB_CHUNK = 512;    // tets per chunk
+constexpr uint32_t EB_SET = 2048;     // slots of the pair set
+constexpr int EB_PROBES = 32;
+constexpr uint64_t EB_FREE = ~0ull;
+constexpr uint32_t EB_GONE = ~0u;     // a slot whose pair went out on its own
+
+struct PairSet {
+  unsigned long long pair[EB_SET];                   // a << 32 | b
+  uint32_t where[EB_SET];                            // vertex place << 16 | rank among the chunk's pairs of a
+  uint32_t vkey[VS_GROUPS];                          // groups of 16 lower vertices, as in VertexSums
+  uint32_t vcnt[VS_GROUPS * VS_RUN];                 // pairs per vertex, then the first one's rank
+  uint32_t nitem, base;
+};
+
+__global__ __launch_bounds__(RT) void k_edge_clear(uint32_t* cnt, uint32_t n, uint32_t* n_item) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *n_item = 0u;
+  for (uint32_t i = blockIdx.x * RT + threadIdx.x; i < n; i += gridDim.x * RT) cnt[i] = 0u;
+}
+
+// cnt[V + 1]: pairs per lower vertex (cleared); n_item: pairs listed (cleared)
+__global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t K, int32_t V, uint32_t* cnt,
+                                                   uint32_t* n_item, uint32_t* la, uint32_t* lb, uint32_t* lr) {
+  __shared__ PairSet S;
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t nchunks = (K + EB_CHUNK - 1u) / EB_CHUNK, nj = (nchunks + 7u) / 8u * 8u;
+  for (uint32_t j = blockIdx.x; j < nj; j += gridDim.x) {
+    const uint32_t ch = xcd_chunk(j, nchunks);
+    if (ch >= nchunks) continue;
+    for (uint32_t i = t; i < EB_SET; i += EB_T) S.pair[i] = EB_FREE;
+    for (uint32_t i = t; i < VS_GROUPS; i += EB_T) S.vkey[i] = 0u;
+    for (uint32_t i = t; i < VS_GROUPS * VS_RUN; i += EB_T) S.vcnt[i] = 0u;
+    if (t == 0u) S.nitem = 0u;
+    __syncthreads();
+    const uint32_t k1 = min(K, (ch + 1u) * EB_CHUNK);
+    for (uint32_t k = ch * EB_CHUNK + vs_item(); k < k1; k += EB_T) {
+      int32_t v[4];
+      if (!load_tet(tets, k, V, v)) continue;
+#pragma unroll
+      for (int e = 0; e < 6; ++e) {
+        const int p = e < 3 ? 0 : (e < 5 ? 1 : 2), q = e == 0 ? 1 : (e == 1 || e == 3) ? 2 : 3;
+        const uint32_t a = (uint32_t)min(v[p], v[q]), b = (uint32_t)max(v[p], v[q]);
+        const uint64_t key = (uint64_t)a << 32 | b;
+        uint32_t h = (a * 2654435761u ^ b * 2246822519u) >> 21;   // 11 bits: EB_SET
+        bool mine = true;   // no slot found: the pair goes out on its own
+        uint32_t slot = EB_SET;
+#pragma unroll 1
+        for (int pr = 0; pr < EB_PROBES; ++pr) {
+          unsigned long long old = S.pair[h];
+          if (old == EB_FREE) {
+            old = atomicCAS(&S.pair[h], EB_FREE, key);
+            if (old == EB_FREE) {
+              slot = h;
+              break;
+            }
+          }
+          if (old == key) {
+            mine = false;
+            break;
+          }
+          h = (h + 1u) & (EB_SET - 1u);
+        }
+        if (!mine) continue;
+        const int place = slot < EB_SET ? group_place(S.vkey, a) : -1;
+        if (place >= 0) {
+          S.where[slot] = (uint32_t)place << 16 | atomicAdd(&S.vcnt[place], 1u);
+        } else {
+          if (slot < EB_SET) S.where[slot] = EB_GONE;
+          const uint32_t i = atomicAdd(n_item, 1u);
+          la[i] = a;
+          lb[i] = b;
+          lr[i] = atomicAdd(&cnt[a], 1u);
+        }
+      }
+    }
+    __syncthreads();
+    // the vertices' counters, a group's 16 at consecutive addresses
+    {
+      constexpr int NV = VS_GROUPS * VS_RUN / EB_T;   // a thread's atomics in flight together
+      uint32_t c[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) c[i] = S.vcnt[t + EB_T * i];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const uint32_t q = t + EB_T * i;
+        if (c[i] != 0u) c[i] = atomicAdd(&cnt[(S.vkey[q / VS_RUN] - 1u) * VS_RUN + q % VS_RUN], c[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < NV; ++i) S.vcnt[t + EB_T * i] = c[i];
+    }
+    // the chunk's pairs into consecutive places of the list
+    uint32_t at_[EB_SET / EB_T];
+#pragma unroll
+    for (uint32_t i = 0; i < EB_SET / EB_T; ++i) {
+      const uint32_t s = t + i * EB_T;
+      const bool out = S.pair[s] != EB_FREE && S.where[s] != EB_GONE;
+      const uint64_t m = __ballot(out);
+      uint32_t w = 0u;
+      if (lane == 0u && m) w = atomicAdd(&S.nitem, (uint32_t)__popcll(m));
+      w = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+      at_[i] = out ? w + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : EB_GONE;
+    }
+    __syncthreads();
+    if (t == 0u) S.base = atomicAdd(n_item, S.nitem);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < EB_SET / EB_T; ++i) {
+      if (at_[i] == EB_GONE) continue;
+      const uint32_t s = t + i * EB_T, o = S.base + at_[i], w = S.where[s];
+      la[o] = (uint32_t)(S.pair[s] >> 32);
+      lb[o] = (uint32_t)S.pair[s];
+      lr[o] = S.vcnt[w >> 16] + (w & 0xffffu);
+    }
+    __syncthreads();
+  }
+}
+
+// sums of 2048 counts each, for the spine
+constexpr uint32_t EB_SCAN = 2048;
+__global__ __launch_bounds__(RT) void k_cnt_sum(const uint32_t* cnt, uint32_t n, uint32_t* bsum) {
+  __shared__ uint32_t lds[RT / 64];
+  const uint32_t i0 = blockIdx.x * EB_SCAN + threadIdx.x;
+  uint32_t s = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < EB_SCAN; i += RT) s += i0 + i < n ? cnt[i0 + i] : 0u;
+  uint32_t tot;
+  block_scan_excl(s, lds, &tot);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+}
+
+// in place: counts to bucket starts (the blocks' first from the spine)
+__global__ __launch_bounds__(RT) void k_cnt_starts(uint32_t* cnt, uint32_t n, const uint32_t* bsum) {
+  __shared__ uint32_t lds[RT / 64];
+  constexpr uint32_t PER = EB_SCAN / RT;
+  const uint32_t i0 = blockIdx.x * EB_SCAN + threadIdx.x * PER;
+  uint32_t c[PER], s = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    c[i] = i0 + i < n ? cnt[i0 + i] : 0u;
+    s += c[i];
+  }
+  uint32_t tot;
+  uint32_t run = bsum[blockIdx.x] + block_scan_excl(s, lds, &tot);
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    if (i0 + i < n) cnt[i0 + i] = run;
+    run += c[i];
+  }
+}
+
+__global__ __launch_bounds__(RT) void k_edge_place(const uint32_t* start, const uint32_t* n_item, const uint32_t* la,
+                                                   const uint32_t* lb, const uint32_t* lr, uint32_t* bucket) {
+  const uint32_t n = *n_item;
+  for (uint32_t i = blockIdx.x * RT + threadIdx.x; i < n; i += gridDim.x * RT) bucket[start[la[i]] + lr[i]] = lb[i];
+}
+
+// Sort of a bucket too long for LDS, by one block: runs of EU_RUN sorted in
+// LDS by comparison counts, merged pairwise between x and y (a run's element
+// goes to its index plus the number of smaller, or for the right run not
+// larger, elements of the other); the result ends in x.
+constexpr uint32_t EU_CAP = 2048;     // entries of a block's buckets in LDS
+constexpr uint32_t EU_VERTS = 64;     // buckets per block
+constexpr uint32_t EU_RUN = 512;
+__device__ void sort_long_bucket(uint32_t* x, uint32_t* y, uint32_t n, uint32_t* lds) {
+  for (uint32_t r0 = 0; r0 < n; r0 += EU_RUN) {
+    const uint32_t m = min(EU_RUN, n - r0);
+    for (uint32_t i = threadIdx.x; i < m; i += RT) lds[i] = x[r0 + i];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < m; i += RT) {
+      const uint32_t k = lds[i];
+      uint32_t p = 0;
+      for (uint32_t j = 0; j < m; ++j) p += (lds[j] < k || (lds[j] == k && j < i)) ? 1u : 0u;
+      x[r0 + p] = k;
+    }
+    __syncthreads();
+  }
+  uint32_t *a = x, *b = y;
+  for (uint32_t w = EU_RUN; w < n; w <<= 1) {
+    for (uint32_t i = threadIdx.x; i < n; i += RT) {
+      const uint32_t k = a[i], pair = i / (2u * w) * (2u * w);
+      const bool left = i - pair < w;
+      const uint32_t o0 = left ? min(pair + w, n) : pair, o1 = left ? min(pair + 2u * w, n) : pair + w;
+      uint32_t lo = o0, hi = o1;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (left ? a[mid] < k : a[mid] <= k) lo = mid + 1u;
+        else hi = mid;
+      }
+      b[left ? i + (lo - o0) : pair + (i - pair - w) + (lo - o0)] = k;
+    }
+    __syncthreads();
+    uint32_t* s = a; a = b; b = s;
+  }
+  if (a != x)
+    for (uint32_t i = threadIdx.x; i < n; i += RT) x[i] = a[i];
+  __syncthreads();
+}
+
+// Each bucket sorted and freed of repeats in place; ucnt: what is left of it,
+// bsum: of the block's buckets.  start[V] is the end of the last bucket.
+__global__ __launch_bounds__(RT) void k_edge_unique(const uint32_t* start, uint32_t V, uint32_t* bucket,
+                                                    uint32_t* scratch, uint32_t* ucnt, uint32_t* bsum) {
+  __shared__ uint32_t b[EU_CAP];
+  __shared__ uint8_t owner[EU_CAP], first[EU_CAP];
+  __shared__ uint32_t s0[EU_VERTS + 1], u[EU_VERTS];
+  const uint32_t v0 = blockIdx.x * EU_VERTS, nv = min(EU_VERTS, V - v0), t = threadIdx.x;
+  if (t <= nv) s0[t] = start[v0 + t];
+  if (t < EU_VERTS) u[t] = 0u;
+  __syncthreads();
+  // as many buckets at a time as fit in LDS
+  for (uint32_t g0 = 0; g0 < nv;) {
+    uint32_t g1 = g0 + 1u;
+    while (g1 < nv && s0[g1 + 1u] - s0[g0] <= EU_CAP) ++g1;
+    const uint32_t e0 = s0[g0], n = s0[g1] - e0;
+    if (n > EU_CAP) {   // one long bucket
+      sort_long_bucket(bucket + e0, scratch + e0, n, b);
+      // repeats out, in chunks of the block's threads
+      __shared__ uint32_t lds[RT / 64];
+      uint32_t run = 0;
+      for (uint32_t i0 = 0; i0 < n; i0 += RT) {
+        const uint32_t i = i0 + t;
+        const uint32_t k = i < n ? bucket[e0 + i] : 0u;
+        const bool keep = i < n && (i == 0u || bucket[e0 + i - 1u] != k);
+        uint32_t tot;
+        const uint32_t p = run + block_scan_excl(keep ? 1u : 0u, lds, &tot);
+        if (keep) scratch[e0 + p] = k;
+        run += tot;
+      }
+      __syncthreads();
+      for (uint32_t i = t; i < run; i += RT) bucket[e0 + i] = scratch[e0 + i];
+      if (t == 0u) u[g0] = run;
+      __syncthreads();
+      g0 = g1;
+      continue;
+    }
+    for (uint32_t i = t; i < n; i += RT) b[i] = bucket[e0 + i];
+    for (uint32_t g = g0 + t; g < g1; g += RT)
+      for (uint32_t i = s0[g] - e0; i < s0[g + 1u] - e0; ++i) owner[i] = (uint8_t)g;
+    __syncthreads();
+    for (uint32_t i = t; i < n; i += RT) {
+      bool f = true;
+      for (uint32_t j = s0[owner[i]] - e0; j < i; ++j) f = f && b[j] != b[i];
+      first[i] = f ? 1 : 0;
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < n; i += RT) {
+      if (!first[i]) continue;
+      const uint32_t g = owner[i], i0 = s0[g] - e0, i1 = s0[g + 1u] - e0;
+      uint32_t p = 0;
+      for (uint32_t j = i0; j < i1; ++j) p += (first[j] && b[j] < b[i]) ? 1u : 0u;
+      bucket[s0[g] + p] = b[i];
+      atomicAdd(&u[g], 1u);
+    }
+    __syncthreads();
+    g0 = g1;
+  }
+  if (t < nv) ucnt[v0 + t] = u[t];
+  if (t < 64u) {
+    uint32_t x = t < nv ? u[t] : 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    if (t == 0u) bsum[blockIdx.x] = x;
+  }
+}
+
+__global__ __launch_bounds__(RT) void k_edge_out(const uint32_t* start, uint32_t V, const uint32_t* bucket,
+                                                 const uint32_t* ucnt, const uint32_t* bsum, int2* edges) {
+  __shared__ uint32_t off[EU_VERTS + 1], s0[EU_VERTS];
+  const uint32_t v0 = blockIdx.x * EU_VERTS, nv = min(EU_VERTS, V - v0), t = threadIdx.x;
+  if (t < 64u) {
+    const uint32_t c = t < nv ? ucnt[v0 + t] : 0u, x = wave_scan_add(c);
+    off[t + 1u] = x;
+    if (t == 0u) off[0] = 0u;
+    if (t < nv) s0[t] = start[v0 + t];
+  }
+  __syncthreads();
+  const uint32_t n = off[EU_VERTS], o0 = bsum[blockIdx.x];
+  for (uint32_t i = t; i < n; i += RT) {
+    uint32_t g = 0;   // the last vertex whose first edge is at or before i
+#pragma unroll
+    for (uint32_t step = EU_VERTS / 2; step > 0u; step >>= 1) g = off[g + step] <= i ? g + step : g;
+    edges[o0 + i] = make_int2((int32_t)(v0 + g), (int32_t)bucket[s0[g] + (i - off[g])]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// regularisers
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(RT) void k_fill_f32(float* p, size_t n, float v) {
+  for (size_t i = blockIdx.x * (size_t)RT + threadIdx.x; i < n; i += (size_t)gridDim.x * RT) p[i] = v;
+}
+
+// the three accumulators of the gradient pass, cleared in one launch
+__global__ __launch_bounds__(RT) void k_reg_clear(float* dm, float* dverts, float* dsdf, size_t V) {
+  for (size_t i = blockIdx.x * (size_t)RT + threadIdx.x; i < 3 * V; i += (size_t)gridDim.x * RT) {
+    dm[i] = 0.0f;
+    dverts[i] = 0.0f;
+    if (i < V) dsdf[i] = 0.0f;
+  }
 }
 
 __device__ __forceinline__ float block_sum_vs(float v, float* lds /*[VS_T/64]*/) {
@@ -568,139 +875,271 @@ constexpr MTTable make_mt_table() {
 }
 __constant__ MTTable c_mt = make_mt_table();
 
-__global__ __launch_bounds__(RT) void k_mt_edge_pass(const float* verts, const float* sdf, int32_t V,
-                                                     const int32_t* edges, const int32_t* n_edges, uint32_t cap,
-                                                     uint32_t* bsum, int32_t* vid, float* out, uint32_t vcap,
-                                                     int write) {
-  __shared__ uint32_t lds[RT / 64];
+// Marching Tetrahedra runs in three passes with a scan between.  The first
+// marks: per edge whether its ends differ in the inside test, per tet its four
+// inside bits, as ballots of 64 consecutive edges or tets (a wave takes eight
+// rows of 64, so that every load is contiguous), and counts per block.  The
+// writing passes read the marks, not the SDF, and only the marked few do any
+// work: the tets that give triangles are first listed per block in LDS, in tet
+// order.  A crossed edge's number is found through the first edge of its lower
+// vertex where the table of those fits the workspace (a binary search over all
+// edges otherwise: some 21 dependent loads against 3).
+constexpr int MT_ROWS = EDGE_ITEMS;   // rows of 64 per wave: EDGE_TILE per block
+
+__global__ __launch_bounds__(RT) void k_mt_edge_mark(const float* sdf, int32_t V, const int32_t* edges,
+                                                     const int32_t* n_edges, uint32_t cap, uint64_t* mark,
+                                                     uint32_t* first_edge, uint32_t* bsum) {
+  __shared__ uint32_t wsum[RT / 64];
   const uint32_t ne = min((uint32_t)max(n_edges[0], 0), cap);
-  const uint32_t j0 = blockIdx.x * EDGE_TILE + threadIdx.x * EDGE_ITEMS;
-  uint32_t bits = 0;
-  int2 ab[EDGE_ITEMS];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t j0 = blockIdx.x * EDGE_TILE + wave * (64u * MT_ROWS);
+  uint32_t cnt = 0;
+  int2 e[MT_ROWS];
 #pragma unroll
-  for (int t = 0; t < EDGE_ITEMS; ++t) {
-    const uint32_t j = j0 + t;
-    ab[t] = make_int2(-1, -1);
-    if (j < ne) {
-      const int2 e = reinterpret_cast<const int2*>(edges)[j];
-      if ((uint32_t)e.x < (uint32_t)V && (uint32_t)e.y < (uint32_t)V) {
-        ab[t] = e;
-        if ((sdf[e.x] < 0.0f) != (sdf[e.y] < 0.0f)) bits |= 1u << t;
-      }
+  for (int i = 0; i < MT_ROWS; ++i) {
+    const uint32_t j = j0 + 64u * i + lane;
+    e[i] = j < ne ? reinterpret_cast<const int2*>(edges)[j] : make_int2(-1, -1);
+  }
+#pragma unroll
+  for (int i = 0; i < MT_ROWS; ++i) {
+    const uint32_t j = j0 + 64u * i + lane;
+    const bool ok = (uint32_t)e[i].x < (uint32_t)V && (uint32_t)e[i].y < (uint32_t)V;
+    const bool cut = ok && (sdf[e[i].x] < 0.0f) != (sdf[e[i].y] < 0.0f);
+    const uint64_t m = __ballot(cut);
+    if (lane == 0u && j0 + 64u * i < ne) mark[(j0 + 64u * i) / 64u] = m;
+    cnt += (uint32_t)__popcll(m);
+    if (first_edge && ok) {
+      // edges ascend by (a, b): the first of its lower vertex differs from the
+      // one before (an unused vertex's entry is never read)
+      int before = __shfl_up(e[i].x, 1, 64);
+      if (lane == 0u) before = j > 0u ? reinterpret_cast<const int2*>(edges)[j - 1u].x : -1;
+      if (before != e[i].x) first_edge[e[i].x] = j;
     }
   }
-  uint32_t tot;
-  const uint32_t base = block_scan_excl(__popc(bits), lds, &tot);
-  if (!write) {
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-    return;
-  }
-  uint32_t o = bsum[blockIdx.x] + base;
-#pragma unroll
-  for (int t = 0; t < EDGE_ITEMS; ++t) {
-    const uint32_t j = j0 + t;
-    if (j >= ne) continue;
-    if (!(bits & (1u << t))) {
-      vid[j] = -1;
-      continue;
-    }
-    vid[j] = (int32_t)o;
-    if (o < vcap) {
-      const float fa = sdf[ab[t].x], fb = sdf[ab[t].y];
-      const float tt = fa / (fa - fb);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const float xa = verts[3 * (size_t)ab[t].x + c], xb = verts[3 * (size_t)ab[t].y + c];
-        out[3 * (size_t)o + c] = xa + tt * (xb - xa);
-      }
-    }
-    ++o;
-  }
+  if (lane == 0u) wsum[wave] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
 
-// index of edge (a, b) in the sorted list, -1 if absent
-__device__ __forceinline__ int32_t find_edge(const int32_t* edges, uint32_t ne, int32_t a, int32_t b) {
-  const int2* E = reinterpret_cast<const int2*>(edges);
-  uint32_t lo = 0, hi = ne;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    const int2 e = E[mid];
-    if (e.x < a || (e.x == a && e.y < b))
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return (lo < ne && E[lo].x == a && E[lo].y == b) ? (int32_t)lo : -1;
+// the edge blocks' and the tet blocks' sums, a block each
+__global__ __launch_bounds__(1024) void k_mt_spines(uint32_t* be, uint32_t ne, uint32_t* bt, uint32_t nt,
+                                                    int32_t* counts) {
+  if (blockIdx.x == 0) spine_1024(be, ne, counts);
+  else spine_1024(bt, nt, counts + 1);
 }
 
-__device__ __forceinline__ int32_t surf_vertex(const int32_t* edges, uint32_t ne, const int32_t* vid, int32_t u,
-                                               int32_t w) {
-  const int32_t e = find_edge(edges, ne, min(u, w), max(u, w));
-  return e < 0 ? -1 : vid[e];
+__global__ __launch_bounds__(RT) void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
+  for (size_t i = blockIdx.x * (size_t)RT + threadIdx.x; i < n; i += (size_t)gridDim.x * RT) p[i] = v;
 }
 
-__global__ __launch_bounds__(RT) void k_mt_tet_pass(const float* verts, const int32_t* tets, const float* sdf,
-                                                    int32_t V, uint32_t K, const int32_t* edges,
-                                                    const int32_t* n_edges, uint32_t cap, const int32_t* vid,
-                                                    uint32_t* bsum, int32_t* tris, uint32_t tcap, int write) {
-  __shared__ uint32_t lds[RT / 64];
-  const uint32_t k0 = blockIdx.x * EDGE_TILE + threadIdx.x * EDGE_ITEMS;
-  uint32_t mask[EDGE_ITEMS];
+__global__ __launch_bounds__(RT) void k_mt_edge_write(const float* verts, const float* sdf, const int32_t* edges,
+                                                      const int32_t* n_edges, uint32_t cap, const uint64_t* mark,
+                                                      const uint32_t* bsum, int32_t* vid, float* out,
+                                                      uint32_t vcap) {
+  __shared__ uint32_t wsum[RT / 64];
+  const uint32_t ne = min((uint32_t)max(n_edges[0], 0), cap);
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t j0 = blockIdx.x * EDGE_TILE + wave * (64u * MT_ROWS);
+  uint64_t m[MT_ROWS];
   uint32_t cnt = 0;
 #pragma unroll
-  for (int t = 0; t < EDGE_ITEMS; ++t) {
-    const uint32_t k = k0 + t;
-    mask[t] = 0;
-    if (k < K) {
-      int32_t v[4];
-      if (load_tet(tets, k, V, v))
-        mask[t] = (sdf[v[0]] < 0.0f ? 1u : 0u) | (sdf[v[1]] < 0.0f ? 2u : 0u) | (sdf[v[2]] < 0.0f ? 4u : 0u) |
-                  (sdf[v[3]] < 0.0f ? 8u : 0u);
-    }
-    cnt += c_mt.c[mask[t]].ntri;
+  for (int i = 0; i < MT_ROWS; ++i) {
+    m[i] = j0 + 64u * i < ne ? mark[(j0 + 64u * i) / 64u] : 0ull;
+    cnt += (uint32_t)__popcll(m[i]);
   }
-  uint32_t tot;
-  const uint32_t base = block_scan_excl(cnt, lds, &tot);
-  if (!write) {
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  if (lane == 0u) wsum[wave] = cnt;
+  __syncthreads();
+  uint32_t o0 = bsum[blockIdx.x];
+  for (uint32_t w = 0; w < wave; ++w) o0 += wsum[w];
+#pragma unroll 1
+  for (int i = 0; i < MT_ROWS; ++i) {
+    const uint32_t j = j0 + 64u * i + lane, o = o0 + (uint32_t)__popcll(m[i] & ((1ull << lane) - 1ull));
+    o0 += (uint32_t)__popcll(m[i]);
+    const bool cut = (m[i] >> lane) & 1ull;
+    if (j < ne) vid[j] = cut ? (int32_t)o : -1;
+    if (!cut || o >= vcap) continue;
+    const int2 ab = reinterpret_cast<const int2*>(edges)[j];
+    const float fa = sdf[ab.x], fb = sdf[ab.y];
+    const float tt = fa / (fa - fb);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float xa = verts[3 * (size_t)ab.x + c], xb = verts[3 * (size_t)ab.y + c];
+      out[3 * (size_t)o + c] = xa + tt * (xb - xa);
+    }
+  }
+}
+
+__global__ __launch_bounds__(RT) void k_mt_tet_mark(const int32_t* tets, const float* sdf, int32_t V, uint32_t K,
+                                                    uint64_t* mark, uint32_t* bsum) {
+  __shared__ uint32_t wsum[RT / 64];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t k0 = blockIdx.x * EDGE_TILE + wave * (64u * MT_ROWS);
+  uint32_t cnt = 0;
+#pragma unroll
+  for (int i = 0; i < MT_ROWS; ++i) {
+    const uint32_t k = k0 + 64u * i + lane;
+    int32_t v[4];
+    bool in[4] = {false, false, false, false};
+    if (k < K && load_tet(tets, k, V, v)) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) in[q] = sdf[v[q]] < 0.0f;
+    }
+    uint64_t m[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = __ballot(in[q]);
+    if (lane < 4u && k0 + 64u * i < K)
+      mark[4 * (size_t)((k0 + 64u * i) / 64u) + lane] = lane == 0u ? m[0] : lane == 1u ? m[1] : lane == 2u ? m[2] : m[3];
+    // one triangle where one or three are inside, two where two are
+    const uint64_t odd = m[0] ^ m[1] ^ m[2] ^ m[3];
+    const uint64_t some = m[0] | m[1] | m[2] | m[3], all = m[0] & m[1] & m[2] & m[3];
+    cnt += (uint32_t)__popcll(odd) + 2u * (uint32_t)__popcll(some & ~all & ~odd);
+  }
+  if (lane == 0u) wsum[wave] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
+// the numbers of four edges' surface vertices (u_q, w_q), -1 if absent, their
+// dependent loads in flight together
+__device__ __forceinline__ void surf_vertices(const int32_t* edges, uint32_t ne, const uint32_t* first_edge,
+                                              const int32_t* vid, const int32_t (&u)[4], const int32_t (&w)[4],
+                                              int32_t (&out)[4]) {
+  const int2* E = reinterpret_cast<const int2*>(edges);
+  int32_t a[4], b[4];
+  uint32_t lo[4];
+  bool open[4];   // E[lo] may still be below (a, b)
+  if (ne == 0u) {   // (an empty list has no last edge to read instead)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = -1;
     return;
   }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    a[q] = min(u[q], w[q]);
+    b[q] = max(u[q], w[q]);
+    lo[q] = first_edge ? first_edge[a[q]] : 0u;   // (past the list for a vertex without edges)
+    open[q] = lo[q] < ne;
+  }
+  if (first_edge) {
+    // a's edges follow its first one, most often within a cache line
+    for (int step = 0; step < 8; ++step) {
+      int2 e[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[q] = E[min(lo[q], ne - 1u)];
+      bool any = false;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        open[q] = open[q] && (e[q].x < a[q] || (e[q].x == a[q] && e[q].y < b[q]));
+        lo[q] += open[q] ? 1u : 0u;
+        open[q] = open[q] && lo[q] < ne;
+        any = any || open[q];
+      }
+      if (!any) break;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (open[q]) {   // no table, or a vertex of many edges
+      uint32_t hi = ne;
+      while (lo[q] < hi) {
+        const uint32_t mid = (lo[q] + hi) >> 1;
+        const int2 e = E[mid];
+        if (e.x < a[q] || (e.x == a[q] && e.y < b[q])) lo[q] = mid + 1u;
+        else hi = mid;
+      }
+    }
+    out[q] = -1;
+    if (lo[q] < ne) {
+      const int2 e = E[lo[q]];
+      if (e.x == a[q] && e.y == b[q]) out[q] = vid[lo[q]];
+    }
+  }
+}
+
+// four blocks per EDGE_TILE tets, each with the rows of one wave: a block of
+// the surface has some 800 crossed tets, whose chains of dependent loads would
+// follow one another
+__global__ __launch_bounds__(RT) void k_mt_tet_write(const float* verts, const int32_t* tets, uint32_t K,
+                                                     const int32_t* edges, const int32_t* n_edges, uint32_t cap,
+                                                     const uint32_t* first_edge, const int32_t* vid,
+                                                     const uint64_t* mark, const uint32_t* bsum, int32_t* tris,
+                                                     uint32_t tcap) {
+  __shared__ uint32_t wsum[RT / 64][2];
+  static_assert(MT_ROWS == 8, "a row per lane 0 to 7");
+  constexpr uint32_t ROWS = 64u * MT_ROWS;
+  __shared__ uint32_t list[ROWS];   // the block's crossed tets: place << 4 | inside bits
+  __shared__ uint32_t tri0[ROWS];   // and their first triangles
+  const uint32_t tile = blockIdx.x / (RT / 64), sub = blockIdx.x % (RT / 64);
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  // the crossed tets and triangles of every wave's rows (the earlier ones' are
+  // this block's offset)
+  uint32_t nx = 0, ntri = 0;
+  uint64_t x8 = 0ull, odd8 = 0ull, in8[4] = {0ull, 0ull, 0ull, 0ull};   // this lane's row (lanes 0 to 7)
+  const uint32_t krow = tile * EDGE_TILE + wave * ROWS + 64u * (lane & (MT_ROWS - 1u));
+  if (lane < (uint32_t)MT_ROWS && krow < K) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) in8[q] = mark[4 * (size_t)(krow / 64u) + q];
+    odd8 = in8[0] ^ in8[1] ^ in8[2] ^ in8[3];
+    x8 = (in8[0] | in8[1] | in8[2] | in8[3]) & ~(in8[0] & in8[1] & in8[2] & in8[3]);
+    nx = (uint32_t)__popcll(x8);
+    ntri = nx + (uint32_t)__popcll(x8 & ~odd8);
+  }
+  const uint32_t sx = wave_scan_add(nx), st = wave_scan_add(ntri);
+  if (lane == 63u) {
+    wsum[wave][0] = sx;
+    wsum[wave][1] = st;
+  }
+  __syncthreads();
+  const uint32_t nlist = wsum[sub][0];
+  if (nlist == 0u) return;
+  if (wave == sub) {
+    uint32_t o0 = bsum[tile];
+    for (uint32_t w = 0; w < sub; ++w) o0 += wsum[w][1];
+    // a lane lists its row's crossed tets
+    uint32_t p = sx - nx, o = o0 + st - ntri;
+    for (uint64_t r = x8; r != 0ull; r &= r - 1ull) {
+      const uint32_t bit = (uint32_t)__ffsll((unsigned long long)r) - 1u;
+      uint32_t bits = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bits |= (uint32_t)((in8[q] >> bit) & 1ull) << q;
+      list[p] = (64u * lane + bit) << 4 | bits;
+      tri0[p] = o;
+      o += ((odd8 >> bit) & 1ull) ? 1u : 2u;
+      ++p;
+    }
+  }
+  __syncthreads();
   const uint32_t ne = min((uint32_t)max(n_edges[0], 0), cap);
-  uint32_t o = bsum[blockIdx.x] + base;
-#pragma unroll 1
-  for (int t = 0; t < EDGE_ITEMS; ++t) {
-    const MTCase c = c_mt.c[mask[t]];
-    if (c.ntri == 0) continue;
-    int32_t v[4];
-    load_tet(tets, k0 + t, V, v);
+  for (uint32_t p = threadIdx.x; p < nlist; p += RT) {
+    const MTCase c = c_mt.c[list[p] & 15u];
+    const int4 row = reinterpret_cast<const int4*>(tets)[tile * EDGE_TILE + sub * ROWS + (list[p] >> 4)];
+    const int32_t v[4] = {row.x, row.y, row.z, row.w};
     // orientation of the tet: sign of det[x1 - x0, x2 - x0, x3 - x0]
     float e[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int m = 0; m < 3; ++m) e[a][m] = verts[3 * (size_t)v[a + 1] + m] - verts[3 * (size_t)v[0] + m];
+      for (int q = 0; q < 3; ++q) e[a][q] = verts[3 * (size_t)v[a + 1] + q] - verts[3 * (size_t)v[0] + q];
     const float det = e[0][0] * (e[1][1] * e[2][2] - e[1][2] * e[2][1]) +
                       e[0][1] * (e[1][2] * e[2][0] - e[1][0] * e[2][2]) +
                       e[0][2] * (e[1][0] * e[2][1] - e[1][1] * e[2][0]);
     const bool flip = det < 0.0f;
-    const int32_t i = v[c.o[0]], j = v[c.o[1]], kk = v[c.o[2]], l = v[c.o[3]];
-    int32_t tri[2][3];
-    if (c.ntri == 1) {
-      tri[0][0] = surf_vertex(edges, ne, vid, i, j);
-      tri[0][1] = surf_vertex(edges, ne, vid, i, kk);
-      tri[0][2] = surf_vertex(edges, ne, vid, i, l);
-    } else {
-      const int32_t ik = surf_vertex(edges, ne, vid, i, kk), il = surf_vertex(edges, ne, vid, i, l);
-      const int32_t jl = surf_vertex(edges, ne, vid, j, l), jk = surf_vertex(edges, ne, vid, j, kk);
-      tri[0][0] = ik; tri[0][1] = il; tri[0][2] = jl;
-      tri[1][0] = ik; tri[1][1] = jl; tri[1][2] = jk;
-    }
+    const auto pick = [&](int q) { return q == 0 ? v[0] : q == 1 ? v[1] : q == 2 ? v[2] : v[3]; };
+    const int32_t i = pick(c.o[0]), j = pick(c.o[1]), kk = pick(c.o[2]), l4 = pick(c.o[3]);
+    // one triangle: edges ij, ik, il; two: ik, il, jl, jk
+    const bool two = c.ntri == 2;
+    const int32_t eu[4] = {i, i, two ? j : i, two ? j : i}, ew[4] = {two ? kk : j, two ? l4 : kk, l4, two ? kk : l4};
+    int32_t sv[4];
+    surf_vertices(edges, ne, first_edge, vid, eu, ew, sv);
+    const int32_t tri[2][3] = {{sv[0], sv[1], sv[2]}, {sv[0], sv[2], sv[3]}};
     const bool rev = flip != (c.rev != 0);
-    for (int q = 0; q < c.ntri; ++q, ++o) {
-      if (o >= tcap) continue;
-      tris[3 * (size_t)o + 0] = tri[q][0];
-      tris[3 * (size_t)o + 1] = rev ? tri[q][2] : tri[q][1];
-      tris[3 * (size_t)o + 2] = rev ? tri[q][1] : tri[q][2];
+    uint32_t to = tri0[p];
+#pragma unroll
+    for (int q = 0; q < 2; ++q, ++to) {
+      if (q >= c.ntri || to >= tcap) continue;
+      tris[3 * (size_t)to + 0] = tri[q][0];
+      tris[3 * (size_t)to + 1] = rev ? tri[q][2] : tri[q][1];
+      tris[3 * (size_t)to + 2] = rev ? tri[q][1] : tri[q][2];
     }
   }
 }
@@ -745,6 +1184,8 @@ EdgeLayout edge_layout(int32_t K) {
   E.n = n;
   E.sort_blocks = (n + SORT_TILE - 1) / SORT_TILE;
   E.edge_blocks = (n + EDGE_TILE - 1) / EDGE_TILE;
+  // binned: the vertices the per-vertex arrays have room for
+  E.verts = 4ull * (uint64_t)K + 1024;
   size_t o = 0;
   E.o_n = o; o += al(16);
   E.o_ka = o; o += al(4 * n);
@@ -752,14 +1193,48 @@ EdgeLayout edge_layout(int32_t K) {
   E.o_kb = o; o += al(4 * n);
   E.o_vb = o; o += al(4 * n);
   E.o_hist = o; o += al(4 * (256 * (size_t)E.sort_blocks + 256));
-  E.o_bsum = o; o += al(4 * ((size_t)E.edge_blocks + 1));
+  E.o_bsum = o; o += al(4 * (std::max<size_t>((size_t)E.edge_blocks, (size_t)E.verts / EU_VERTS + 1) + 1));
+  E.o_start = o; o += al(4 * ((size_t)E.verts + VS_RUN + 1));
+  E.o_ucnt = o; o += al(4 * (size_t)E.verts);
   E.bytes = o;
   return E;
+}
+
+// The binned build; V + 1 <= E.verts.
+static hipError_t mesh_edges_binned(const int32_t* tets, uint32_t K, uint32_t V, int32_t* edges, int32_t* n_edges,
+                                    char* w, const EdgeLayout& E, hipStream_t st) {
+  uint32_t* n_item = reinterpret_cast<uint32_t*>(w + E.o_n);
+  uint32_t* la = reinterpret_cast<uint32_t*>(w + E.o_ka);
+  uint32_t* lb = reinterpret_cast<uint32_t*>(w + E.o_va);
+  uint32_t* lr = reinterpret_cast<uint32_t*>(w + E.o_kb);
+  uint32_t* bucket = reinterpret_cast<uint32_t*>(w + E.o_vb);
+  uint32_t* bsum = reinterpret_cast<uint32_t*>(w + E.o_bsum);
+  uint32_t* start = reinterpret_cast<uint32_t*>(w + E.o_start);
+  uint32_t* ucnt = reinterpret_cast<uint32_t*>(w + E.o_ucnt);
+  const uint32_t nc = V + 1u;   // the counts and, behind them, the total
+  k_edge_clear<<<std::max(1u, std::min((nc + RT - 1) / RT, 2048u)), RT, 0, st>>>(start, nc + VS_RUN, n_item);
+  const uint32_t chunks = (K + EB_CHUNK - 1u) / EB_CHUNK;
+  if (K > 0) k_edge_bin<<<std::min(chunks + 7u, 2048u), EB_T, 0, st>>>(tets, K, (int32_t)V, start, n_item, la, lb, lr);
+  const uint32_t nb = (nc + EB_SCAN - 1u) / EB_SCAN;
+  k_cnt_sum<<<nb, RT, 0, st>>>(start, nc, bsum);
+  k_edge_spine<<<1, 1024, 0, st>>>(bsum, nb, n_edges);   // (n_edges is rewritten below)
+  k_cnt_starts<<<nb, RT, 0, st>>>(start, nc, bsum);
+  const uint32_t nu = (V + EU_VERTS - 1u) / EU_VERTS;
+  if (K > 0)
+    k_edge_place<<<(unsigned)std::min<uint64_t>((E.n + RT - 1) / RT, 4096), RT, 0, st>>>(start, n_item, la, lb, lr,
+                                                                                         bucket);
+  if (nu > 0) k_edge_unique<<<nu, RT, 0, st>>>(start, V, bucket, la, ucnt, bsum);
+  k_edge_spine<<<1, 1024, 0, st>>>(bsum, nu, n_edges);
+  if (nu > 0) k_edge_out<<<nu, RT, 0, st>>>(start, V, bucket, ucnt, bsum, reinterpret_cast<int2*>(edges));
+  return hipGetLastError();
 }
 
 hipError_t launch_mesh_edges(const int32_t* tets, int32_t K, int32_t V, int32_t* edges, int32_t* n_edges, void* ws,
                              const EdgeLayout& E, hipStream_t st) {
   char* w = static_cast<char*>(ws);
+  if ((uint64_t)V + 1 <= E.verts) return mesh_edges_binned(tets, (uint32_t)K, (uint32_t)V, edges, n_edges, w, E, st);
+  // more vertices than the workspace (sized by K) has room for: most belong to
+  // no tet.  The 6 K pairs sorted by b, then stably by a
   uint32_t* n_dev = reinterpret_cast<uint32_t*>(w + E.o_n);
   uint32_t* ka = reinterpret_cast<uint32_t*>(w + E.o_ka);
   uint32_t* va = reinterpret_cast<uint32_t*>(w + E.o_va);
@@ -857,8 +1332,12 @@ MTLayout mt_layout(int32_t K, int64_t edge_cap) {
   MTLayout M{};
   M.edge_blocks = ((uint64_t)edge_cap + EDGE_TILE - 1) / EDGE_TILE;
   M.tet_blocks = ((uint64_t)K + EDGE_TILE - 1) / EDGE_TILE;
+  M.verts = (uint64_t)edge_cap;   // vertices whose first edges the table holds
   size_t o = 0;
   M.o_vid = o; o += al(4 * (size_t)edge_cap);
+  M.o_first = o; o += al(4 * (size_t)M.verts);
+  M.o_emark = o; o += al(8 * ((size_t)edge_cap / 64 + 1));
+  M.o_tmark = o; o += al(32 * ((size_t)K / 64 + 1));
   M.o_bsum_e = o; o += al(4 * ((size_t)M.edge_blocks + 1));
   M.o_bsum_t = o; o += al(4 * ((size_t)M.tet_blocks + 1));
   M.bytes = o;
@@ -871,23 +1350,26 @@ hipError_t launch_marching_tets(const float* verts, const int32_t* tets, const f
                                 const MTLayout& M, hipStream_t st) {
   char* w = static_cast<char*>(ws);
   int32_t* vid = reinterpret_cast<int32_t*>(w + M.o_vid);
+  uint32_t* first = (uint64_t)V <= M.verts && V > 0 ? reinterpret_cast<uint32_t*>(w + M.o_first) : nullptr;
+  uint64_t* emark = reinterpret_cast<uint64_t*>(w + M.o_emark);
+  uint64_t* tmark = reinterpret_cast<uint64_t*>(w + M.o_tmark);
   uint32_t* be = reinterpret_cast<uint32_t*>(w + M.o_bsum_e);
   uint32_t* bt = reinterpret_cast<uint32_t*>(w + M.o_bsum_t);
   const unsigned ne = (unsigned)M.edge_blocks, nt = (unsigned)M.tet_blocks;
+  const uint32_t ec = (uint32_t)edge_cap;
   const uint32_t vc = (uint32_t)std::min<int64_t>(vert_cap, 0xffffffffll);
   const uint32_t tc = (uint32_t)std::min<int64_t>(tri_cap, 0xffffffffll);
-  if (ne > 0)
-    k_mt_edge_pass<<<ne, RT, 0, st>>>(verts, sdf, V, edges, n_edges, (uint32_t)edge_cap, be, vid, out_verts, vc, 0);
-  k_edge_spine<<<1, 1024, 0, st>>>(be, ne, counts);
-  if (ne > 0)
-    k_mt_edge_pass<<<ne, RT, 0, st>>>(verts, sdf, V, edges, n_edges, (uint32_t)edge_cap, be, vid, out_verts, vc, 1);
+  if (ne > 0) {
+    // (a vertex without edges of its own keeps 0xffffffff, past every list)
+    if (first) k_fill_u32<<<std::min(((unsigned)V + RT - 1) / RT, 2048u), RT, 0, st>>>(first, (size_t)V, ~0u);
+    k_mt_edge_mark<<<ne, RT, 0, st>>>(sdf, V, edges, n_edges, ec, emark, first, be);
+  }
+  if (nt > 0) k_mt_tet_mark<<<nt, RT, 0, st>>>(tets, sdf, V, (uint32_t)K, tmark, bt);
+  k_mt_spines<<<2, 1024, 0, st>>>(be, ne, bt, nt, counts);
+  if (ne > 0) k_mt_edge_write<<<ne, RT, 0, st>>>(verts, sdf, edges, n_edges, ec, emark, be, vid, out_verts, vc);
   if (nt > 0)
-    k_mt_tet_pass<<<nt, RT, 0, st>>>(verts, tets, sdf, V, (uint32_t)K, edges, n_edges, (uint32_t)edge_cap, vid, bt,
-                                     out_tris, tc, 0);
-  k_edge_spine<<<1, 1024, 0, st>>>(bt, nt, counts + 1);
-  if (nt > 0)
-    k_mt_tet_pass<<<nt, RT, 0, st>>>(verts, tets, sdf, V, (uint32_t)K, edges, n_edges, (uint32_t)edge_cap, vid, bt,
-                                     out_tris, tc, 1);
+    k_mt_tet_write<<<nt * (RT / 64), RT, 0, st>>>(verts, tets, (uint32_t)K, edges, n_edges, ec, ne > 0 ? first : nullptr, vid,
+                                      tmark, bt, out_tris, tc);
   return hipGetLastError();
 }
 

@@ -233,7 +233,8 @@ hipError_t radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b
 struct EdgeLayout {
   uint64_t n;            // 6 K candidate pairs
   uint64_t sort_blocks, edge_blocks;
-  size_t o_n, o_ka, o_va, o_kb, o_vb, o_hist, o_bsum, bytes;
+  uint64_t verts;        // vertices (and one more) that the per-vertex arrays hold
+  size_t o_n, o_ka, o_va, o_kb, o_vb, o_hist, o_bsum, o_start, o_ucnt, bytes;
 };
 struct RegLayout {
   size_t o_m, o_dm, o_part, bytes;
@@ -257,7 +258,8 @@ hipError_t launch_cube_grid(int R, const float* cube, float* verts, int32_t* tet
 
 struct MTLayout {
   uint64_t edge_blocks, tet_blocks;
-  size_t o_vid, o_bsum_e, o_bsum_t, bytes;
+  uint64_t verts;   // vertices that the table of first edges holds
+  size_t o_vid, o_first, o_emark, o_tmark, o_bsum_e, o_bsum_t, bytes;
 };
 MTLayout mt_layout(int32_t K, int64_t edge_cap);
 hipError_t launch_marching_tets(const float* verts, const int32_t* tets, const float* sdf, int32_t V, int32_t K,
