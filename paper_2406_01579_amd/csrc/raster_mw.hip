@@ -72,10 +72,11 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
     if (wave == NWV - 1) hm[lane] = 0ull;
     if (wave == 0) chunk_pairs<CHN>(recs, n, c, ~*done_mask, pm);
     __syncthreads();
-    for_each_pair<CHN>(pm, NT, [&](int e, int pix) {
-      const float qx = (float)(c.tx * 8 + (pix & 7)) + 0.5f, qy = (float)(c.ty * 8 + (pix >> 3)) + 0.5f;
-      PixEval h;
-      if (pixel_eval(recs[e], qx, qy, s, h) && h.alpha >= alpha_min) {
+    for_each_pair<CHN>(pm, NT, [&](int e, int x, int y) {
+      const float qx = (float)(c.tx * 8 + x) + 0.5f, qy = (float)(c.ty * 8 + y) + 0.5f;
+      PixHit h;
+      if (pixel_hit(recs[e], qx, qy, s, h) && h.alpha >= alpha_min) {
+        const int pix = y * 8 + x;
         alds[e][pix] = h.alpha;
         atomicOr(&hm[pix], 1ull << e);
       }
@@ -197,7 +198,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
       return;
     }
   }
+  PairSelect<CHN, 64 * NWV> ps;
+  ps.load();
   const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order));
+  ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
   const uint32_t start = c.start, end = c.end;
@@ -292,7 +296,10 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   const TileSlot* bslots = at<const TileSlot>(ws, L.o_bwd_order);
   if (!recompute && blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work) return;
   if (!recompute && at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x] == bslots[blockIdx.x].start) return;
+  PairSelect<CHB, NT> ps;
+  ps.load();
   const Tile8 c = tile8(vw, bslots);
+  ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
   const uint32_t start = c.start, end = c.end;
@@ -375,13 +382,14 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
       pair_map<CHB>(n, bm_cur, pm);
     }
     __syncthreads();
-    for_each_pair<CHB>(pm, NT, [&](int e, int pix) {
-      const float px_ = (float)(c.tx * 8 + (pix & 7)) + 0.5f, py_ = (float)(c.ty * 8 + (pix >> 3)) + 0.5f;
-      PixEval h;
-      if (pixel_eval(recs[e], px_, py_, s, h)) {
+    for_each_pair<CHB>(pm, NT, [&](int e, int x, int y) {
+      const float px_ = (float)(c.tx * 8 + x) + 0.5f, py_ = (float)(c.ty * 8 + y) + 0.5f;
+      PixHit h;
+      if (pixel_hit(recs[e], px_, py_, s, h)) {
+        const int pix = y * 8 + x;
         abuf[e][pix] = h.alpha;
         e2buf[e][pix] = h.e2;
-        sel[e][pix] = (uint8_t)(h.fe | (h.fx << 2));
+        sel[e][pix] = (uint8_t)h.faces;
         if (h.alpha >= alpha_min) atomicOr(&hmask[pix], 1ull << e);
       }
     });

@@ -127,7 +127,10 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
   __shared__ float pay[WS][8][64];      // per slot: alpha, c[3], zt, n[3]
   __shared__ unsigned long long done_mask;
 
+  PairSelect<CHW, NT> ps;
+  ps.load();
   const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order));
+  ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
   const uint32_t start = c.start, end = c.end;
@@ -191,10 +194,11 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
     if (wave == NWV - 1) hm[lane] = 0u;
     if (wave == 0) chunk_pairs<CHW>(recs, n, c, ~done_mask, pm);
     __syncthreads();
-    for_each_pair<CHW>(pm, NT, [&](int e, int pix) {
-      const float px_ = (float)(c.tx * 8 + (pix & 7)) + 0.5f, py_ = (float)(c.ty * 8 + (pix >> 3)) + 0.5f;
-      PixEval h;
-      if (pixel_eval(recs[e], px_, py_, s, h) && h.alpha >= alpha_min) {
+    for_each_pair<CHW>(pm, NT, [&](int e, int x, int y) {
+      const float px_ = (float)(c.tx * 8 + x) + 0.5f, py_ = (float)(c.ty * 8 + y) + 0.5f;
+      PixHit h;
+      if (pixel_hit(recs[e], px_, py_, s, h) && h.alpha >= alpha_min) {
+        const int pix = y * 8 + x;
         alds[e][pix] = h.alpha;
         zlds[e][pix] = h.zin_inv;
         atomicOr(&hm[pix], 1u << e);
@@ -319,7 +323,10 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   if (blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work) return;
   const uint32_t pend = at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x];
   if (pend == bslots[blockIdx.x].start) return;
+  PairSelect<CHB, NT> ps;
+  ps.load();
   const Tile8 c = tile8(vw, bslots);
+  ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
   const uint32_t start = c.start, end = pend;   // the forward walked [start, pend)
@@ -402,14 +409,15 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
     }
     if (wave == 0) chunk_pairs<CHB>(recs, n, c, ~done_mask, pm);
     __syncthreads();
-    for_each_pair<CHB>(pm, NT, [&](int e, int pix) {
-      const float px_ = (float)(c.tx * 8 + (pix & 7)) + 0.5f, py_ = (float)(c.ty * 8 + (pix >> 3)) + 0.5f;
-      PixEval h;
-      if (pixel_eval(recs[e], px_, py_, s, h) && h.alpha >= alpha_min) {
+    for_each_pair<CHB>(pm, NT, [&](int e, int x, int y) {
+      const float px_ = (float)(c.tx * 8 + x) + 0.5f, py_ = (float)(c.ty * 8 + y) + 0.5f;
+      PixHit h;
+      if (pixel_hit(recs[e], px_, py_, s, h) && h.alpha >= alpha_min) {
+        const int pix = y * 8 + x;
         alds[e][pix] = h.alpha;
         zlds[e][pix] = h.zin_inv;
         e2lds[e][pix] = h.e2;
-        sel[e][pix] = (uint8_t)(h.fe | (h.fx << 2));
+        sel[e][pix] = (uint8_t)h.faces;
         atomicOr(&hm[pix], 1u << e);
       }
     });

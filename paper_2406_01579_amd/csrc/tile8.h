@@ -125,23 +125,37 @@ __device__ __forceinline__ uint64_t hull_mask(const ViewRec& R, const Tile8& c) 
   return rect_mask(R, c) & (((uint64_t)m[1] << 32) | m[0]);
 }
 
-// Position of the k-th (from 0) set bit of m; m has more than k set bits.
-__device__ __forceinline__ int select_bit(uint64_t m, uint32_t k) {
-  int pos = 0;
-  uint32_t c = (uint32_t)__popc((uint32_t)m);
-  const bool hi = k >= c;
-  k = hi ? k - c : k;
-  uint32_t x = hi ? (uint32_t)(m >> 32) : (uint32_t)m;
-  pos = hi ? 32 : 0;
-#pragma unroll
-  for (int w = 16; w >= 1; w >>= 1) {
-    c = (uint32_t)__popc(x & ((1u << w) - 1u));
-    const bool up = k >= c;
-    k = up ? k - c : k;
-    x = up ? x >> w : x;
-    pos = up ? pos + w : pos;
+// Positions of a byte's set bits: the k-th (from 0) in bits [4k, 4k + 3).
+struct ByteSelect {
+  uint32_t v[256];
+};
+constexpr ByteSelect make_byte_select() {
+  ByteSelect T{};
+  for (uint32_t b = 0; b < 256; ++b) {
+    uint32_t k = 0;
+    for (uint32_t j = 0; j < 8; ++j)
+      if ((b >> j) & 1u) T.v[b] |= j << (4 * k++);
   }
-  return pos;
+  return T;
+}
+__constant__ ByteSelect c_byte_select = make_byte_select();
+
+// The byte number (sel - 0x0c0c0c00) of the eight bytes hi:lo, and zeros above.
+__device__ __forceinline__ uint32_t byte_of(uint64_t x, uint32_t sel) {
+  return __builtin_amdgcn_perm((uint32_t)(x >> 32), (uint32_t)x, sel);
+}
+
+// Set bits of m in the bytes below each byte (byte 0: none), as eight bytes.
+__device__ __forceinline__ uint64_t bits_below(uint64_t m) {
+  uint32_t x[2] = {(uint32_t)m, (uint32_t)(m >> 32)};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    x[i] -= (x[i] >> 1) & 0x55555555u;
+    x[i] = (x[i] & 0x33333333u) + ((x[i] >> 2) & 0x33333333u);
+    x[i] = ((x[i] + (x[i] >> 4)) & 0x0f0f0f0fu) * 0x01010101u;   // up to and with each byte
+  }
+  x[1] += (x[0] >> 24) * 0x01010101u;
+  return ((uint64_t)x[1] << 32 | x[0]) << 8;
 }
 
 // Wave 0, lane e < n: m_e is entry e's pair mask.  Writes pmask[0..CH) and
@@ -166,13 +180,34 @@ __device__ __forceinline__ void pair_offsets(int n, uint64_t m_e, uint64_t* pmas
 // marks the pairs that begin a listed entry and bfirst counts the listed
 // entries that begin before the block.  Pair p (block b = p / 64) then
 // belongs to listed entry bfirst[b] + (starts in block b at or before p) - 1.
+// Its pixel is the mask's bit number p - first: the row is the last one whose
+// pixels below number at most that (eight compares in two subtractions, on
+// the bytes that pair_map leaves beside the mask), the column a table's.
+// (Six halvings of the mask instead: 45 instructions of a pair's 205.)
 template <int CH>
 struct PairMap {
   uint64_t bstart[CH];   // per block of 64 pairs: bit q set where a listed entry's pairs begin
-  uint64_t lmask[CH];    // listed entry k: its pixel mask
+  ulonglong2 lmask[CH];  // listed entry k: its pixel mask, and its pixels below each row (bytes)
   uint32_t bfirst[CH];   // per block: listed entries beginning before it
   uint32_t lent[CH];     // listed entry k: its chunk index | its first pair << 8
   uint32_t total;        // pairs in the chunk
+  uint32_t bsel[256];    // c_byte_select (PairSelect)
+};
+
+// The map's table, loaded at the start of a kernel and stored before the
+// first barrier.
+template <int CH, int NT>
+struct PairSelect {
+  static constexpr int N = (256 + NT - 1) / NT;
+  uint32_t v[N];
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = c_byte_select.v[(threadIdx.x + NT * i) & 255u];
+  }
+  __device__ __forceinline__ void store(PairMap<CH>& M) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) M.bsel[(threadIdx.x + NT * i) & 255u] = v[i];
+  }
 };
 
 // Wave 0, lane e < n: m_e is entry e's pixel mask.  Every lane of the wave
@@ -191,7 +226,7 @@ __device__ __forceinline__ void pair_map(int n, uint64_t m_e, PairMap<CH>& M) {
   if (lane < CH) M.bstart[lane] = 0ull;
   __builtin_amdgcn_wave_barrier();
   if (m != 0ull) {
-    M.lmask[k] = m;
+    M.lmask[k] = make_ulonglong2(m, bits_below(m));
     M.lent[k] = (uint32_t)lane | (first << 8);
     atomicOr(&M.bstart[first >> 6], 1ull << (first & 63u));
   }
@@ -212,8 +247,8 @@ __device__ __forceinline__ void chunk_pairs(const ViewRec* recs, int n, const Ti
   pair_map<CH>(n, lane < n ? hull_mask(recs[lane], c) & live_e : 0ull, M);
 }
 
-// All threads: f(e, pix) for every listed pair (entry e, local pixel pix),
-// entry-major, pixels in ascending order inside an entry.
+// All threads: f(e, x, y) for every listed pair (entry e, the tile's pixel
+// (x, y)), entry-major, pixels in ascending order inside an entry.
 template <int CH, class F>
 __device__ __forceinline__ void for_each_pair(const PairMap<CH>& M, int nthreads, F&& f) {
   const uint32_t total = M.total;
@@ -221,8 +256,15 @@ __device__ __forceinline__ void for_each_pair(const PairMap<CH>& M, int nthreads
     const uint32_t b = p >> 6;
     // pair 0 begins the first listed entry, so at least one start lies at or before p
     const uint32_t k = M.bfirst[b] + (uint32_t)__popcll(M.bstart[b] & (~0ull >> (63u - (p & 63u)))) - 1u;
-    const uint32_t le = M.lent[k];
-    f((int)(le & 0xffu), select_bit(M.lmask[k], p - (le >> 8)));
+    const uint32_t le = M.lent[k], j = p - (le >> 8);
+    const ulonglong2 m = M.lmask[k];
+    // per byte, the top bit: at most j pixels below the row (j, its pixels < 128)
+    const uint32_t jj = __builtin_amdgcn_perm(0u, j, 0u) | 0x80808080u;
+    const uint32_t rows = (uint32_t)__popc((jj - (uint32_t)m.y) & 0x80808080u) +
+                          (uint32_t)__popc((jj - (uint32_t)(m.y >> 32)) & 0x80808080u);
+    const uint32_t sel = rows + (0x0c0c0c00u - 1u);
+    const uint32_t x = M.bsel[byte_of(m.x, sel)] >> (4u * (j - byte_of(m.y, sel)));
+    f((int)(le & 0xffu), (int)(x & 7u), (int)(rows - 1u));
   }
 }
 
