@@ -24,10 +24,10 @@ namespace {
 
 // Forward sweep over [start, end) with NWV waves; wave 0 ends with the
 // pixel's blend state.  Used by the forward kernel and by the backward's
-// state replay.
+// state replay.  rp: the first chunk's indexes are in flight.
 template <int NWV, int CHN>
-__device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, const uint32_t* __restrict__ srec,
-                                              uint32_t start, uint32_t end, const Tile8& c, float s, float alpha_min,
+__device__ __forceinline__ void forward_sweep(RecPipe<CHN, 64 * NWV>& rp, const ViewRec* __restrict__ vrec,
+                                              const uint32_t* __restrict__ srec, uint32_t start, uint32_t end, const Tile8& c, float s, float alpha_min,
                                               float alpha_clamp, float t_min, ViewRec* recs, float (*alds)[64],
                                               PairMap<CHN>& pm, uint64_t* hm, float (*feat)[CHN],
                                               unsigned long long* done_mask,
@@ -38,25 +38,24 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
   constexpr int NT = 64 * NWV;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool done = !c.inside;
-  if (threadIdx.x == 0) *done_mask = 0ull;
-  __syncthreads();
   if (wave == 0) {
     const unsigned long long m = __ballot(done);
     if (lane == 0) *done_mask = m;
   }
-  RecPipe<CHN, NT> rp;
   if (start < end) {
-    rp.fetch_idx(srec, start, end - 1);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, start + CHN, end - 1);
   }
-  // the last chunk's blend masks, still in LDS: the last wave writes them out
-  // after the next chunk's loads have been issued (loads and stores share one
-  // counter, so a store issued before the wait for a load is waited for too)
+  // the last chunk's blended entries per pixel, still in LDS: the last wave
+  // turns them into the pixels per entry (what the backward's pairs are) and
+  // writes these out while the first lists the next chunk's pairs (not before
+  // that chunk's wait for its loads: loads and stores share one counter)
   uint32_t mbase = start;
   int mn = 0;
   const auto write_masks = [&] {
-    if (wave == NWV - 1 && lane < mn) bmask[mbase + lane] = bml[lane];
+    if (wave != NWV - 1 || mn == 0) return;
+    const uint64_t m = wave_transpose64(bml[lane]);
+    if (lane < mn) bmask[mbase + lane] = m;
   };
   for (uint32_t base = start; base < end; base += CHN) {
     __syncthreads();
@@ -65,12 +64,12 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
     rp.store(recs, n, feat);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, base + 2 * CHN, end - 1);
-    if (bmask) write_masks();
     __syncthreads();
     // phase A: coverage and Eq. 1 of the live (entry, pixel) pairs, packed;
     // hm[pixel] collects the chunk entries the pixel may blend
     if (wave == NWV - 1) hm[lane] = 0ull;
     if (wave == 0) chunk_pairs<CHN>(recs, n, c, ~*done_mask, pm);
+    if (bmask) write_masks();
     __syncthreads();
     for_each_pair<CHN>(pm, NT, [&](int e, int x, int y) {
       const float qx = (float)(c.tx * 8 + x) + 0.5f, qy = (float)(c.ty * 8 + y) + 0.5f;
@@ -115,11 +114,7 @@ __device__ __forceinline__ void forward_sweep(const ViewRec* __restrict__ vrec, 
         }
       }
       nblend += (uint32_t)__popcll(blended);   // the chunk's blended pairs (per lane)
-      if (bmask) {
-        // per entry of the chunk, the pixels that blended it (what the
-        // backward's pairs are): entry e's mask in lane e
-        bml[lane] = wave_transpose64(blended);
-      }
+      if (bmask) bml[lane] = blended;
       const unsigned long long m = __ballot(done);
       if (lane == 0) *done_mask = m;
     }
@@ -185,6 +180,9 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   __shared__ unsigned long long bml[64];
   __shared__ unsigned long long done_mask;
 
+  // a tile has some two chunks, so the chain of loads before the first counts:
+  // the slot, then the first records' indexes, then whatever the view gives
+  const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
   // the tiles with an empty list take the last slots (length bucket 0):
   // workgroups past the others write their background, EMPTY_PER_WG tiles
   // each, and the rest of the grid leaves at once
@@ -199,30 +197,33 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
     }
   }
   PairSelect<CHN, 64 * NWV> ps;
+  RecPipe<CHN, 64 * NWV> rp;
   ps.load();
-  const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order));
+  if (sl.start < sl.end) rp.fetch_idx(srec, sl.start, sl.end - 1);
+  const Tile8 c = tile8(vw, sl);
   ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
+  // what the end needs of the view, loaded here (not behind the sweep's stores)
+  const size_t plane = (size_t)V.W * V.H;
+  const size_t px = (size_t)c.j * V.W + c.i;
+  const float bg[3] = {uniform_f(V.bg[0]), uniform_f(V.bg[1]), uniform_f(V.bg[2])};
+  const int32_t pix_base = V.pix_base;
+  auto* out = gmem(V.out);
   const uint32_t start = c.start, end = c.end;
   float T = 1.0f, Tb = 1.0f, O = 0.0f;
   float acc[7] = {0, 0, 0, 0, 0, 0, 0};
   int last = -1;
   uint32_t nblend = 0;
   const bool count = L.o_pairs != 0;
-  forward_sweep<NWV, CHN>(vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
+  forward_sweep<NWV, CHN>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
                           feat, &done_mask, T, Tb, O, acc, last, true, nblend,
                           L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr, bml);
   if ((threadIdx.x >> 6) == 0) {
     // end of the tile's blended prefix: where the backward starts its walk
-    int wmax = last;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      wmax = max(wmax, __shfl_xor(wmax, o, 64));
-      nblend += (uint32_t)__shfl_xor((int)nblend, o, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      const uint32_t pend = wmax >= (int)start ? (uint32_t)wmax + 1u : start;
+    const uint32_t pend = wave_max((uint32_t)(last + 1 > (int)start ? last + 1 : (int)start));
+    nblend = wave_scan_add(nblend);
+    if ((threadIdx.x & 63) == 63) {
       at<uint32_t>(ws, L.o_tile_pend)[blockIdx.x] = pend;
       if (count) at<uint32_t>(ws, L.o_slot_pairs)[blockIdx.x] = nblend;
       // the backward dispatch order's histograms of walked lengths and of
@@ -239,19 +240,16 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
     }
   }
   if ((threadIdx.x >> 6) == 0 && c.inside) {
-    const size_t plane = (size_t)V.W * V.H;
-    const size_t px = (size_t)c.j * V.W + c.i;
-    auto* out = gmem(V.out);
-    out[0 * plane + px] = fmaf(T, V.bg[0], acc[0]);
-    out[1 * plane + px] = fmaf(T, V.bg[1], acc[1]);
-    out[2 * plane + px] = fmaf(T, V.bg[2], acc[2]);
+    out[0 * plane + px] = fmaf(T, bg[0], acc[0]);
+    out[1 * plane + px] = fmaf(T, bg[1], acc[1]);
+    out[2 * plane + px] = fmaf(T, bg[2], acc[2]);
     out[3 * plane + px] = O;
     out[4 * plane + px] = acc[3];
     out[5 * plane + px] = acc[4];
     out[6 * plane + px] = acc[5];
     out[7 * plane + px] = acc[6];
     if (keeps_pixel_state(L)) {
-      const size_t g = (size_t)V.pix_base + px;
+      const size_t g = (size_t)pix_base + px;
       last_out[g] = last;
       tlast_out[g] = Tb;
     }
@@ -294,11 +292,14 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   // dispatch order by the length the forward walked (longest first); the
   // tiles where nothing was blended come last and leave at once
   const TileSlot* bslots = at<const TileSlot>(ws, L.o_bwd_order);
-  if (!recompute && blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work) return;
-  if (!recompute && at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x] == bslots[blockIdx.x].start) return;
+  const TileSlot sl = bslots[blockIdx.x];
+  const uint32_t pend_f = at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x];
+  // where this tile's pairs go
+  uint32_t pair_run = at<const uint32_t>(ws, L.o_bwd_base)[blockIdx.x];
+  if (!recompute && (blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work || pend_f == sl.start)) return;
   PairSelect<CHB, NT> ps;
   ps.load();
-  const Tile8 c = tile8(vw, bslots);
+  const Tile8 c = tile8(vw, sl);
   ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
@@ -318,7 +319,9 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     float T = 1.0f, O = 0.0f;
     float acc[7];
     uint32_t nb_unused = 0;
-    forward_sweep<NWV, CHB>(vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
+    RecPipe<CHB, NT> rp;
+    if (start < end) rp.fetch_idx(srec, start, end - 1);
+    forward_sweep<NWV, CHB>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
                             hmask, feat, &done_mask, T, Tb, O, acc, last, false, nb_unused);
     if (wave == 0) {
       int wmax = last;
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     __syncthreads();
     pend = smax >= (int)start ? (uint32_t)smax + 1u : start;
   } else {
-    pend = at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x];
+    pend = pend_f;
     if (wave == 0 && c.inside) Tb = tlast_in[(size_t)V.pix_base + px];
   }
   float gr[8];
@@ -339,8 +342,6 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gmem(V.dout)[q * plane + px] : 0.0f;
     Rbehind = gr[0] * V.bg[0] + gr[1] * V.bg[1] + gr[2] * V.bg[2];
   }
-  // where this tile's pairs go
-  uint32_t pair_run = at<const uint32_t>(ws, L.o_bwd_base)[blockIdx.x];
   const uint32_t tile_xy = (uint32_t)c.tx | ((uint32_t)c.ty << 16);
 
   bool first = true;
@@ -349,8 +350,10 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   const int64_t cb0 = (int64_t)start + (((int64_t)pend - 1 - (int64_t)start) / CHB) * CHB;
   const uint32_t* rfirst = at<const uint32_t>(ws, L.o_rfirst);
   RecPipe<CHB, NT, true> rp;
-  // wave 0, lane e: the blend mask of the current chunk's entry e, and of the
-  // next chunk's (its load in flight across the current chunk)
+  // lane e of the waves that work on masks: the blend mask of the current
+  // chunk's entry e, and of the next chunk's (its load in flight across the
+  // current chunk)
+  const bool masks = (wave == 0 || wave == NWV / 2 || wave == NWV - 1) && lane < (unsigned)CHB;
   uint64_t bm_cur = 0ull, bm_next = 0ull;
   // the chunk starting at b, or below the list the entry pend - 1 again
   const auto below = [&](int64_t b) { return b >= (int64_t)start ? (uint32_t)b : pend - 1u; };
@@ -358,7 +361,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     rp.fetch_idx(srec, (uint32_t)cb0, pend - 1u);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, below(cb0 - CHB), pend - 1u);
-    if (wave == 0 && lane < pend - (uint32_t)cb0 && lane < (unsigned)CHB) bm_next = bmask[(uint32_t)cb0 + lane];
+    if (masks && lane < pend - (uint32_t)cb0) bm_next = bmask[(uint32_t)cb0 + lane];
   }
   for (int64_t cb = cb0; cb >= (int64_t)start && pend > start; cb -= CHB) {
     const uint32_t base = (uint32_t)cb;
@@ -368,43 +371,19 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     // over the current masks (a wait for their load, a chunk old) does not
     // also wait for the record loads just issued
     bm_cur = bm_next;
-    if (wave == 0 && cb - CHB >= (int64_t)start && lane < (unsigned)CHB) bm_next = bmask[base - CHB + lane];
+    if (masks && cb - CHB >= (int64_t)start) bm_next = bmask[base - CHB + lane];
     rp.store(recs, n, feat, ridx);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, below(cb - 2 * CHB), pend - 1u);
     __syncthreads();
-    // phase A: coverage, faces and Eq. 1 of every (entry, pixel) pair the
-    // forward blended, packed
-    if (wave == NWV - 1) hmask[lane] = 0ull;
-    if (wave == 0) {
-      // lane e: the pixels that blended entry e (the forward's masks, loaded
-      // a chunk ahead)
-      pair_map<CHB>(n, bm_cur, pm);
-    }
-    __syncthreads();
-    for_each_pair<CHB>(pm, NT, [&](int e, int x, int y) {
-      const float px_ = (float)(c.tx * 8 + x) + 0.5f, py_ = (float)(c.ty * 8 + y) + 0.5f;
-      PixHit h;
-      if (pixel_hit(recs[e], px_, py_, s, h)) {
-        const int pix = y * 8 + x;
-        abuf[e][pix] = h.alpha;
-        e2buf[e][pix] = h.e2;
-        sel[e][pix] = (uint8_t)h.faces;
-        if (h.alpha >= alpha_min) atomicOr(&hmask[pix], 1ull << e);
-      }
-    });
-    __syncthreads();
-    // phase B (wave 0): the chunk's pairs are the bits of hmask (every
-    // candidate at or before the pixel's last blend was blended); their
-    // places first, then the reverse recurrence writes each pair
-    if (wave == 0) {
-      const uint32_t m0 = (uint32_t)hmask[lane];   // CHB <= 32 entries
-      const uint64_t lt = (1ull << lane) - 1ull;
-      // lane e: the pixels that blended entry e
-      const uint64_t cmask_e = wave_transpose64((uint64_t)m0);
-      pair_offsets<CHB, 1>(n, cmask_e, pmask, poff);
-      // the entries with a blended pixel: what every one of their pairs carries
-      if ((int)lane < n && cmask_e != 0ull) {
+    // from the masks (lane e: the pixels that blended entry e), a wave each
+    // where there are as many: the chunk's pair list, every pixel's entries,
+    // and the places of the pairs with what every pair of an entry carries
+    if (wave == 0) pair_map<CHB>(n, bm_cur, pm);
+    if (wave == NWV - 1) hmask[lane] = (uint32_t)wave_transpose64((int)lane < n ? bm_cur : 0ull);
+    if (wave == NWV / 2) {
+      pair_offsets<CHB, 1>(n, bm_cur, pmask, poff);
+      if ((int)lane < n && bm_cur != 0ull) {
         const ViewRec& R = recs[lane];
         int i0, i1, j0, j1;
         unpack_rect(R, i0, i1, j0, j1);
@@ -412,6 +391,23 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
         const uint32_t d = R.entry0 + (uint32_t)((c.ty - ty0) * nx + (c.tx - tx0));
         eseg[lane] = make_uint4(ridx[lane], (uint32_t)c.view, tile_xy, d);
       }
+    }
+    __syncthreads();
+    // phase A: faces and Eq. 1 of every pair, packed
+    for_each_pair<CHB>(pm, NT, [&](int e, int x, int y) {
+      const float px_ = (float)(c.tx * 8 + x) + 0.5f, py_ = (float)(c.ty * 8 + y) + 0.5f;
+      PixHit h;
+      (void)pixel_hit(recs[e], px_, py_, s, h);   // (the forward found that it hits)
+      const int pix = y * 8 + x;
+      abuf[e][pix] = h.alpha;
+      e2buf[e][pix] = h.e2;
+      sel[e][pix] = (uint8_t)h.faces;
+    });
+    __syncthreads();
+    // phase B (wave 0): the reverse recurrence writes each pair
+    if (wave == 0) {
+      const uint32_t m0 = (uint32_t)hmask[lane];   // CHB <= 32 entries
+      const uint64_t lt = (1ull << lane) - 1ull;
       // each pixel visits only the entries it blended, nearest-last first
       uint32_t m = m0;
       while (__ballot(m != 0u) != 0ull) {

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
 
   PairSelect<CHW, NT> ps;
   ps.load();
-  const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order));
+  const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x]);
   ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   if (pend == bslots[blockIdx.x].start) return;
   PairSelect<CHB, NT> ps;
   ps.load();
-  const Tile8 c = tile8(vw, bslots);
+  const Tile8 c = tile8(vw, bslots[blockIdx.x]);
   ps.store(pm);
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);

@@ -38,9 +38,10 @@ struct Tile8 {
   uint32_t start, end;   // the tile's entry range
 };
 
-__device__ __forceinline__ Tile8 tile8(const DevView* vw, const TileSlot* slots) {
+// sl: the workgroup's slot.  (The caller loads it first of all and starts its
+// records' index loads from it before the view's fields are waited for here.)
+__device__ __forceinline__ Tile8 tile8(const DevView* vw, const TileSlot& sl) {
   Tile8 c;
-  const TileSlot sl = slots[blockIdx.x];
   c.tile = (int)sl.tile;
   c.view = (int)sl.view;
   c.start = sl.start;

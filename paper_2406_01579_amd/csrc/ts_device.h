@@ -477,6 +477,17 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
   return x;
 }
 
+// The same steps with max: lane 63 holds the wave's largest value.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, dpp_u32<0x111>(x));
+  x = max(x, dpp_u32<0x112>(x));
+  x = max(x, dpp_u32<0x114>(x));
+  x = max(x, dpp_u32<0x118>(x));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
 // ---------------------------------------------------------------------------
 // Transpose of the 64 x 64 bit matrix whose row r is lane r's word: bit c of
 // lane r becomes bit r of lane c.  Six butterfly steps; at step j, lanes r
