@@ -260,9 +260,12 @@ __global__ __launch_bounds__(TW* TH) void k_composite_bwd(void* ws, Layout L, fl
   }
 
   // upstream gradient
+  const auto* dout = gmem(V.dout);
   float gr[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gmem(V.dout)[q * plane + px] : 0.0f;
+  for (int q = 0; q < 8; ++q) gr[q] = dout[q * plane + px];   // (pixel 0 for a lane outside)
+#pragma unroll
+  for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gr[q] : 0.0f;
   float Rbehind = gr[0] * V.bg[0] + gr[1] * V.bg[1] + gr[2] * V.bg[2];
 
   // the tile is processed from its largest last-blended position down

@@ -297,72 +297,87 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   // where this tile's pairs go
   uint32_t pair_run = at<const uint32_t>(ws, L.o_bwd_base)[blockIdx.x];
   if (!recompute && (blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work || pend_f == sl.start)) return;
-  PairSelect<CHB, NT> ps;
-  ps.load();
-  const Tile8 c = tile8(vw, sl);
-  ps.store(pm);
-  const DevView& V = vw[c.view];
-  const float s = uniform_f(V.s);
-  const uint32_t start = c.start, end = c.end;
-  const size_t plane = (size_t)V.W * V.H;
-  const size_t px = c.inside ? (size_t)c.j * V.W + c.i : 0;
+  const uint32_t start = sl.start, end = sl.end;
   const unsigned lane = threadIdx.x & 63u;
   const int wave = threadIdx.x >> 6;
   const uint64_t cap = (uint64_t)L.entry_cap;
-
-  // per-pixel state (wave 0): T before the last blend, upstream gradient;
-  // pend: end of the tile's blended prefix (from the forward, or the replay)
-  int last = -1;
-  float Tb = 1.0f;
-  uint32_t pend;
-  if (recompute) {
-    float T = 1.0f, O = 0.0f;
-    float acc[7];
-    uint32_t nb_unused = 0;
-    RecPipe<CHB, NT> rp;
-    if (start < end) rp.fetch_idx(srec, start, end - 1);
-    forward_sweep<NWV, CHB>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
-                            hmask, feat, &done_mask, T, Tb, O, acc, last, false, nb_unused);
-    if (wave == 0) {
-      int wmax = last;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, __shfl_xor(wmax, o, 64));
-      if (lane == 0) smax = wmax;
-    }
-    __syncthreads();
-    pend = smax >= (int)start ? (uint32_t)smax + 1u : start;
-  } else {
-    pend = pend_f;
-    if (wave == 0 && c.inside) Tb = tlast_in[(size_t)V.pix_base + px];
-  }
-  float gr[8];
-  float Rbehind = 0.0f;
-  if (wave == 0) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gmem(V.dout)[q * plane + px] : 0.0f;
-    Rbehind = gr[0] * V.bg[0] + gr[1] * V.bg[1] + gr[2] * V.bg[2];
-  }
-  const uint32_t tile_xy = (uint32_t)c.tx | ((uint32_t)c.ty << 16);
-
-  bool first = true;
-  float Tnext = 1.0f;
-  // chunks from the one holding pend - 1 down to start; only the first is partial
-  const int64_t cb0 = (int64_t)start + (((int64_t)pend - 1 - (int64_t)start) / CHB) * CHB;
   const uint32_t* rfirst = at<const uint32_t>(ws, L.o_rfirst);
+
+  // The chunks run from the one holding pend - 1 down to start; only the first
+  // is partial.  pend: end of the tile's blended prefix (from the forward, or
+  // the replay).
   RecPipe<CHB, NT, true> rp;
   // lane e of the waves that work on masks: the blend mask of the current
   // chunk's entry e, and of the next chunk's (its load in flight across the
   // current chunk)
   const bool masks = (wave == 0 || wave == NWV / 2 || wave == NWV - 1) && lane < (unsigned)CHB;
   uint64_t bm_cur = 0ull, bm_next = 0ull;
+  uint32_t pend = pend_f;
+  const auto last_chunk = [&] { return (int64_t)start + (((int64_t)pend - 1 - (int64_t)start) / CHB) * CHB; };
+  // The loads before the first chunk are a chain that a tile's few chunks have
+  // to carry (it was a third of their time): the slot, the first records'
+  // indexes, the records, and beside those two whatever the view leads to.
+  const auto first_idx = [&] {
+    const uint32_t b = (uint32_t)last_chunk();
+    rp.fetch_idx(srec, b, pend - 1u);
+    if (masks && lane < pend - b) bm_next = bmask[b + lane];
+  };
+  if (!recompute) first_idx();
+  PairSelect<CHB, NT> ps;
+  ps.load();
+  const Tile8 c = tile8(vw, sl);
+  const DevView& V = vw[c.view];
+  const float s = uniform_f(V.s);
+  const size_t plane = (size_t)V.W * V.H;
+  const size_t px = c.inside ? (size_t)c.j * V.W + c.i : 0;
+  const float bg[3] = {V.bg[0], V.bg[1], V.bg[2]};
+  const size_t pix_base = (size_t)V.pix_base;
+  const auto* dout = gmem(V.dout);
+  ps.store(pm);
+
+  // per-pixel state (wave 0): T before the last blend, upstream gradient
+  int last = -1;
+  float Tb = 1.0f;
+  if (recompute) {
+    float T = 1.0f, O = 0.0f;
+    float acc[7];
+    uint32_t nb_unused = 0;
+    RecPipe<CHB, NT> rq;
+    if (start < end) rq.fetch_idx(srec, start, end - 1);
+    forward_sweep<NWV, CHB>(rq, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
+                            hmask, feat, &done_mask, T, Tb, O, acc, last, false, nb_unused);
+    if (wave == 0) {
+      const uint32_t w = wave_max((uint32_t)(last + 1 > (int)start ? last + 1 : (int)start));
+      if (lane == 63u) smax = (int)w;
+    }
+    __syncthreads();
+    pend = (uint32_t)smax;
+    if (pend > start) first_idx();
+  }
   // the chunk starting at b, or below the list the entry pend - 1 again
   const auto below = [&](int64_t b) { return b >= (int64_t)start ? (uint32_t)b : pend - 1u; };
+  const int64_t cb0 = last_chunk();
   if (pend > start) {
-    rp.fetch_idx(srec, (uint32_t)cb0, pend - 1u);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, below(cb0 - CHB), pend - 1u);
-    if (masks && lane < pend - (uint32_t)cb0) bm_next = bmask[(uint32_t)cb0 + lane];
   }
+  // (no load under a lane's condition, but at pixel 0 for a lane outside: each
+  // was waited for before the next, eight in a row, 8 to 12 k cycles)
+  float gr[8];
+  if (wave == 0) {
+    float tl = 1.0f;
+    if (!recompute) tl = tlast_in[pix_base + px];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) gr[q] = dout[q * plane + px];
+    if (!recompute && c.inside) Tb = tl;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gr[q] : 0.0f;
+  }
+  float Rbehind = 0.0f;   // (before the first chunk's recurrence: gr . background)
+  const uint32_t tile_xy = (uint32_t)c.tx | ((uint32_t)c.ty << 16);
+
+  bool first = true;
+  float Tnext = 1.0f;
   for (int64_t cb = cb0; cb >= (int64_t)start && pend > start; cb -= CHB) {
     const uint32_t base = (uint32_t)cb;
     const int n = (int)min((uint32_t)CHB, pend - base);
@@ -407,6 +422,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
     // phase B (wave 0): the reverse recurrence writes each pair
     if (wave == 0) {
       const uint32_t m0 = (uint32_t)hmask[lane];   // CHB <= 32 entries
+      if (cb == cb0) Rbehind = gr[0] * bg[0] + gr[1] * bg[1] + gr[2] * bg[2];
       const uint64_t lt = (1ull << lane) - 1ull;
       // each pixel visits only the entries it blended, nearest-last first
       uint32_t m = m0;

@@ -337,9 +337,12 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   const uint32_t tile_xy = (uint32_t)c.tx | ((uint32_t)c.ty << 16);
   const size_t plane = (size_t)V.W * V.H;
   const size_t px = c.inside ? (size_t)c.j * V.W + c.i : 0;
+  const auto* dout = gmem(V.dout);
   float gr[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gmem(V.dout)[q * plane + px] : 0.0f;
+  for (int q = 0; q < 8; ++q) gr[q] = dout[q * plane + px];   // (pixel 0 for a lane outside)
+#pragma unroll
+  for (int q = 0; q < 8; ++q) gr[q] = c.inside ? gr[q] : 0.0f;
 
   // ---- sweep 1 (window and blend records in wave 0)
   float T = 1.0f;
