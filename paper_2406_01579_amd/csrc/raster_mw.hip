@@ -22,20 +22,37 @@ namespace ts {
 namespace {
 
 
+// The blended features of a pixel (c, zt, n and the opacity, a feature of 1)
+// are eight sums that only add up what the recurrence has decided.  They are
+// left to waves other than the recurrence's, FeatSums::N of them with G sums
+// each per pixel, which add a chunk's terms, in the pixel's order, while the
+// first wave lists the next chunk's pairs.
+template <int NWV>
+struct FeatSums {
+  static constexpr int N = NWV >= 4 ? 2 : 1, G = 8 / N, W0 = NWV > 1 ? 1 : 0;   // waves W0 .. W0 + N - 1
+};
+constexpr int FEATS = 8;
+
 // Forward sweep over [start, end) with NWV waves; wave 0 ends with the
-// pixel's blend state.  Used by the forward kernel and by the backward's
-// state replay.  rp: the first chunk's indexes are in flight.
-template <int NWV, int CHN>
+// pixel's blend state, and with ACC the waves of FeatSums with its sums.  Used
+// by the forward kernel and by the backward's state replay.  rp: the first
+// chunk's indexes are in flight.
+//   Per chunk: the records into LDS; the first wave lists the pairs that may
+// hit; all waves evaluate them; the first wave runs the recurrence.  Both
+// one-wave phases are as short as they can be made: the recurrence decides who
+// blends and with what weight (left in place of alpha), and nothing else.
+template <int NWV, int CHN, bool ACC, class Rec>
 __device__ __forceinline__ void forward_sweep(RecPipe<CHN, 64 * NWV>& rp, const ViewRec* __restrict__ vrec,
-                                              const uint32_t* __restrict__ srec, uint32_t start, uint32_t end, const Tile8& c, float s, float alpha_min,
-                                              float alpha_clamp, float t_min, ViewRec* recs, float (*alds)[64],
-                                              PairMap<CHN>& pm, uint64_t* hm, float (*feat)[CHN],
-                                              unsigned long long* done_mask,
-                                              float& T, float& Tb, float& O, float (&acc)[7], int& last,
-                                              bool want_acc, uint32_t& nblend,
+                                              const uint32_t* __restrict__ srec, uint32_t start, uint32_t end,
+                                              const Tile8& c, float s, float alpha_min, float alpha_clamp, float t_min,
+                                              Rec* recs, float (*alds)[64], PairMap<CHN>& pm, uint64_t* hm,
+                                              float (*feat)[CHN] /* FEATS rows, twice with ACC */,
+                                              unsigned long long* done_mask, float& T, float& Tb, int& last,
+                                              uint32_t& nblend, float (&acc)[FeatSums<NWV>::G],
                                               unsigned long long* bmask = nullptr,
                                               unsigned long long* bml = nullptr) {
   constexpr int NT = 64 * NWV;
+  using FS = FeatSums<NWV>;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool done = !c.inside;
   if (wave == 0) {
@@ -46,22 +63,37 @@ __device__ __forceinline__ void forward_sweep(RecPipe<CHN, 64 * NWV>& rp, const 
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, start + CHN, end - 1);
   }
-  // the last chunk's blended entries per pixel, still in LDS: the last wave
+  // the last chunk's blended entries per pixel are still in LDS: the last wave
   // turns them into the pixels per entry (what the backward's pairs are) and
-  // writes these out while the first lists the next chunk's pairs (not before
-  // that chunk's wait for its loads: loads and stores share one counter)
+  // writes these out (not before the next chunk's wait for its loads: loads and
+  // stores share one counter), the waves of FeatSums add their terms
   uint32_t mbase = start;
   int mn = 0;
-  const auto write_masks = [&] {
-    if (wave != NWV - 1 || mn == 0) return;
-    const uint64_t m = wave_transpose64(bml[lane]);
-    if (lane < mn) bmask[mbase + lane] = m;
+  const auto finish_chunk = [&] {
+    if (mn == 0) return;
+    if (bmask && wave == NWV - 1) {
+      const uint64_t m = wave_transpose64(bml[lane]);
+      if (lane < mn) bmask[mbase + lane] = m;
+    }
+    if (ACC && wave >= FS::W0 && wave < FS::W0 + FS::N) {
+      const float(*ft)[CHN] = feat + ((mbase - start) / CHN & 1u) * FEATS + (wave - FS::W0) * FS::G;
+      uint64_t b = bml[lane];
+      while (__ballot(b != 0ull) != 0ull) {
+        if (b != 0ull) {
+          const int e = __ffsll((unsigned long long)b) - 1;
+          b &= b - 1ull;
+          const float w = alds[e][lane];
+#pragma unroll
+          for (int k = 0; k < FS::G; ++k) acc[k] = fmaf(w, ft[k][e], acc[k]);
+        }
+      }
+    }
   };
   for (uint32_t base = start; base < end; base += CHN) {
     __syncthreads();
     if (*done_mask == ~0ull) break;
     const int n = (int)min((uint32_t)CHN, end - base);
-    rp.store(recs, n, feat);
+    rp.store(recs, n, ACC ? feat + ((base - start) / CHN & 1u) * FEATS : feat);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, base + 2 * CHN, end - 1);
     __syncthreads();
@@ -69,7 +101,7 @@ __device__ __forceinline__ void forward_sweep(RecPipe<CHN, 64 * NWV>& rp, const 
     // hm[pixel] collects the chunk entries the pixel may blend
     if (wave == NWV - 1) hm[lane] = 0ull;
     if (wave == 0) chunk_pairs<CHN>(recs, n, c, ~*done_mask, pm);
-    if (bmask) write_masks();
+    finish_chunk();
     __syncthreads();
     for_each_pair<CHN>(pm, NT, [&](int e, int x, int y) {
       const float qx = (float)(c.tx * 8 + x) + 0.5f, qy = (float)(c.ty * 8 + y) + 0.5f;
@@ -82,47 +114,45 @@ __device__ __forceinline__ void forward_sweep(RecPipe<CHN, 64 * NWV>& rp, const 
     });
     __syncthreads();
     if (wave == 0) {
-      // each pixel visits only its candidate entries, front to back
-      uint64_t cand = hm[lane];
+      // each pixel visits only its candidate entries, front to back; the next
+      // one's alpha is read before this one is decided
+      uint64_t cand = done ? 0ull : hm[lane];
       uint64_t blended = 0ull;   // this lane's blended entries of the chunk
-      while (__ballot(cand != 0ull && !done) != 0ull) {
-        if (cand != 0ull && !done) {
-          const int e = __ffsll((unsigned long long)cand) - 1;
+      int e = (__ffsll((unsigned long long)cand) - 1) & 63;
+      float araw = alds[e & (CHN - 1)][lane];
+      while (__ballot(cand != 0ull) != 0ull) {
+        if (cand != 0ull) {
           cand &= cand - 1ull;
-          const float a = fminf(alds[e][lane], alpha_clamp);
+          const int en = (__ffsll((unsigned long long)cand) - 1) & 63;
+          const float anext = alds[en & (CHN - 1)][lane];
+          const float a = fminf(araw, alpha_clamp);
           const float Tn = T * (1.0f - a);
           if (Tn < t_min) {
             done = true;
           } else {
-            const float w = T * a;
-            if (want_acc) {
-              acc[0] = fmaf(w, feat[0][e], acc[0]);
-              acc[1] = fmaf(w, feat[1][e], acc[1]);
-              acc[2] = fmaf(w, feat[2][e], acc[2]);
-              acc[3] = fmaf(w, feat[3][e], acc[3]);
-              acc[4] = fmaf(w, feat[4][e], acc[4]);
-              acc[5] = fmaf(w, feat[5][e], acc[5]);
-              acc[6] = fmaf(w, feat[6][e], acc[6]);
-              O += w;
-            }
+            if (ACC) alds[e][lane] = T * a;   // the blend weight
             Tb = T;
             T = Tn;
-            last = (int)(base + e);
             blended |= 1ull << e;
             if (T == 0.0f) done = true;
           }
+          if (done) cand = 0ull;
+          e = en;
+          araw = anext;
         }
       }
+      if (blended != 0ull) last = (int)base + 63 - __clzll((long long)blended);
       nblend += (uint32_t)__popcll(blended);   // the chunk's blended pairs (per lane)
-      if (bmask) bml[lane] = blended;
+      if (ACC) bml[lane] = blended;
       const unsigned long long m = __ballot(done);
       if (lane == 0) *done_mask = m;
     }
     mbase = base;
     mn = n;
   }
+  if (ACC && wave == 0) reinterpret_cast<float*>(hm)[lane] = T;   // for whoever writes the sums
   __syncthreads();
-  if (bmask) write_masks();
+  finish_chunk();
 }
 
 // Background of `count` tiles with an empty list (the dispatch slots from
@@ -172,11 +202,11 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
   int32_t* last_out = at<int32_t>(ws, L.o_last);
   float* tlast_out = at<float>(ws, L.o_tlast);
-  __shared__ ViewRec recs[CHN];
+  __shared__ EvalRec recs[CHN];
   __shared__ float alds[CHN][64];
   __shared__ PairMap<CHN> pm;
   __shared__ uint64_t hm[64];
-  __shared__ float feat[7][CHN];
+  __shared__ float feat[2 * FEATS][CHN];   // a chunk's features, and the last one's: c, zt, n and 1
   __shared__ unsigned long long bml[64];
   __shared__ unsigned long long done_mask;
 
@@ -202,6 +232,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   if (sl.start < sl.end) rp.fetch_idx(srec, sl.start, sl.end - 1);
   const Tile8 c = tile8(vw, sl);
   ps.store(pm);
+  for (int q = threadIdx.x; q < 2 * CHN; q += 64 * NWV) feat[q < CHN ? FEATS - 1 : 2 * FEATS - 1][q % CHN] = 1.0f;
   const DevView& V = vw[c.view];
   const float s = uniform_f(V.s);
   // what the end needs of the view, loaded here (not behind the sweep's stores)
@@ -211,14 +242,15 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   const int32_t pix_base = V.pix_base;
   auto* out = gmem(V.out);
   const uint32_t start = c.start, end = c.end;
-  float T = 1.0f, Tb = 1.0f, O = 0.0f;
-  float acc[7] = {0, 0, 0, 0, 0, 0, 0};
+  float T = 1.0f, Tb = 1.0f;
+  using FS = FeatSums<NWV>;
+  float acc[FS::G] = {};
   int last = -1;
   uint32_t nblend = 0;
   const bool count = L.o_pairs != 0;
-  forward_sweep<NWV, CHN>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
-                          feat, &done_mask, T, Tb, O, acc, last, true, nblend,
-                          L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr, bml);
+  forward_sweep<NWV, CHN, true>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
+                                feat, &done_mask, T, Tb, last, nblend, acc,
+                                L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr, bml);
   if ((threadIdx.x >> 6) == 0) {
     // end of the tile's blended prefix: where the backward starts its walk
     const uint32_t pend = wave_max((uint32_t)(last + 1 > (int)start ? last + 1 : (int)start));
@@ -239,20 +271,21 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
       }
     }
   }
-  if ((threadIdx.x >> 6) == 0 && c.inside) {
-    out[0 * plane + px] = fmaf(T, bg[0], acc[0]);
-    out[1 * plane + px] = fmaf(T, bg[1], acc[1]);
-    out[2 * plane + px] = fmaf(T, bg[2], acc[2]);
-    out[3 * plane + px] = O;
-    out[4 * plane + px] = acc[3];
-    out[5 * plane + px] = acc[4];
-    out[6 * plane + px] = acc[5];
-    out[7 * plane + px] = acc[6];
-    if (keeps_pixel_state(L)) {
-      const size_t g = (size_t)pix_base + px;
-      last_out[g] = last;
-      tlast_out[g] = Tb;
+  const int wave = threadIdx.x >> 6;
+  if (wave >= FS::W0 && wave < FS::W0 + FS::N && c.inside) {
+    const float Tend = reinterpret_cast<const float*>(hm)[threadIdx.x & 63];
+    const int f0 = (wave - FS::W0) * FS::G;
+#pragma unroll
+    for (int k = 0; k < FS::G; ++k) {
+      // features c, zt, n and the opacity to the planes c, opacity, zt, n
+      const int f = f0 + k, p = f < 3 ? f : f < 7 ? f + 1 : 3;
+      out[p * plane + px] = f < 3 ? fmaf(Tend, f == 0 ? bg[0] : f == 1 ? bg[1] : bg[2], acc[k]) : acc[k];
     }
+  }
+  if (wave == 0 && c.inside && keeps_pixel_state(L)) {
+    const size_t g = (size_t)pix_base + px;
+    last_out[g] = last;
+    tlast_out[g] = Tb;
   }
 }
 
@@ -339,13 +372,13 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   int last = -1;
   float Tb = 1.0f;
   if (recompute) {
-    float T = 1.0f, O = 0.0f;
-    float acc[7];
+    float T = 1.0f;
+    float acc[FeatSums<NWV>::G];
     uint32_t nb_unused = 0;
     RecPipe<CHB, NT> rq;
     if (start < end) rq.fetch_idx(srec, start, end - 1);
-    forward_sweep<NWV, CHB>(rq, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
-                            hmask, feat, &done_mask, T, Tb, O, acc, last, false, nb_unused);
+    forward_sweep<NWV, CHB, false>(rq, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, abuf, pm,
+                                   hmask, feat, &done_mask, T, Tb, last, nb_unused, acc);
     if (wave == 0) {
       const uint32_t w = wave_max((uint32_t)(last + 1 > (int)start ? last + 1 : (int)start));
       if (lane == 63u) smax = (int)w;

@@ -24,6 +24,14 @@ __device__ __forceinline__ void load_recs(ViewRec* recs, const ViewRec* __restri
   }
 }
 
+// What the forward's evaluation needs of a record: all but the features,
+// which go to a table of their own.
+struct alignas(16) EvalRec {
+  float px[4], py[4], iz[4], f[4], rD[4];
+  uint32_t rx, ry, span[2];
+};
+static_assert(sizeof(EvalRec) == 96 && offsetof(EvalRec, rx) == 80, "six 16-byte parts");
+
 __device__ __forceinline__ bool has_pixel(const ViewRec& R, int i, int j) {
   int i0, i1, j0, j1;
   unpack_rect(R, i0, i1, j0, j1);
@@ -97,7 +105,8 @@ __device__ __forceinline__ void store_entry_grads(const ViewRec* recs, const flo
 // workgroup's lanes take consecutive pairs.
 // ---------------------------------------------------------------------------
 // Pixels of the tile (bit = row-major local index) inside R's rectangle.
-__device__ __forceinline__ uint64_t rect_mask(const ViewRec& R, const Tile8& c) {
+template <class Rec>
+__device__ __forceinline__ uint64_t rect_mask(const Rec& R, const Tile8& c) {
   int i0, i1, j0, j1;
   unpack_rect(R, i0, i1, j0, j1);
   const int x0 = max(i0 - c.tx * 8, 0), x1 = min(i1 - c.tx * 8, 7);
@@ -109,7 +118,8 @@ __device__ __forceinline__ uint64_t rect_mask(const ViewRec& R, const Tile8& c) 
 }
 
 // Of those, the pixels that R's hull may cover (its spans).
-__device__ __forceinline__ uint64_t hull_mask(const ViewRec& R, const Tile8& c) {
+template <class Rec>
+__device__ __forceinline__ uint64_t hull_mask(const Rec& R, const Tile8& c) {
   int i0, i1, j0, j1;
   unpack_rect(R, i0, i1, j0, j1);
   const int sx = span_shift(i1 - i0 + 1, 4), sy = span_shift(j1 - j0 + 1, 3);
@@ -241,8 +251,8 @@ __device__ __forceinline__ void pair_map(int n, uint64_t m_e, PairMap<CH>& M) {
 
 // Wave 0, lane e < n: entry e's pairs are the pixels its hull may cover, in
 // live_e (the pixels that still take part for that entry).
-template <int CH>
-__device__ __forceinline__ void chunk_pairs(const ViewRec* recs, int n, const Tile8& c, uint64_t live_e,
+template <int CH, class Rec>
+__device__ __forceinline__ void chunk_pairs(const Rec* recs, int n, const Tile8& c, uint64_t live_e,
                                             PairMap<CH>& M) {
   const int lane = threadIdx.x & 63;
   pair_map<CH>(n, lane < n ? hull_mask(recs[lane], c) & live_e : 0ull, M);
@@ -312,6 +322,33 @@ struct RecPipe {
   // their own, whose per-lane gathers have no bank conflicts.  With ridx, so
   // does each record's index (what a chunk needs of srec later comes from LDS
   // then, not from a global load on its critical path).
+  __device__ __forceinline__ void store(EvalRec* recs, int n, float (*feat)[CH]) const {
+#pragma unroll
+    for (int j = 0; j < PQ; ++j) {
+      const int q = (int)threadIdx.x + j * NT;
+      if (q < n * 8) {
+        const int e = q >> 3, part = q & 7;
+        float4* d = reinterpret_cast<float4*>(&recs[e]);
+        if (part < 5) {
+          d[part] = make_float4(vx[j], vy[j], vz[j], vw[j]);
+        } else if (part == 5) {
+          feat[0][e] = vx[j];
+          feat[1][e] = vy[j];
+          feat[2][e] = vz[j];
+          feat[3][e] = vw[j];
+        } else if (part == 6) {
+          feat[4][e] = vx[j];
+          feat[5][e] = vy[j];
+          feat[6][e] = vz[j];
+          recs[e].rx = __float_as_uint(vw[j]);
+        } else {
+          recs[e].ry = __float_as_uint(vx[j]);
+          recs[e].span[0] = __float_as_uint(vy[j]);
+          recs[e].span[1] = __float_as_uint(vz[j]);
+        }
+      }
+    }
+  }
   __device__ __forceinline__ void store(ViewRec* recs, int n, float (*feat)[CH], uint32_t* ridx = nullptr) const {
 #pragma unroll
     for (int j = 0; j < PQ; ++j) {

@@ -185,7 +185,8 @@ struct PixHit {
   int faces;       // entry face | exit face << 2
 };
 
-__device__ __forceinline__ bool pixel_hit(const ViewRec& r, float qx, float qy, float s, PixHit& h) {
+template <class Rec>
+__device__ __forceinline__ bool pixel_hit(const Rec& r, float qx, float qy, float s, PixHit& h) {
   float ax[4], ay[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -274,7 +275,8 @@ __device__ __forceinline__ bool pixel_hit(const ViewRec& r, float qx, float qy, 
   return lane_bit(two);
 }
 
-__device__ __forceinline__ void unpack_rect(const ViewRec& r, int& i0, int& i1, int& j0, int& j1) {
+template <class Rec>
+__device__ __forceinline__ void unpack_rect(const Rec& r, int& i0, int& i1, int& j0, int& j1) {
   i0 = (int)(r.rx & 0xffffu);
   i1 = (int)(r.rx >> 16);
   j0 = (int)(r.ry & 0xffffu);
