@@ -383,7 +383,7 @@ static_assert(sizeof(BinHash) <= 256 * PROJ_STRIDE * 16, "the hash takes the rec
 static_assert(sizeof(TetRec) == 6 * 16 && sizeof(ViewRec) == 8 * 16, "record sizes in 16-byte units");
 static_assert(BIN_SLOTS == 1u << 10, "the tile hash keeps 10 bits");
 
-__global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2, int th_log2) {
+__global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2, int th_log2, float alpha_min) {
   DevHeader* hdr = at<DevHeader>(ws, L.o_hdr);
   const DevView* vw = at<const DevView>(ws, L.o_view);
   const int32_t* kbase = at<const int32_t>(ws, L.o_scene_kept_base);
@@ -477,7 +477,9 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
           R.n[0] = T.n[0]; R.n[1] = T.n[1]; R.n[2] = T.n[2];
           R.rx = (uint32_t)i0 | ((uint32_t)i1 << 16);
           R.ry = (uint32_t)j0 | ((uint32_t)j1 << 16);
-          hull_spans(px, py, D, fmaxf(xmax - xmin, ymax - ymin), i0, i1, j0, j1, R.span);
+          const float ext = fmaxf(xmax - xmin, ymax - ymin);
+          hull_spans(px, py, D, ext, i0, i1, j0, j1, R.span);
+          if (never_blends(X, Y, Z, T.f, D, ext, V.s, alpha_min)) R.span[0] = R.span[1] = SPAN_NONE;
           R.entry0 = 0;
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];
@@ -573,7 +575,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
 hipError_t launch_project(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
   int twl = __builtin_ctz((unsigned)p.tile_w), thl = __builtin_ctz((unsigned)p.tile_h);
   dim3 grid(512, (unsigned)L.nv);
-  k_project<<<grid, 256, 0, st>>>(ws, L, twl, thl);
+  k_project<<<grid, 256, 0, st>>>(ws, L, twl, thl, p.alpha_min);
   return hipGetLastError();
 }
 
