@@ -522,7 +522,7 @@ int render_forward(const render_scene* scenes, int n_scenes, const render_view* 
   TS_STAGE(RENDER_STAGE_PROJECT, launch_project(workspace, L, *params, st), "project and bin");
   TS_STAGE(RENDER_STAGE_SCAN, launch_tile_lists(workspace, L, st), "tile lists");
   TS_STAGE(RENDER_STAGE_EMIT, launch_emit(workspace, L, st), "emit and tile order");
-  TS_STAGE(RENDER_STAGE_DEPTH_SORT, launch_tile_depth_sort(workspace, L, st), "depth order in tiles");
+  TS_STAGE(RENDER_STAGE_DEPTH_SORT, launch_tile_depth_sort(workspace, L, params->window > 0 || multiwave(*params), st), "depth order in tiles");
   TS_STAGE(RENDER_STAGE_COMPOSITE,
            params->window > 0 ? launch_composite_win(workspace, L, with_waves(*params), st)
            : multiwave(*params) ? launch_composite_mw(workspace, L, with_waves(*params), st)

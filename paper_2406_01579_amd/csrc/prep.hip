@@ -401,6 +401,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
   const uint64_t cap = (uint64_t)L.entry_cap;
   __shared__ uint4 sbuf[256 * PROJ_STRIDE];
   __shared__ unsigned long long svalid[4];   // bit: the record covers a pixel
+  __shared__ unsigned long long sidle[4];    // bit: and cannot blend
   __shared__ uint32_t loff[256];
   __shared__ uint2 lrect[256];
   __shared__ uint32_t lds[8];
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
       for (int q = 0; q < 6; ++q) reinterpret_cast<uint4*>(&T)[q] = sbuf[t * PROJ_STRIDE + q];
     }
     __syncthreads();
-    uint32_t valid = 0, cnt = 0;
+    uint32_t valid = 0, cnt = 0, idle = 0;   // idle: none of the record's pixels can blend it
     if (t < nloc) {
       const int k = k0 + t;
       const int r = r0 + k;
@@ -478,8 +479,8 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
           R.rx = (uint32_t)i0 | ((uint32_t)i1 << 16);
           R.ry = (uint32_t)j0 | ((uint32_t)j1 << 16);
           const float ext = fmaxf(xmax - xmin, ymax - ymin);
-          hull_spans(px, py, D, ext, i0, i1, j0, j1, R.span);
-          if (never_blends(X, Y, Z, T.f, D, ext, V.s, alpha_min)) R.span[0] = R.span[1] = SPAN_NONE;
+          if (!hull_spans(px, py, D, ext, i0, i1, j0, j1, R.span)) idle = 1;
+          if (never_blends(X, Y, Z, T.f, D, ext, V.s, alpha_min)) idle = 1;
           R.entry0 = 0;
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];
@@ -494,7 +495,11 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
     loff[t] = off;
     if (valid) lrect[t] = make_uint2(sbuf[t * PROJ_STRIDE + 6].w, sbuf[t * PROJ_STRIDE + 7].x);
     const uint64_t vb = __ballot(valid != 0u);
-    if ((t & 63) == 0) svalid[t >> 6] = vb;
+    const uint64_t ib = __ballot(idle != 0u);
+    if ((t & 63) == 0) {
+      svalid[t >> 6] = vb;
+      sidle[t >> 6] = ib;
+    }
     // (the places' counter is not waited for before the records have gone out)
     unsigned long long place = 0ull;
     if (t == 0 && tot > 0u) place = atomicAdd((unsigned long long*)&hdr->entries_needed, (unsigned long long)tot);
@@ -565,7 +570,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
         if (e >= tot || d >= cap) continue;
         etile[d] = tile[i];
         erank[d] = rank[i] + (slot[i] < BIN_SLOTS ? H.cnt[slot[i]] : 0u);
-        erec[d] = (uint32_t)(r0 + k0) + q[i];
+        erec[d] = ((uint32_t)(r0 + k0) + q[i]) << 1 | (uint32_t)((sidle[q[i] >> 6] >> (q[i] & 63u)) & 1ull);
       }
     }
     __syncthreads();
@@ -900,7 +905,7 @@ __device__ __forceinline__ unsigned long long* lds_merge_sort(unsigned long long
   return k;
 }
 
-// The merge sort of a tile's list: records rv[0, n) by (zkey[record], record),
+// The merge sort of a tile's list: items rv[0, n) by (zkey[record], item),
 // through the scratch pair xk, xv, with the tile keys rk as scratch too
 // (rewritten by the caller).
 __device__ __forceinline__ void merge_sort_list(uint32_t* rk, uint32_t* rv, uint32_t* xk, uint32_t* xv,
@@ -909,7 +914,7 @@ __device__ __forceinline__ void merge_sort_list(uint32_t* rk, uint32_t* rv, uint
     const uint32_t m = min((uint32_t)DS_RUN, n - r0);
     for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) {
       const uint32_t r = rv[r0 + i];
-      lds[i] = ((unsigned long long)zkey[r] << 32) | r;
+      lds[i] = ((unsigned long long)zkey[r >> 1] << 32) | r;
     }
     __syncthreads();
     const unsigned long long* srt = lds_merge_sort(lds, lds + DS_RUN, m);
@@ -1011,7 +1016,7 @@ __device__ __forceinline__ bool bucket_sort_list(uint32_t* rv, const uint32_t* z
   for (int i = 0; i < DS_PER; ++i) {
     if (256u * i >= n) break;
     const bool in = t + 256u * i < n;
-    z[i] = in ? zkey[r[i]] : 0u;
+    z[i] = in ? zkey[r[i] >> 1] : 0u;
     lo = min(lo, in ? z[i] : 0xffffffffu);
     hi = max(hi, in ? z[i] : 0u);
   }
@@ -1043,7 +1048,7 @@ __device__ __forceinline__ bool bucket_sort_list(uint32_t* rv, const uint32_t* z
                            ((unsigned long long)z[i] << 32) | r[i]);
   }
   __syncthreads();
-  // the records in order, staged in LDS and written out contiguously
+  // the records in order, left in LDS
   uint32_t* out = reinterpret_cast<uint32_t*>(S.key);
 #pragma unroll
   for (int i = 0; i < DS_PER; ++i) {
@@ -1051,7 +1056,6 @@ __device__ __forceinline__ bool bucket_sort_list(uint32_t* rv, const uint32_t* z
     if (t + 256u * i < n) out[rank[i]] = r[i];
   }
   __syncthreads();
-  for (uint32_t i = t; i < n; i += 256u) rv[i] = out[i];
   return true;
 }
 
@@ -1062,7 +1066,7 @@ __device__ __forceinline__ bool bucket_sort_long(uint32_t* rv, uint32_t* xk, uin
   const uint32_t t = threadIdx.x;
   uint32_t lo = 0xffffffffu, hi = 0u;
   for (uint32_t i = t; i < n; i += 256u) {
-    const uint32_t z = zkey[rv[i]];
+    const uint32_t z = zkey[rv[i] >> 1];
     xk[i] = z;
     lo = min(lo, z);
     hi = max(hi, z);
@@ -1105,30 +1109,66 @@ __device__ __forceinline__ bool bucket_sort_long(uint32_t* rv, uint32_t* xk, uin
   return true;
 }
 
-__global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L) {
+// An item of a list is its record's index, shifted up, and in bit 0 whether the
+// record cannot blend.  With blend_lists the records that can also go to a list
+// of their own (their index in the full list beside them), which the
+// compositing kernels walk: of a tile's entries half or more face away from the
+// camera or cover none of its pixels' centres, and a tile's walk is a serial
+// chain.
+__global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L, int blend_lists) {
   __shared__ DepthSort S;
   static_assert(DS_LIST >= 2 * DS_RUN, "the merge sort's two LDS buffers");
   const uint32_t n_empty = at<const uint32_t>(ws, L.o_tile_hist)[0];
   if (blockIdx.x >= (uint32_t)L.total_tiles - n_empty) return;
   const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
-  const uint32_t s0 = sl.start, n = sl.end - sl.start;
+  const uint32_t s0 = sl.start, n = sl.end - sl.start, t = threadIdx.x;
   uint32_t* rk = at<uint32_t>(ws, sorted_tile_keys(L)) + s0;       // result pair: tile keys, records
   uint32_t* rv = at<uint32_t>(ws, sorted_entry_records(L)) + s0;
   const uint32_t* zkey = at<const uint32_t>(ws, L.o_key1a);        // depth bits per record
-  const bool res_a = sorted_entry_records(L) == L.o_val2a;         // scratch pair: the other buffers
-  uint32_t* xk = at<uint32_t>(ws, res_a ? L.o_key2b : L.o_key2a) + s0;
-  uint32_t* xv = at<uint32_t>(ws, res_a ? L.o_val2b : L.o_val2a) + s0;
+  // scratch pair, then the blend lists
+  uint32_t* xk = at<uint32_t>(ws, blend_entry_index(L)) + s0;
+  uint32_t* xv = at<uint32_t>(ws, blend_entry_records(L)) + s0;
+  const uint32_t* src = rv;
   if (n > 1u) {
-    const bool done = n <= (uint32_t)DS_LIST ? bucket_sort_list(rv, zkey, n, S)
-                                             : bucket_sort_long(rv, xk, xv, zkey, n, S);
+    bool done;
+    if (n <= (uint32_t)DS_LIST) {
+      done = bucket_sort_list(rv, zkey, n, S);
+      if (done) src = reinterpret_cast<const uint32_t*>(S.key);
+    } else {
+      done = bucket_sort_long(rv, xk, xv, zkey, n, S);
+    }
     if (!done) merge_sort_list(rk, rv, xk, xv, zkey, n, S.key);
   }
-  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) rk[i] = sl.tile;   // the list's tile keys
+  __syncthreads();
+  uint32_t m = 0u;   // of the blend list so far
+  for (uint32_t i0 = 0; i0 < n; i0 += 256u) {
+    const uint32_t i = i0 + t, v = i < n ? src[i] : 1u;
+    if (i < n) {
+      rv[i] = v >> 1;
+      rk[i] = sl.tile;   // the list's tile keys
+    }
+    if (!blend_lists) continue;
+    const uint64_t b = __ballot((v & 1u) == 0u);
+    if ((t & 63u) == 0u) S.red[t >> 6] = (uint32_t)__popcll(b);
+    __syncthreads();
+    uint32_t o = m + (uint32_t)__popcll(b & ((1ull << (t & 63u)) - 1ull));
+#pragma unroll
+    for (uint32_t w = 0; w < 4u; ++w) {
+      o += w < t >> 6 ? S.red[w] : 0u;
+      m += S.red[w];
+    }
+    if ((v & 1u) == 0u) {
+      xv[o] = v >> 1;
+      xk[o] = s0 + i;
+    }
+    __syncthreads();
+  }
+  if (blend_lists && t == 0u) at<TileSlot>(ws, L.o_tile_order)[blockIdx.x].end = s0 + m;
 }
 
-hipError_t launch_tile_depth_sort(void* ws, const Layout& L, hipStream_t st) {
+hipError_t launch_tile_depth_sort(void* ws, const Layout& L, bool blend_lists, hipStream_t st) {
   if (L.total_tiles == 0) return hipSuccess;
-  k_tile_depth_sort<<<(unsigned)L.total_tiles, 256, 0, st>>>(ws, L);
+  k_tile_depth_sort<<<(unsigned)L.total_tiles, 256, 0, st>>>(ws, L, blend_lists ? 1 : 0);
   return hipGetLastError();
 }
 

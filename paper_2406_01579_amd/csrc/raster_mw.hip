@@ -198,7 +198,7 @@ template <int NWV, int CHN>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_composite_mw(void* ws, Layout L, float alpha_min, float alpha_clamp,
                                                            float t_min) {
   const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* srec = at<const uint32_t>(ws, sorted_entry_records(L));
+  const uint32_t* srec = at<const uint32_t>(ws, blend_entry_records(L));
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
   int32_t* last_out = at<int32_t>(ws, L.o_last);
   float* tlast_out = at<float>(ws, L.o_tlast);
@@ -212,12 +212,12 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
 
   // a tile has some two chunks, so the chain of loads before the first counts:
   // the slot, then the first records' indexes, then whatever the view gives
-  const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
+  const TileSlot sl = tile_slot(at<const TileSlot>(ws, L.o_tile_order));
   // the tiles with an empty list take the last slots (length bucket 0):
   // workgroups past the others write their background, EMPTY_PER_WG tiles
   // each, and the rest of the grid leaves at once
   {
-    const uint32_t n_empty = at<const uint32_t>(ws, L.o_tile_hist)[0];
+    const uint32_t n_empty = *cmem(at<const uint32_t>(ws, L.o_tile_hist));
     const uint32_t n_work = (uint32_t)L.total_tiles - n_empty;
     if (blockIdx.x >= n_work) {
       const uint32_t first = n_work + (blockIdx.x - n_work) * EMPTY_PER_WG;
@@ -233,12 +233,12 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   const Tile8 c = tile8(vw, sl);
   ps.store(pm);
   for (int q = threadIdx.x; q < 2 * CHN; q += 64 * NWV) feat[q < CHN ? FEATS - 1 : 2 * FEATS - 1][q % CHN] = 1.0f;
-  const DevView& V = vw[c.view];
-  const float s = uniform_f(V.s);
+  const auto& V = cmem(vw)[c.view];
+  const float s = V.s;
   // what the end needs of the view, loaded here (not behind the sweep's stores)
   const size_t plane = (size_t)V.W * V.H;
   const size_t px = (size_t)c.j * V.W + c.i;
-  const float bg[3] = {uniform_f(V.bg[0]), uniform_f(V.bg[1]), uniform_f(V.bg[2])};
+  const float bg[3] = {V.bg[0], V.bg[1], V.bg[2]};
   const int32_t pix_base = V.pix_base;
   auto* out = gmem(V.out);
   const uint32_t start = c.start, end = c.end;
@@ -251,6 +251,13 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
   forward_sweep<NWV, CHN, true>(rp, vrec, srec, start, end, c, s, alpha_min, alpha_clamp, t_min, recs, alds, pm, hm,
                                 feat, &done_mask, T, Tb, last, nblend, acc,
                                 L.o_bmask ? at<unsigned long long>(ws, L.o_bmask) : nullptr, bml);
+  // the pixel's state, before the atomics below (a load after them would be
+  // waited for with them, 2 us of a tile's 14)
+  if ((threadIdx.x >> 6) == 0 && c.inside && keeps_pixel_state(L)) {
+    const size_t g = (size_t)pix_base + px;
+    last_out[g] = last < 0 ? -1 : (int)at<const uint32_t>(ws, blend_entry_index(L))[last];
+    tlast_out[g] = Tb;
+  }
   if ((threadIdx.x >> 6) == 0) {
     // end of the tile's blended prefix: where the backward starts its walk
     const uint32_t pend = wave_max((uint32_t)(last + 1 > (int)start ? last + 1 : (int)start));
@@ -282,11 +289,6 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(5, 8))
       out[p * plane + px] = f < 3 ? fmaf(Tend, f == 0 ? bg[0] : f == 1 ? bg[1] : bg[2], acc[k]) : acc[k];
     }
   }
-  if (wave == 0 && c.inside && keeps_pixel_state(L)) {
-    const size_t g = (size_t)pix_base + px;
-    last_out[g] = last;
-    tlast_out[g] = Tb;
-  }
 }
 
 // Backward, walk and recurrence: per chunk, coverage and Eq. 1 of every
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   static_assert(CHB <= 32, "a pixel's chunk candidates are a 32-bit mask");
   constexpr int NT = 64 * NWV;
   const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* srec = at<const uint32_t>(ws, sorted_entry_records(L));
+  const uint32_t* srec = at<const uint32_t>(ws, blend_entry_records(L));
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
   const float* tlast_in = at<const float>(ws, L.o_tlast);
   const unsigned long long* bmask = at<const unsigned long long>(ws, L.o_bmask);
@@ -325,11 +327,11 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   // dispatch order by the length the forward walked (longest first); the
   // tiles where nothing was blended come last and leave at once
   const TileSlot* bslots = at<const TileSlot>(ws, L.o_bwd_order);
-  const TileSlot sl = bslots[blockIdx.x];
-  const uint32_t pend_f = at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x];
+  const TileSlot sl = tile_slot(bslots);
+  const uint32_t pend_f = cmem(at<const uint32_t>(ws, L.o_bwd_pend))[blockIdx.x];
   // where this tile's pairs go
-  uint32_t pair_run = at<const uint32_t>(ws, L.o_bwd_base)[blockIdx.x];
-  if (!recompute && (blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work || pend_f == sl.start)) return;
+  uint32_t pair_run = cmem(at<const uint32_t>(ws, L.o_bwd_base))[blockIdx.x];
+  if (!recompute && (blockIdx.x >= cmem(at<const DevHeader>(ws, L.o_hdr))->bwd_work || pend_f == sl.start)) return;
   const uint32_t start = sl.start, end = sl.end;
   const unsigned lane = threadIdx.x & 63u;
   const int wave = threadIdx.x >> 6;
@@ -359,8 +361,8 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_mw(void* ws, Layout 
   PairSelect<CHB, NT> ps;
   ps.load();
   const Tile8 c = tile8(vw, sl);
-  const DevView& V = vw[c.view];
-  const float s = uniform_f(V.s);
+  const auto& V = cmem(vw)[c.view];
+  const float s = V.s;
   const size_t plane = (size_t)V.W * V.H;
   const size_t px = c.inside ? (size_t)c.j * V.W + c.i : 0;
   const float bg[3] = {V.bg[0], V.bg[1], V.bg[2]};

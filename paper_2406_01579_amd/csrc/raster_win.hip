@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
                                                             float t_min, int nw) {
   constexpr int NT = 64 * NWV;
   const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* srec = at<const uint32_t>(ws, sorted_entry_records(L));
+  const uint32_t* srec = at<const uint32_t>(ws, blend_entry_records(L));
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
   int32_t* last_out = at<int32_t>(ws, L.o_last);
   float* tlast_out = at<float>(ws, L.o_tlast);
@@ -127,12 +127,15 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
   __shared__ float pay[WS][8][64];      // per slot: alpha, c[3], zt, n[3]
   __shared__ unsigned long long done_mask;
 
+  const TileSlot sl = tile_slot(at<const TileSlot>(ws, L.o_tile_order));
   PairSelect<CHW, NT> ps;
+  RecPipe<CHW, NT> rp;
   ps.load();
-  const Tile8 c = tile8(vw, at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x]);
+  if (sl.start < sl.end) rp.fetch_idx(srec, sl.start, sl.end - 1);
+  const Tile8 c = tile8(vw, sl);
   ps.store(pm);
-  const DevView& V = vw[c.view];
-  const float s = uniform_f(V.s);
+  const auto& V = cmem(vw)[c.view];
+  const float s = V.s;
   const uint32_t start = c.start, end = c.end;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float qx = (float)c.i + 0.5f, qy = (float)c.j + 0.5f;
@@ -176,9 +179,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
     const unsigned long long m = __ballot(done);
     if (lane == 0) done_mask = m;
   }
-  RecPipe<CHW, NT> rp;
   if (start < end) {
-    rp.fetch_idx(srec, start, end - 1);
     rp.fetch_rec(vrec);
     rp.fetch_idx(srec, start + CHW, end - 1);
   }
@@ -237,24 +238,6 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
         blend(m, idx);
       }
     }
-    // the tile's blends and walked length: where the backward puts its
-    // records and pairs, and its dispatch order (a tile with no blend has
-    // nothing to walk back)
-    uint32_t nb = nblend;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nb += (uint32_t)__shfl_xor((int)nb, o, 64);
-    if (lane == 0) {
-      const uint32_t pend = nb > 0u ? walked : start;
-      at<uint32_t>(ws, L.o_tile_pend)[blockIdx.x] = pend;
-      at<uint32_t>(ws, L.o_slot_pairs)[blockIdx.x] = nb;
-      if (pend > start) {
-        uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
-        const int b = len_bucket(pend - start);
-        atomicAdd(bh + b, 1u);
-        atomicAdd(bh + 2 * TILE_BUCKETS + b, nb);
-        atomicAdd((unsigned long long*)&at<DevHeader>(ws, L.o_hdr)->pairs_needed, (unsigned long long)nb);
-      }
-    }
     if (c.inside) {
       const size_t plane = (size_t)V.W * V.H;
       const size_t px = (size_t)c.j * V.W + c.i;
@@ -269,8 +252,24 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_win(void* ws, Layout L, 
       out[7 * plane + px] = acc[6];
       if (keeps_pixel_state(L)) {
         const size_t g = (size_t)V.pix_base + px;
-        last_out[g] = last;
+        last_out[g] = last < 0 ? -1 : (int)at<const uint32_t>(ws, blend_entry_index(L))[last];
         tlast_out[g] = Tb;
+      }
+    }
+    // the tile's blends and walked length: where the backward puts its
+    // records and pairs, and its dispatch order (a tile with no blend has
+    // nothing to walk back)
+    const uint32_t nb = wave_scan_add(nblend);
+    if (lane == 63) {
+      const uint32_t pend = nb > 0u ? walked : start;
+      at<uint32_t>(ws, L.o_tile_pend)[blockIdx.x] = pend;
+      at<uint32_t>(ws, L.o_slot_pairs)[blockIdx.x] = nb;
+      if (pend > start) {
+        uint32_t* bh = at<uint32_t>(ws, L.o_bwd_hist);
+        const int b = len_bucket(pend - start);
+        atomicAdd(bh + b, 1u);
+        atomicAdd(bh + 2 * TILE_BUCKETS + b, nb);
+        atomicAdd((unsigned long long*)&at<DevHeader>(ws, L.o_hdr)->pairs_needed, (unsigned long long)nb);
       }
     }
   }
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   constexpr int NT = 64 * NWV;
   constexpr int CHB = CHW_BWD;
   const DevView* vw = at<const DevView>(ws, L.o_view);
-  const uint32_t* srec = at<const uint32_t>(ws, sorted_entry_records(L));
+  const uint32_t* srec = at<const uint32_t>(ws, blend_entry_records(L));
   const ViewRec* vrec = at<const ViewRec>(ws, L.o_vrec);
   const uint32_t* rfirst = at<const uint32_t>(ws, L.o_rfirst);
   uint4* blends = at<uint4>(ws, L.o_wblend);
@@ -320,20 +319,22 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
   __shared__ unsigned long long done_mask;
 
   const TileSlot* bslots = at<const TileSlot>(ws, L.o_bwd_order);
-  if (blockIdx.x >= at<const DevHeader>(ws, L.o_hdr)->bwd_work) return;
-  const uint32_t pend = at<const uint32_t>(ws, L.o_bwd_pend)[blockIdx.x];
-  if (pend == bslots[blockIdx.x].start) return;
+  const TileSlot sl = tile_slot(bslots);
+  const uint32_t pend = cmem(at<const uint32_t>(ws, L.o_bwd_pend))[blockIdx.x];
+  const uint32_t pair0 = cmem(at<const uint32_t>(ws, L.o_bwd_base))[blockIdx.x];   // the tile's first blend / pair
+  if (blockIdx.x >= cmem(at<const DevHeader>(ws, L.o_hdr))->bwd_work || pend == sl.start) return;
   PairSelect<CHB, NT> ps;
+  RecPipe<CHB, NT, true> rp;
   ps.load();
-  const Tile8 c = tile8(vw, bslots[blockIdx.x]);
+  rp.fetch_idx(srec, sl.start, pend - 1);
+  const Tile8 c = tile8(vw, sl);
   ps.store(pm);
-  const DevView& V = vw[c.view];
-  const float s = uniform_f(V.s);
+  const auto& V = cmem(vw)[c.view];
+  const float s = V.s;
   const uint32_t start = c.start, end = pend;   // the forward walked [start, pend)
   const unsigned lane = threadIdx.x & 63u;
   const int wave = threadIdx.x >> 6;
   const uint64_t lt = (1ull << lane) - 1ull;
-  const uint32_t pair0 = at<const uint32_t>(ws, L.o_bwd_base)[blockIdx.x];   // the tile's first blend / pair
   const uint32_t tile_xy = (uint32_t)c.tx | ((uint32_t)c.ty << 16);
   const size_t plane = (size_t)V.W * V.H;
   const size_t px = c.inside ? (size_t)c.j * V.W + c.i : 0;
@@ -384,9 +385,7 @@ __global__ __launch_bounds__(64 * NWV) void k_composite_bwd_win(void* ws, Layout
     const unsigned long long m = __ballot(done);
     if (lane == 0) done_mask = m;
   }
-  RecPipe<CHB, NT, true> rp;
   if (start < end) {
-    rp.fetch_idx(srec, start, end - 1);
     rp.fetch_rec(vrec, rfirst);
     rp.fetch_idx(srec, start + CHB, end - 1);
   }

@@ -46,6 +46,12 @@ struct Tile8 {
   uint32_t start, end;   // the tile's entry range
 };
 
+// The slot of a workgroup.
+__device__ __forceinline__ TileSlot tile_slot(const TileSlot* slots) {
+  const auto* p = cmem(slots) + blockIdx.x;
+  return TileSlot{p->tile, p->view, p->start, p->end};
+}
+
 // sl: the workgroup's slot.  (The caller loads it first of all and starts its
 // records' index loads from it before the view's fields are waited for here.)
 __device__ __forceinline__ Tile8 tile8(const DevView* vw, const TileSlot& sl) {
@@ -54,7 +60,7 @@ __device__ __forceinline__ Tile8 tile8(const DevView* vw, const TileSlot& sl) {
   c.view = (int)sl.view;
   c.start = sl.start;
   c.end = sl.end;
-  const DevView& V = vw[c.view];
+  const auto& V = cmem(vw)[c.view];
   const int lt = c.tile - V.tile_base;
   const int lane = threadIdx.x & 63;
   c.tx = lt % V.tiles_x;

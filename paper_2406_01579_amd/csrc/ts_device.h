@@ -78,6 +78,14 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p) {
   return (__attribute__((address_space(1))) T*)p;
 }
 
+// What a kernel only reads and one workgroup reads alike (its slot, its view),
+// through the constant space: by scalar loads into scalar registers, beside
+// the vector loads' counter instead of in it.
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* cmem(const T* p) {
+  return (const __attribute__((address_space(4))) T*)p;
+}
+
 // A tet's four vertex ids through a global-space pointer.
 __device__ __forceinline__ int4 load_tet(const int32_t* tets, size_t k) {
   const auto* t = gmem(tets) + 4 * k;
@@ -306,16 +314,16 @@ __device__ __forceinline__ int span_shift(int n, int units_log2) {
 // 0.52 to 0.61): forward 96 to 82 us at 4 x 512^2 and 870 to 757 us at
 // 8 x 1024^2, for 7 and 19 us more in the projection, which computes them.
 constexpr float SPAN_MARGIN = 0.05f;
-constexpr uint32_t SPAN_NONE = 0x01010101u;   // no column in any strip
 
-__device__ __forceinline__ void hull_spans(const float (&px)[4], const float (&py)[4], const float (&D)[4], float ext,
+// (false if no pixel is left)
+__device__ __forceinline__ bool hull_spans(const float (&px)[4], const float (&py)[4], const float (&D)[4], float ext,
                                            int i0, int i1, int j0, int j1, uint32_t (&span)[2]) {
   bool tight = ext < 65536.0f;
   const float thin = ext * ext * ext * (1.0f / (262144.0f * SPAN_MARGIN));
 #pragma unroll
   for (int F = 0; F < 4; ++F) tight = tight && (D[F] == 0.0f || fabsf(D[F]) >= thin);
   span[0] = span[1] = 0xf0f0f0f0u;   // every column
-  if (!tight) return;
+  if (!tight) return true;
   constexpr int EA[6] = {0, 0, 0, 1, 1, 2}, EB[6] = {1, 2, 3, 2, 3, 3};
   float dx[6], inv[6];
 #pragma unroll
@@ -326,6 +334,7 @@ __device__ __forceinline__ void hull_spans(const float (&px)[4], const float (&p
   const int sx = span_shift(i1 - i0 + 1, 4), sy = span_shift(j1 - j0 + 1, 3);
   const float fi0 = (float)i0, fi1 = (float)i1;
   uint32_t w[2] = {0u, 0u};
+  bool any = false;
   for (int k = 0; k < 8; ++k) {
     const int ja = j0 + (k << sy), jb = min(ja + (1 << sy) - 1, j1);
     if (ja > j1) break;
@@ -345,10 +354,12 @@ __device__ __forceinline__ void hull_spans(const float (&px)[4], const float (&p
     const float ca = fmaxf(ceilf(lo - (0.5f + SPAN_MARGIN)), fi0), cb = fminf(floorf(hi - (0.5f - SPAN_MARGIN)), fi1);
     uint32_t b = 1u;   // none
     if (ca <= cb) b = (uint32_t)(((int)ca - i0) >> sx) | (uint32_t)(((int)cb - i0) >> sx) << 4;
+    any = any || ca <= cb;
     w[k >> 2] |= b << (8 * (k & 3));
   }
   span[0] = w[0];
   span[1] = w[1];
+  return any;
 }
 
 // Whether no ray of the view can blend the tet: f does not fall along any ray

@@ -168,6 +168,12 @@ bool plan_layout(const render_scene* scenes, int ns, const render_view* views, i
 // and record; then key2b and val2b are the depth sort's scratch
 inline __host__ __device__ size_t sorted_tile_keys(const Layout& L) { return L.o_key2a; }
 inline __host__ __device__ size_t sorted_entry_records(const Layout& L) { return L.o_val2a; }
+// The lists as the kernels that share an 8x8 tile between waves walk them:
+// without the entries that cannot blend (see never_blends), each tile's from
+// its list's start on, to the end in its dispatch slot; and every such entry's
+// index in the full lists.
+inline __host__ __device__ size_t blend_entry_records(const Layout& L) { return L.o_val2b; }
+inline __host__ __device__ size_t blend_entry_index(const Layout& L) { return L.o_key2b; }
 
 // Place of a tile's entry counter: neighbouring tiles, whose counters the same
 // workgroups add to at the same time, lie in different cache lines (32 rows an
@@ -190,7 +196,7 @@ hipError_t launch_prefilter(void* ws, const Layout& L, const render_params& p, h
 hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, int nv, const int32_t* scene_views,
                                  void* ws, const Layout& L, const render_params& p, hipStream_t st);
 hipError_t launch_project(void* ws, const Layout& L, const render_params& p, hipStream_t st);
-hipError_t launch_tile_depth_sort(void* ws, const Layout& L, hipStream_t st);
+hipError_t launch_tile_depth_sort(void* ws, const Layout& L, bool blend_lists, hipStream_t st);
 hipError_t launch_tile_lists(void* ws, const Layout& L, hipStream_t st);
 // the entries into the tile lists, and the forward's dispatch order
 hipError_t launch_emit(void* ws, const Layout& L, hipStream_t st);
