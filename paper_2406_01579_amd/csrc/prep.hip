@@ -360,15 +360,16 @@ hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, 
 // record) from one global counter, and every entry its rank inside its tile's
 // list from the tile's counter; neighbouring records touch neighbouring tiles,
 // so the block's entries are counted per tile in an LDS hash first (integer
-// LDS adds are fast on this chip) and each tile costs one global atomic.  (tile, rank, record) go out per entry; once the tiles' counts are
-// scanned, an entry's place in the lists is its tile's start plus its rank.
+// LDS adds are fast on this chip) and each tile costs one global atomic.
+// (tile, rank, record and whether it cannot blend) go out per entry; once the
+// tiles' counts are scanned, an entry's place in the lists is its tile's start plus its rank.
 // The order inside a list is left to the atomics: the per-tile depth sort
 // imposes the final one.
 //   At the training shape (496k records, 1.75 M entries) this took the place of
 // a projection (27 us), a count of every tile's entries (25), the scan of the
 // counts (11), and a second pass that found every entry's tile again to place
-// it (29): now 49 us here and 10 us in k_emit; 8 x 1024^2: 142 + 91 + 114 to
-// 225 + 80 us.  Bound by the latency of a step's phases (two rounds of four
+// it (29): now 51 us here (with the hull spans and never_blends) and 10 us in
+// k_emit; 8 x 1024^2: 142 + 91 + 114 to 235 + 78 us.  Bound by the latency of a step's phases (two rounds of four
 // workgroups per CU there; LDS, 40 KB, sets the four).  Grouping a wave's
 // entries by ballots instead of the hash: 56 us, and 111 against 68 us for six
 // mixed scenes.
@@ -1112,9 +1113,11 @@ __device__ __forceinline__ bool bucket_sort_long(uint32_t* rv, uint32_t* xk, uin
 // An item of a list is its record's index, shifted up, and in bit 0 whether the
 // record cannot blend.  With blend_lists the records that can also go to a list
 // of their own (their index in the full list beside them), which the
-// compositing kernels walk: of a tile's entries half or more face away from the
-// camera or cover none of its pixels' centres, and a tile's walk is a serial
-// chain.
+// compositing kernels walk: half the entries or more face away from the camera
+// or cover no pixel's centre, and a tile's walk is a serial chain of chunks.
+// 19 to 21 us at 4 x 512^2, 122 to 140 at 8 x 1024^2, for 69 to 67 and 59 to 50
+// us in the two walks there (634 to 594 in the forward, the backward's pairs
+// bound at 590), 151 + 237 to 138 + 217 with the resort window of five.
 __global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L, int blend_lists) {
   __shared__ DepthSort S;
   static_assert(DS_LIST >= 2 * DS_RUN, "the merge sort's two LDS buffers");

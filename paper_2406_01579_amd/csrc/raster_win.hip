@@ -10,7 +10,7 @@
 // arrival order.
 //
 // Forward: as in the multi-wave kernels, all waves evaluate the chunk's packed
-// (entry, pixel) pairs -- pixel live and inside the entry's rectangle -- into
+// (entry, pixel) pairs -- pixel live and in the record's hull spans -- into
 // LDS (alpha and the entry depth) and mark each pixel's candidates; wave 0
 // runs the window over each pixel's candidates and the blend.  A lane's
 // window keys live in registers with static slot indices; each slot's payload
