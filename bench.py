@@ -52,17 +52,17 @@ TET_GRAD_RW_B = 2 * 92
 # waves per CU).  Valid only for the kernel sources with these digests;
 # reported as null once they change.
 MEASURED = {"sha256": {"paper_2406_01579_amd/csrc/raster_mw.hip":
-                       "7f36afe759b9aeec766c2ede0548d202ef80bc2fd31a3774392e682bc9030b53",
+                       "adceae9b5f68a1d70ef44fc078f117ea6f63bb468b1f9ad11cb64aba04f5efbd",
                        "paper_2406_01579_amd/csrc/ts_device.h":
-                       "1d460977169d1c084a1b36e572048bb91e1e0af4ea703fbdbf89cf80f8df331e",
+                       "91dfa6f4b65781ccefa39441a99441322b181261721fe70a0febd58b7259fcee",
                        "paper_2406_01579_amd/csrc/tile8.h":
-                       "b308d3fc0738dac2ddb4960fda876cb143f47fd59d7a375eaf162feb96fcdf03",
+                       "c1e24f1b20ee4ec5d6c600e500742674e61d6e8767507334a71ca7d76033690c",
                        "paper_2406_01579_amd/csrc/ts_internal.h":
-                       "9298470473e3e0da2dfd9da801ff73e14b0c9f9cda8d4121051e5e9ecd1f02d3"},
-            "composite_bwd": {"traffic": 255.8e6, "valu_issue_frac": 0.44, "lds_util": 0.1575,
-                              "lds_active_bytes": 1.1938e9, "lds_bank_conflict_frac": 0.275, "occupancy_pct": 37.2},
-            "composite": {"traffic": 125.3e6, "valu_issue_frac": 0.658, "lds_util": 0.185,
-                          "lds_active_bytes": 0.8162e9, "lds_bank_conflict_frac": 0.367, "occupancy_pct": 40.0}}
+                       "621ecdf71c3f71ae616a9355611c98d8345a17cb1c7f505a68d8a3636f7213b7"},
+            "composite_bwd": {"traffic": 235.0e6, "valu_issue_frac": 0.536, "lds_util": 0.179,
+                              "lds_active_bytes": 1.0922e9, "lds_bank_conflict_frac": 0.152, "occupancy_pct": 42.9},
+            "composite": {"traffic": 110.5e6, "valu_issue_frac": 0.488, "lds_util": 0.157,
+                          "lds_active_bytes": 0.6509e9, "lds_bank_conflict_frac": 0.191, "occupancy_pct": 42.6}}
 
 
 def measured_counters(kernel, args):
