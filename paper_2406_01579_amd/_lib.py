@@ -5,6 +5,8 @@ from __future__ import annotations
 import ctypes as C
 import os
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtetsplat.so")
 
@@ -110,6 +112,13 @@ def check(rc: int):
     if rc != RENDER_OK:
         raise RenderError(rc, lib().render_last_error().decode())
     return rc
+
+
+def current_stream(device: torch.device) -> int:
+    """Handle of the device's current stream in this thread, without the Stream
+    object that torch.cuda.current_stream makes (5 us of a call each)."""
+    i = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if i is None else i)
 
 
 def profile(enable: bool):

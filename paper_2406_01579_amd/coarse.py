@@ -20,7 +20,7 @@ from .frontend import Params, SceneT
 
 
 def _stream(dev):
-    return torch.cuda.current_stream(dev).cuda_stream
+    return _lib.current_stream(dev)
 
 
 def cube_grid(R: int, cube: torch.Tensor, with_tets: bool = True):

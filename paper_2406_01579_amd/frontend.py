@@ -87,18 +87,14 @@ class SceneT:
 def make_views(cams: np.ndarray, view_scene, outs) -> C.Array:
     cams = np.asarray(cams, np.float32)
     arr = (_lib.render_view * cams.shape[0])()
-    for v in range(cams.shape[0]):
-        c = cams[v]
+    for v, c in enumerate(cams.tolist()):   # (plain floats: numpy's scalars cost several times as much each)
         rv = arr[v]
         rv.scene = int(view_scene[v])
         rv.width, rv.height = int(c[0]), int(c[1])
-        for k in range(9):
-            rv.R[k] = float(c[2 + k])
-        for k in range(3):
-            rv.t[k] = float(c[11 + k])
-        rv.fx, rv.fy, rv.cx, rv.cy, rv.znear = (float(x) for x in c[14:19])
-        for k in range(3):
-            rv.bg[k] = float(c[19 + k])
+        rv.R[:] = c[2:11]
+        rv.t[:] = c[11:14]
+        rv.fx, rv.fy, rv.cx, rv.cy, rv.znear = c[14:19]
+        rv.bg[:] = c[19:22]
         rv.out = outs[v].data_ptr()
     return arr
 
@@ -149,7 +145,7 @@ class Renderer:
     # -- sizing ---------------------------------------------------------------
     def _signature(self, scenes, cams, view_scene):
         return (tuple((int(s.verts.shape[0]), int(s.tets.shape[0])) for s in scenes),
-                tuple((int(c[0]), int(c[1])) for c in np.asarray(cams)), tuple(int(x) for x in view_scene),
+                tuple((int(c[0]), int(c[1])) for c in np.asarray(cams).tolist()), tuple(int(x) for x in view_scene),
                 self.params.tile_w, self.params.tile_h)
 
     def workspace_bytes(self, scene_c, view_c, params_c, kept_cap, entry_cap) -> int:
@@ -178,7 +174,8 @@ class Renderer:
         nv = cams.shape[0]
         if view_scene is None:
             view_scene = np.zeros(nv, np.int32)
-        sizes = {(int(c[0]), int(c[1])) for c in cams}
+        wh = [(int(c[0]), int(c[1])) for c in cams.tolist()]
+        sizes = set(wh)
         if len(sizes) == 1:
             # one [nv, 8, H, W] tensor; the views are its slices
             W0, H0 = sizes.pop()
@@ -186,11 +183,11 @@ class Renderer:
             outs = list(stacked.unbind(0))
         else:
             stacked = None
-            outs = [torch.empty((8, int(c[1]), int(c[0])), device=self.device, dtype=torch.float32) for c in cams]
+            outs = [torch.empty((8, h, w), device=self.device, dtype=torch.float32) for w, h in wh]
         scene_c = (_lib.render_scene * len(scenes))(*[s.c() for s in scenes])
         view_c = make_views(cams, view_scene, outs)
         params_c = self.params.c()
-        st = torch.cuda.current_stream(self.device).cuda_stream if stream is None else stream
+        st = _lib.current_stream(self.device) if stream is None else stream
         sig = self._signature(scenes, cams, view_scene)
         kept_cap, entry_cap = self._caps.get(sig, (0, 0)) if caps is None else (int(caps[0]), int(caps[1]))
         if entry_cap == 0:
@@ -260,7 +257,7 @@ class Renderer:
             self._verify(p)
 
     def read_status(self, plan: Plan, stream=None) -> _lib.render_status:
-        st = torch.cuda.current_stream(self.device).cuda_stream if stream is None else stream
+        st = _lib.current_stream(self.device) if stream is None else stream
         s = _lib.render_status()
         check(_lib.lib().render_read_status(plan.workspace.data_ptr(), C.byref(s), st))
         plan.status = s
@@ -272,7 +269,7 @@ class Renderer:
             if getattr(self, "_pending", None) is plan:
                 self._pending = None
             self._verify(plan)
-        st = torch.cuda.current_stream(self.device).cuda_stream if stream is None else stream
+        st = _lib.current_stream(self.device) if stream is None else stream
         douts = [d.float().contiguous() for d in douts]
         dptr = (C.c_void_p * len(douts))(*[d.data_ptr() for d in douts])
         grads = []

@@ -31,7 +31,7 @@ def marching_tets(verts: torch.Tensor, sdf: torch.Tensor, tets: torch.Tensor, ed
     check(_lib.lib().render_marching_tets(verts.data_ptr(), tets.data_ptr(), sdf.data_ptr(), V, K,
                                           edges.buffer.data_ptr(), edges.count.data_ptr(), edges.capacity,
                                           out_v.data_ptr(), vcap, out_t.data_ptr(), tcap, counts.data_ptr(),
-                                          ws.data_ptr(), int(n.value), torch.cuda.current_stream(dev).cuda_stream))
+                                          ws.data_ptr(), int(n.value), _lib.current_stream(dev)))
     nv, nt = (int(x) for x in counts.cpu())
     if nv > vcap or nt > tcap:
         raise RuntimeError(f"marching tets needs {nv} vertices / {nt} triangles, capacities {vcap} / {tcap}")

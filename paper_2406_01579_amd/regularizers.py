@@ -17,7 +17,7 @@ from ._lib import check
 
 
 def _stream(device):
-    return torch.cuda.current_stream(device).cuda_stream
+    return _lib.current_stream(device)
 
 
 class MeshEdges:
