@@ -334,10 +334,20 @@ __device__ __forceinline__ uint32_t vs_item() {
 // counters whose totals go to the vertices' counters in runs of 16.  The
 // counts' scan gives every vertex a bucket, the pairs' upper vertices are
 // placed there, and each bucket is sorted and freed of the repeats that other
-// chunks brought (ranks by comparison; some 13 entries a bucket).  The sort of
-// all 6 K pairs by both vertices, which this replaces where the vertex arrays
-// fit the workspace (V <= 4 K, as when every vertex belongs to a tet), read and
-// wrote them six times: 870 us at 1.57 M tets, 230 us so.
+// chunks brought.  The sort of all 6 K pairs by both vertices, which this
+// replaces where mesh_edges_binned_fits says so, read and wrote them six times.
+//   A bucket of up to EU_SMALL entries (some 13 on a cube grid) is sorted by
+// comparison counts, several buckets at a time; one of up to EU_CAP by a bitonic
+// network in LDS; a longer one (a vertex that thousands of tets share) goes to
+// k_edge_long.  A pair that finds no slot in the set, or whose vertex finds no
+// place, goes out on its own; in tets of no order most pairs do.
+// 64^3 grid, 1.57 M tets: 787 us with the sort, 221 us so; its tets and vertices
+// in random order 1161 and 950 us; a 96^3 grid with every boundary face joined
+// to one point (a bucket of thousands) 3434 and 786 us.  Bound by k_edge_bin's
+// LDS set (101 us) and, without order, by an atomic per pair.  (Buckets past LDS
+// sorted by one block's merges instead: 13.5 ms for that point.)  What the sort
+// would still do faster is tets that all share one vertex, and few others: 60,000
+// of them 110 and 151 us, 500,000 394 and 845 us, a block's pass over a bucket.
 // ---------------------------------------------------------------------------
 constexpr int EB_T = 512;             // threads
 constexpr uint32_t EB_CHUNK = 512;    // tets per chunk
@@ -354,14 +364,24 @@ struct PairSet {
   uint32_t nitem, base;
 };
 
+// pair e of a tet, its vertices in order: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+__device__ __forceinline__ uint32_t pair_low(const int32_t (&v)[4], int e) {
+  return (uint32_t)min(v[e < 3 ? 0 : (e < 5 ? 1 : 2)], v[e == 0 ? 1 : (e == 1 || e == 3) ? 2 : 3]);
+}
+__device__ __forceinline__ uint32_t pair_high(const int32_t (&v)[4], int e) {
+  return (uint32_t)max(v[e < 3 ? 0 : (e < 5 ? 1 : 2)], v[e == 0 ? 1 : (e == 1 || e == 3) ? 2 : 3]);
+}
+
+// n_item: the list's pairs, and behind them the count of long buckets
 __global__ __launch_bounds__(RT) void k_edge_clear(uint32_t* cnt, uint32_t n, uint32_t* n_item) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_item = 0u;
+  if (blockIdx.x == 0 && threadIdx.x < 2) n_item[threadIdx.x] = 0u;
   for (uint32_t i = blockIdx.x * RT + threadIdx.x; i < n; i += gridDim.x * RT) cnt[i] = 0u;
 }
 
 // cnt[V + 1]: pairs per lower vertex (cleared); n_item: pairs listed (cleared)
 __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t K, int32_t V, uint32_t* cnt,
                                                    uint32_t* n_item, uint32_t* la, uint32_t* lb, uint32_t* lr) {
+  static_assert(EB_CHUNK == EB_T && EB_T == VS_T, "a tet per thread");
   __shared__ PairSet S;
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t nchunks = (K + EB_CHUNK - 1u) / EB_CHUNK, nj = (nchunks + 7u) / 8u * 8u;
@@ -373,17 +393,18 @@ __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t
     for (uint32_t i = t; i < VS_GROUPS * VS_RUN; i += EB_T) S.vcnt[i] = 0u;
     if (t == 0u) S.nitem = 0u;
     __syncthreads();
-    const uint32_t k1 = min(K, (ch + 1u) * EB_CHUNK);
-    for (uint32_t k = ch * EB_CHUNK + vs_item(); k < k1; k += EB_T) {
-      int32_t v[4];
-      if (!load_tet(tets, k, V, v)) continue;
+    const uint32_t k = ch * EB_CHUNK + vs_item();
+    int32_t v[4] = {0, 0, 0, 0};
+    const bool tet_ok = k < min(K, (ch + 1u) * EB_CHUNK) && load_tet(tets, k, V, v);
+    uint32_t own = 0u;   // bit e: pair e goes out on its own, with ow[e] its where (EB_GONE: no vertex place)
+    uint32_t ow[6] = {EB_GONE, EB_GONE, EB_GONE, EB_GONE, EB_GONE, EB_GONE};
+    if (tet_ok) {
 #pragma unroll
       for (int e = 0; e < 6; ++e) {
-        const int p = e < 3 ? 0 : (e < 5 ? 1 : 2), q = e == 0 ? 1 : (e == 1 || e == 3) ? 2 : 3;
-        const uint32_t a = (uint32_t)min(v[p], v[q]), b = (uint32_t)max(v[p], v[q]);
+        const uint32_t a = pair_low(v, e), b = pair_high(v, e);
         const uint64_t key = (uint64_t)a << 32 | b;
         uint32_t h = (a * 2654435761u ^ b * 2246822519u) >> 21;   // 11 bits: EB_SET
-        bool mine = true;   // no slot found: the pair goes out on its own
+        bool mine = true;
         uint32_t slot = EB_SET;
 #pragma unroll 1
         for (int pr = 0; pr < EB_PROBES; ++pr) {
@@ -402,15 +423,12 @@ __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t
           h = (h + 1u) & (EB_SET - 1u);
         }
         if (!mine) continue;
-        const int place = slot < EB_SET ? group_place(S.vkey, a) : -1;
-        if (place >= 0) {
-          S.where[slot] = (uint32_t)place << 16 | atomicAdd(&S.vcnt[place], 1u);
-        } else {
-          if (slot < EB_SET) S.where[slot] = EB_GONE;
-          const uint32_t i = atomicAdd(n_item, 1u);
-          la[i] = a;
-          lb[i] = b;
-          lr[i] = atomicAdd(&cnt[a], 1u);
+        const int place = group_place(S.vkey, a);
+        const uint32_t where = place >= 0 ? (uint32_t)place << 16 | atomicAdd(&S.vcnt[place], 1u) : EB_GONE;
+        if (slot < EB_SET) S.where[slot] = where;
+        if (slot == EB_SET || place < 0) {
+          own |= 1u << e;
+          ow[e] = where;
         }
       }
     }
@@ -429,6 +447,27 @@ __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t
 #pragma unroll
       for (int i = 0; i < NV; ++i) S.vcnt[t + EB_T * i] = c[i];
     }
+    // and those of the vertices without a place, a pair each, but the lanes that
+    // share the first one's vertex together (a vertex of very many tets)
+    uint32_t orank[6];
+    uint64_t same[6];
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      const bool gone = ((own >> e) & 1u) && ow[e] == EB_GONE;
+      const uint64_t m = __ballot(gone);
+      same[e] = 0ull;
+      if (m == 0ull) continue;
+      const int lead = __ffsll((unsigned long long)m) - 1;
+      const uint32_t a = pair_low(v, e), a0 = (uint32_t)__builtin_amdgcn_readlane((int)a, lead);
+      same[e] = __ballot(gone && a == a0);
+      if (gone && (a != a0 || (int)lane == lead)) orank[e] = atomicAdd(&cnt[a], a == a0 ? (uint32_t)__popcll(same[e]) : 1u);
+    }
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      if (same[e] == 0ull) continue;
+      const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)orank[e], __ffsll((unsigned long long)same[e]) - 1);
+      if ((same[e] >> lane) & 1ull) orank[e] = r0 + (uint32_t)__popcll(same[e] & ((1ull << lane) - 1ull));
+    }
     // the chunk's pairs into consecutive places of the list
     uint32_t at_[EB_SET / EB_T];
 #pragma unroll
@@ -441,6 +480,13 @@ __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t
       w = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
       at_[i] = out ? w + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : EB_GONE;
     }
+    uint32_t oat = 0u;
+    if (__ballot(own != 0u)) {
+      const uint32_t c = (uint32_t)__popc(own), x = wave_scan_add(c);
+      uint32_t w = 0u;
+      if (lane == 63u) w = atomicAdd(&S.nitem, x);
+      oat = (uint32_t)__builtin_amdgcn_readlane((int)w, 63) + x - c;
+    }
     __syncthreads();
     if (t == 0u) S.base = atomicAdd(n_item, S.nitem);
     __syncthreads();
@@ -451,6 +497,17 @@ __global__ __launch_bounds__(EB_T) void k_edge_bin(const int32_t* tets, uint32_t
       la[o] = (uint32_t)(S.pair[s] >> 32);
       lb[o] = (uint32_t)S.pair[s];
       lr[o] = S.vcnt[w >> 16] + (w & 0xffffu);
+    }
+    if (own != 0u) {
+      uint32_t o = S.base + oat;
+#pragma unroll
+      for (int e = 0; e < 6; ++e) {
+        if (!((own >> e) & 1u)) continue;
+        la[o] = pair_low(v, e);
+        lb[o] = pair_high(v, e);
+        lr[o] = ow[e] != EB_GONE ? S.vcnt[ow[e] >> 16] + (ow[e] & 0xffffu) : orank[e];
+        ++o;
+      }
     }
     __syncthreads();
   }
@@ -495,103 +552,119 @@ __global__ __launch_bounds__(RT) void k_edge_place(const uint32_t* start, const 
   for (uint32_t i = blockIdx.x * RT + threadIdx.x; i < n; i += gridDim.x * RT) bucket[start[la[i]] + lr[i]] = lb[i];
 }
 
-// Sort of a bucket too long for LDS, by one block: runs of EU_RUN sorted in
-// LDS by comparison counts, merged pairwise between x and y (a run's element
-// goes to its index plus the number of smaller, or for the right run not
-// larger, elements of the other); the result ends in x.
 constexpr uint32_t EU_CAP = 2048;     // entries of a block's buckets in LDS
 constexpr uint32_t EU_VERTS = 64;     // buckets per block
-constexpr uint32_t EU_RUN = 512;
-__device__ void sort_long_bucket(uint32_t* x, uint32_t* y, uint32_t n, uint32_t* lds) {
-  for (uint32_t r0 = 0; r0 < n; r0 += EU_RUN) {
-    const uint32_t m = min(EU_RUN, n - r0);
-    for (uint32_t i = threadIdx.x; i < m; i += RT) lds[i] = x[r0 + i];
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < m; i += RT) {
-      const uint32_t k = lds[i];
-      uint32_t p = 0;
-      for (uint32_t j = 0; j < m; ++j) p += (lds[j] < k || (lds[j] == k && j < i)) ? 1u : 0u;
-      x[r0 + p] = k;
-    }
-    __syncthreads();
-  }
-  uint32_t *a = x, *b = y;
-  for (uint32_t w = EU_RUN; w < n; w <<= 1) {
-    for (uint32_t i = threadIdx.x; i < n; i += RT) {
-      const uint32_t k = a[i], pair = i / (2u * w) * (2u * w);
-      const bool left = i - pair < w;
-      const uint32_t o0 = left ? min(pair + w, n) : pair, o1 = left ? min(pair + 2u * w, n) : pair + w;
-      uint32_t lo = o0, hi = o1;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (left ? a[mid] < k : a[mid] <= k) lo = mid + 1u;
-        else hi = mid;
-      }
-      b[left ? i + (lo - o0) : pair + (i - pair - w) + (lo - o0)] = k;
-    }
-    __syncthreads();
-    uint32_t* s = a; a = b; b = s;
-  }
-  if (a != x)
-    for (uint32_t i = threadIdx.x; i < n; i += RT) x[i] = a[i];
+constexpr uint32_t EU_SMALL = 64;     // entries of a bucket sorted by comparison counts
+constexpr int EU_PER = EU_CAP / RT;   // entries per thread
+static_assert(EU_SMALL <= 64, "a small bucket's bits lie in two words");
+
+// b[0, n), n <= EU_CAP, ascending (every thread; b is padded up to a power of two)
+__device__ __forceinline__ void bitonic_sort(uint32_t* b, uint32_t n) {
+  uint32_t p = 1u;
+  while (p < n) p <<= 1;
+  for (uint32_t i = n + threadIdx.x; i < p; i += RT) b[i] = ~0u;
   __syncthreads();
+  for (uint32_t k = 2u; k <= p; k <<= 1)
+    for (uint32_t j = k >> 1; j > 0u; j >>= 1) {
+      for (uint32_t q = threadIdx.x; q < p / 2u; q += RT) {
+        const uint32_t i = ((q & ~(j - 1u)) << 1) | (q & (j - 1u));
+        const uint32_t x = b[i], y = b[i + j];
+        if ((x > y) == ((i & k) == 0u)) {
+          b[i] = y;
+          b[i + j] = x;
+        }
+      }
+      __syncthreads();
+    }
 }
 
 // Each bucket sorted and freed of repeats in place; ucnt: what is left of it,
-// bsum: of the block's buckets.  start[V] is the end of the last bucket.
+// bsum: of the block's buckets.  start[V] is the end of the last bucket.  The
+// long ones are listed for k_edge_long.
 __global__ __launch_bounds__(RT) void k_edge_unique(const uint32_t* start, uint32_t V, uint32_t* bucket,
-                                                    uint32_t* scratch, uint32_t* ucnt, uint32_t* bsum) {
+                                                    uint32_t* n_long, uint32_t* long_v, uint32_t* ucnt,
+                                                    uint32_t* bsum) {
   __shared__ uint32_t b[EU_CAP];
-  __shared__ uint8_t owner[EU_CAP], first[EU_CAP];
+  __shared__ uint8_t owner[EU_CAP];
+  __shared__ uint64_t keep[EU_CAP / 64];
   __shared__ uint32_t s0[EU_VERTS + 1], u[EU_VERTS];
+  __shared__ uint32_t lds[RT / 64];
   const uint32_t v0 = blockIdx.x * EU_VERTS, nv = min(EU_VERTS, V - v0), t = threadIdx.x;
   if (t <= nv) s0[t] = start[v0 + t];
   if (t < EU_VERTS) u[t] = 0u;
   __syncthreads();
-  // as many buckets at a time as fit in LDS
   for (uint32_t g0 = 0; g0 < nv;) {
     uint32_t g1 = g0 + 1u;
-    while (g1 < nv && s0[g1 + 1u] - s0[g0] <= EU_CAP) ++g1;
-    const uint32_t e0 = s0[g0], n = s0[g1] - e0;
-    if (n > EU_CAP) {   // one long bucket
-      sort_long_bucket(bucket + e0, scratch + e0, n, b);
-      // repeats out, in chunks of the block's threads
-      __shared__ uint32_t lds[RT / 64];
+    const uint32_t e0 = s0[g0], n0 = s0[g1] - e0;
+    if (n0 > EU_CAP) {
+      if (t == 0u) long_v[atomicAdd(n_long, 1u)] = v0 + g0;
+      g0 = g1;
+      continue;
+    }
+    if (n0 > EU_SMALL) {
+      for (uint32_t i = t; i < n0; i += RT) b[i] = bucket[e0 + i];
+      bitonic_sort(b, n0);
       uint32_t run = 0;
-      for (uint32_t i0 = 0; i0 < n; i0 += RT) {
+      for (uint32_t i0 = 0; i0 < n0; i0 += RT) {
         const uint32_t i = i0 + t;
-        const uint32_t k = i < n ? bucket[e0 + i] : 0u;
-        const bool keep = i < n && (i == 0u || bucket[e0 + i - 1u] != k);
+        const bool keep = i < n0 && (i == 0u || b[i - 1u] != b[i]);
         uint32_t tot;
         const uint32_t p = run + block_scan_excl(keep ? 1u : 0u, lds, &tot);
-        if (keep) scratch[e0 + p] = k;
+        if (keep) bucket[e0 + p] = b[i];
         run += tot;
       }
-      __syncthreads();
-      for (uint32_t i = t; i < run; i += RT) bucket[e0 + i] = scratch[e0 + i];
       if (t == 0u) u[g0] = run;
       __syncthreads();
       g0 = g1;
       continue;
     }
+    // as many small buckets at a time as fit in LDS: an entry's place is the
+    // number of entries before it in the bucket's order
+    while (g1 < nv && s0[g1 + 1u] - e0 <= EU_CAP && s0[g1 + 1u] - s0[g1] <= EU_SMALL) ++g1;
+    const uint32_t n = s0[g1] - e0;
     for (uint32_t i = t; i < n; i += RT) b[i] = bucket[e0 + i];
     for (uint32_t g = g0 + t; g < g1; g += RT)
       for (uint32_t i = s0[g] - e0; i < s0[g + 1u] - e0; ++i) owner[i] = (uint8_t)g;
     __syncthreads();
-    for (uint32_t i = t; i < n; i += RT) {
-      bool f = true;
-      for (uint32_t j = s0[owner[i]] - e0; j < i; ++j) f = f && b[j] != b[i];
-      first[i] = f ? 1 : 0;
+    uint32_t x[EU_PER], p[EU_PER];
+#pragma unroll
+    for (int q = 0; q < EU_PER; ++q) {
+      const uint32_t i = t + RT * q;
+      if (i >= n) continue;
+      x[q] = b[i];
+      const uint32_t g = owner[i], i0 = s0[g] - e0, i1 = s0[g + 1u] - e0;
+      p[q] = i0;
+      for (uint32_t j = i0; j < i1; ++j) p[q] += (b[j] < x[q] || (b[j] == x[q] && j < i)) ? 1u : 0u;
     }
     __syncthreads();
-    for (uint32_t i = t; i < n; i += RT) {
-      if (!first[i]) continue;
-      const uint32_t g = owner[i], i0 = s0[g] - e0, i1 = s0[g + 1u] - e0;
-      uint32_t p = 0;
-      for (uint32_t j = i0; j < i1; ++j) p += (first[j] && b[j] < b[i]) ? 1u : 0u;
-      bucket[s0[g] + p] = b[i];
-      atomicAdd(&u[g], 1u);
+#pragma unroll
+    for (int q = 0; q < EU_PER; ++q)
+      if (t + RT * q < n) b[p[q]] = x[q];
+    __syncthreads();
+    // the first of every run of equal ones, as a bit per entry
+#pragma unroll
+    for (int q = 0; q < EU_PER; ++q) {
+      const uint32_t i = t + RT * q;
+      const bool first = i < n && (i == s0[owner[i]] - e0 || b[i - 1u] != b[i]);
+      const uint64_t m = __ballot(first);
+      if ((t & 63u) == 0u) keep[i >> 6] = m;
     }
+    __syncthreads();
+    // set bits of keep in [i0, i1), at most EU_SMALL apart
+    const auto kept = [&](uint32_t i0, uint32_t i1) {
+      const uint32_t w = i0 >> 6;
+      const uint64_t lo = keep[w] & (~0ull << (i0 & 63u)), hi = w + 1u < EU_CAP / 64u ? keep[w + 1u] : 0ull;
+      if (i1 <= 64u * w + 64u) return (uint32_t)__popcll(i1 > i0 ? lo & (~0ull >> (63u - ((i1 - 1u) & 63u))) : 0ull);
+      return (uint32_t)__popcll(lo) + (uint32_t)__popcll(hi & (~0ull >> (63u - ((i1 - 1u) & 63u))));
+    };
+#pragma unroll
+    for (int q = 0; q < EU_PER; ++q) {
+      const uint32_t i = t + RT * q;
+      if (i >= n || !((keep[i >> 6] >> (i & 63u)) & 1ull)) continue;
+      const uint32_t i0 = s0[owner[i]] - e0;
+      bucket[e0 + i0 + kept(i0, i)] = b[i];
+    }
+    for (uint32_t g = g0 + t; g < g1; g += RT) u[g] = kept(s0[g] - e0, s0[g + 1u] - e0);
     __syncthreads();
     g0 = g1;
   }
@@ -604,22 +677,107 @@ __global__ __launch_bounds__(RT) void k_edge_unique(const uint32_t* start, uint3
   }
 }
 
-__global__ __launch_bounds__(RT) void k_edge_out(const uint32_t* start, uint32_t V, const uint32_t* bucket,
-                                                 const uint32_t* ucnt, const uint32_t* bsum, int2* edges) {
-  __shared__ uint32_t off[EU_VERTS + 1], s0[EU_VERTS];
-  const uint32_t v0 = blockIdx.x * EU_VERTS, nv = min(EU_VERTS, V - v0), t = threadIdx.x;
-  if (t < 64u) {
-    const uint32_t c = t < nv ? ucnt[v0 + t] : 0u, x = wave_scan_add(c);
-    off[t + 1u] = x;
-    if (t == 0u) off[0] = 0u;
-    if (t < nv) s0[t] = start[v0 + t];
+// The buckets past EU_CAP: a bitmap of the upper vertices in LDS, EL_BITS of
+// them at a time, gives a bucket in order and without repeats in one pass over
+// its entries per window.  A block per bucket; the result goes to long_out, at
+// the bucket's own place, and ucnt and bsum as above.
+constexpr uint32_t EL_T = 1024;
+constexpr uint32_t EL_BITS = 1u << 20;   // 128 KB of LDS
+constexpr uint32_t EL_PER = 16;          // loads of a thread in flight together
+__global__ __launch_bounds__(EL_T) void k_edge_long(const uint32_t* start, uint32_t V, const uint32_t* bucket,
+                                                    uint32_t* long_out, const uint32_t* n_long,
+                                                    const uint32_t* long_v, uint32_t* ucnt, uint32_t* bsum) {
+  __shared__ uint32_t bits[EL_BITS / 32];
+  __shared__ uint32_t wsum[EL_T / 64];
+  const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, nl = *n_long;
+  for (uint32_t l = blockIdx.x; l < nl; l += gridDim.x) {
+    const uint32_t a = long_v[l], e0 = start[a], n = start[a + 1u] - e0;
+    uint32_t run = 0;
+    for (uint32_t w0 = a; w0 < V; w0 += EL_BITS) {   // (a tet with a repeated vertex has the pair (a, a))
+      const uint32_t nw = min(EL_BITS, V - w0), words = (nw + 31u) / 32u;
+      for (uint32_t i = t; i < words; i += EL_T) bits[i] = 0u;
+      __syncthreads();
+      for (uint32_t r0 = 0; r0 < n; r0 += EL_T * EL_PER) {
+        uint32_t x[EL_PER];   // (past the bucket: its last entry again; below the window: wraps past it)
+#pragma unroll
+        for (uint32_t q = 0; q < EL_PER; ++q) x[q] = bucket[e0 + min(r0 + q * EL_T + t, n - 1u)] - w0;
+#pragma unroll
+        for (uint32_t q = 0; q < EL_PER; ++q)
+          if (x[q] < nw) atomicOr(&bits[x[q] >> 5], 1u << (x[q] & 31u));
+      }
+      __syncthreads();
+      // a wave's words are consecutive, 64 of them a round
+      const uint32_t per = (words + EL_T - 1u) / EL_T * 64u, i0 = wave * per, i1 = min(i0 + per, words);
+      uint32_t c = 0u;
+      for (uint32_t i = i0 + lane; i < i1; i += 64u) c += (uint32_t)__popc(bits[i]);
+      c = wave_scan_add(c);
+      if (lane == 63u) wsum[wave] = c;
+      __syncthreads();
+      uint32_t o = run;
+#pragma unroll
+      for (uint32_t w = 0; w < EL_T / 64; ++w) {
+        o += w < wave ? wsum[w] : 0u;
+        run += wsum[w];
+      }
+      for (uint32_t i = i0; i < i1; i += 64u) {
+        uint32_t m = i + lane < i1 ? bits[i + lane] : 0u;
+        const uint32_t m1 = (uint32_t)__popc(m), x = wave_scan_add(m1);
+        uint32_t p = e0 + o + x - m1;
+        for (; m != 0u; m &= m - 1u) long_out[p++] = w0 + 32u * (i + lane) + (uint32_t)__ffs(m) - 1u;
+        o += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+      }
+      __syncthreads();
+    }
+    if (t == 0u) {
+      ucnt[a] = run;
+      atomicAdd(&bsum[a / EU_VERTS], run);
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const uint32_t n = off[EU_VERTS], o0 = bsum[blockIdx.x];
+}
+
+// The edges out, 64 vertices a block; a long bucket by EO_PARTS of the blocks
+// past those (256 threads would take 1.4 ms for a million edges).
+constexpr uint32_t EO_PARTS = 16, EO_LONG = 512;   // EO_LONG: blocks for the long buckets
+__global__ __launch_bounds__(RT) void k_edge_out(const uint32_t* start, uint32_t V, uint32_t nu, const uint32_t* bucket,
+                                                 const uint32_t* long_out, const uint32_t* n_long,
+                                                 const uint32_t* long_v, const uint32_t* ucnt, const uint32_t* bsum,
+                                                 int2* edges) {
+  __shared__ uint32_t off[EU_VERTS + 1], s0[EU_VERTS + 1];
+  const uint32_t t = threadIdx.x;
+  // a block's vertices: the bounds of their buckets and their edges' offsets
+  const auto load = [&](uint32_t blk) {
+    const uint32_t v0 = blk * EU_VERTS, nv = min(EU_VERTS, V - v0);
+    if (t < 64u) {
+      const uint32_t c = t < nv ? ucnt[v0 + t] : 0u, x = wave_scan_add(c);
+      off[t + 1u] = x;
+      if (t == 0u) off[0] = 0u;
+    }
+    if (t <= nv) s0[t] = start[v0 + t];
+    __syncthreads();
+  };
+  if (blockIdx.x >= nu) {
+    const uint32_t nw = *n_long * EO_PARTS;
+    for (uint32_t w = blockIdx.x - nu; w < nw; w += gridDim.x - nu) {
+      const uint32_t a = long_v[w / EO_PARTS], g = a % EU_VERTS;
+      load(a / EU_VERTS);
+      const uint32_t n = off[g + 1u] - off[g], o = bsum[a / EU_VERTS] + off[g], e0 = s0[g];
+      for (uint32_t i = w % EO_PARTS * RT + t; i < n; i += EO_PARTS * RT)
+        edges[o + i] = make_int2((int32_t)a, (int32_t)long_out[e0 + i]);
+      __syncthreads();
+    }
+    return;
+  }
+  load(blockIdx.x);
+  const uint32_t v0 = blockIdx.x * EU_VERTS, n = off[EU_VERTS], o0 = bsum[blockIdx.x];
   for (uint32_t i = t; i < n; i += RT) {
     uint32_t g = 0;   // the last vertex whose first edge is at or before i
 #pragma unroll
     for (uint32_t step = EU_VERTS / 2; step > 0u; step >>= 1) g = off[g + step] <= i ? g + step : g;
+    if (s0[g + 1u] - s0[g] > EU_CAP) {   // on to the end of the long bucket
+      i += (off[g + 1u] - 1u - i) / RT * RT;
+      continue;
+    }
     edges[o0 + i] = make_int2((int32_t)(v0 + g), (int32_t)bucket[s0[g] + (i - off[g])]);
   }
 }
@@ -1200,7 +1358,15 @@ EdgeLayout edge_layout(int32_t K) {
   return E;
 }
 
-// The binned build; V + 1 <= E.verts.
+// The binned build where the vertex arrays fit the workspace (sized by K; past
+// that most vertices belong to no tet) and the buckets are short on average: a
+// mesh has some six tets per vertex, and up to eight are allowed.  Random tets, a
+// million of them: at 6 per vertex 777 us against 778 us with the sort, at 11
+// 846 and 777, at 50 1590 and 608, where what counts is the buckets' own sort.
+static bool mesh_edges_binned_fits(uint64_t K, uint64_t V, const EdgeLayout& E) {
+  return V + 1 <= E.verts && K <= 8 * V;
+}
+
 static hipError_t mesh_edges_binned(const int32_t* tets, uint32_t K, uint32_t V, int32_t* edges, int32_t* n_edges,
                                     char* w, const EdgeLayout& E, hipStream_t st) {
   uint32_t* n_item = reinterpret_cast<uint32_t*>(w + E.o_n);
@@ -1223,18 +1389,24 @@ static hipError_t mesh_edges_binned(const int32_t* tets, uint32_t K, uint32_t V,
   if (K > 0)
     k_edge_place<<<(unsigned)std::min<uint64_t>((E.n + RT - 1) / RT, 4096), RT, 0, st>>>(start, n_item, la, lb, lr,
                                                                                          bucket);
-  if (nu > 0) k_edge_unique<<<nu, RT, 0, st>>>(start, V, bucket, la, ucnt, bsum);
+  // (the list's arrays have been read: la takes the long buckets' edges, lr their vertices)
+  const uint32_t nlong = (uint32_t)std::min<uint64_t>(E.n / EU_CAP, 256);   // 0: no bucket can be long
+  if (nu > 0) k_edge_unique<<<nu, RT, 0, st>>>(start, V, bucket, n_item + 1, lr, ucnt, bsum);
+  if (nu > 0 && nlong > 0)
+    k_edge_long<<<nlong, EL_T, 0, st>>>(start, V, bucket, la, n_item + 1, lr, ucnt, bsum);
   k_edge_spine<<<1, 1024, 0, st>>>(bsum, nu, n_edges);
-  if (nu > 0) k_edge_out<<<nu, RT, 0, st>>>(start, V, bucket, ucnt, bsum, reinterpret_cast<int2*>(edges));
+  if (nu > 0)
+    k_edge_out<<<nu + (nlong > 0 ? EO_LONG : 0u), RT, 0, st>>>(start, V, nu, bucket, la, n_item + 1, lr, ucnt, bsum,
+                                                               reinterpret_cast<int2*>(edges));
   return hipGetLastError();
 }
 
 hipError_t launch_mesh_edges(const int32_t* tets, int32_t K, int32_t V, int32_t* edges, int32_t* n_edges, void* ws,
                              const EdgeLayout& E, hipStream_t st) {
   char* w = static_cast<char*>(ws);
-  if ((uint64_t)V + 1 <= E.verts) return mesh_edges_binned(tets, (uint32_t)K, (uint32_t)V, edges, n_edges, w, E, st);
-  // more vertices than the workspace (sized by K) has room for: most belong to
-  // no tet.  The 6 K pairs sorted by b, then stably by a
+  if (mesh_edges_binned_fits((uint64_t)K, (uint64_t)V, E))
+    return mesh_edges_binned(tets, (uint32_t)K, (uint32_t)V, edges, n_edges, w, E, st);
+  // the 6 K pairs sorted by b, then stably by a
   uint32_t* n_dev = reinterpret_cast<uint32_t*>(w + E.o_n);
   uint32_t* ka = reinterpret_cast<uint32_t*>(w + E.o_ka);
   uint32_t* va = reinterpret_cast<uint32_t*>(w + E.o_va);
