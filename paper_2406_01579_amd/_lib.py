@@ -114,11 +114,18 @@ def check(rc: int):
     return rc
 
 
+# (a private function: where torch lacks it, the public one)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def current_stream(device: torch.device) -> int:
     """Handle of the device's current stream in this thread, without the Stream
-    object that torch.cuda.current_stream makes (5 us of a call each)."""
-    i = device.index
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if i is None else i)
+    object that torch.cuda.current_stream makes (5 us of a call each).  Any
+    other device is refused, as there: its tensors are not the kernels' to read."""
+    if device.type != "cuda":
+        raise ValueError(f"expected a cuda device, got {device}")
+    i = torch.cuda.current_device() if device.index is None else device.index
+    return _raw_stream(i) if _raw_stream is not None else torch.cuda.current_stream(i).cuda_stream
 
 
 def profile(enable: bool):
