@@ -410,6 +410,7 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
   BinHash& H = *reinterpret_cast<BinHash*>(sbuf);
   const int v = blockIdx.y;
   const DevView V = vw[v];
+  const float ifx = rcp(fabsf(V.fx)), ify = rcp(fabsf(V.fy));
   const int n = kcount[V.scene];
   const int r0 = rbase[v];
   const int kb = kbase[V.scene];
@@ -481,7 +482,8 @@ __global__ __launch_bounds__(256) void k_project(void* ws, Layout L, int tw_log2
           R.ry = (uint32_t)j0 | ((uint32_t)j1 << 16);
           const float ext = fmaxf(xmax - xmin, ymax - ymin);
           if (!hull_spans(px, py, D, ext, i0, i1, j0, j1, R.span)) idle = 1;
-          if (never_blends(X, Y, Z, T.f, D, ext, V.s, alpha_min)) idle = 1;
+          const float reach = fmaxf(1.0f, fmaxf(fmaxf(fabsf(xmin), fabsf(xmax)) * ifx, fmaxf(fabsf(ymin), fabsf(ymax)) * ify));
+          if (never_blends(X, Y, Z, T.f, D, ext, reach, V.s, alpha_min)) idle = 1;
           R.entry0 = 0;
 #pragma unroll
           for (int q = 0; q < 8; ++q) sbuf[t * PROJ_STRIDE + q] = reinterpret_cast<const uint4*>(&R)[q];

@@ -371,18 +371,26 @@ __device__ __forceinline__ bool hull_spans(const float (&px)[4], const float (&p
 // continuation to the camera: smallest at a vertex.  d is then at most
 // max(0, -min_k g . X_k) (Zmax / Zmin - 1), plus what g, computed in floats,
 // misses of the vertices' values (its residual r, once per face).
-//   The evaluation of a pair orders the two faces by depths that are rounded,
-// so a ray through less than 2^-21 of relative thickness may see them exchanged
-// and d with the other sign; where f falls so steeply (against s) that this
-// could blend, the tet is kept, as with ext^2 / |D| over 64 (the face weights'
-// own error).  NaNs compare false: kept.
+//   The evaluation of a pair rounds, and what that can add to d stands beside it:
+// the two interpolated values (8 rounding units of the largest |f| each, however
+// flat f is); the order and the place of the two faces, whose weights and
+// depths are off by the cross products' rounding over a face's area (thin:
+// hull extent^2 / least area; a ray through less than that of relative thickness
+// may see the faces exchanged and d with the other sign); the projected vertices
+// (reach: |pixel| / focal length), which move a tet's faces by more of its
+// height the flatter it is (e^3 / det).  The units of the last two are twice and
+// five times what random tets down to slivers were seen to need (none of 280 M
+// pairs near a projected edge would blend in a tet left out).  Where s makes
+// that matter, or thin is past 64, the tet is kept: 53.5 in 100 records of a
+// 64^3 grid at s = 320 are left out, 53.9 without these terms.  NaNs compare
+// false: kept.
 //   Half the kept tets around a surface face away.  Most are behind it, but
 // they are 19 to 22 in 100 of the pairs that were evaluated (64^3 grids with
 // noise, s = 320, from 2.5 away): forward 73 to 69 us at 4 x 512^2, 684 to 635
 // us at 8 x 1024^2, for 1 and 4 us of the projection; and half the entries of
 // the lists (see k_tile_depth_sort).
 __device__ __forceinline__ bool never_blends(const float (&X)[4], const float (&Y)[4], const float (&Z)[4],
-                                             const float (&f)[4], const float (&D)[4], float ext, float s,
+                                             const float (&f)[4], const float (&D)[4], float ext, float reach, float s,
                                              float alpha_min) {
   float ex[3], ey[3], ez[3], df[3];
 #pragma unroll
@@ -419,9 +427,17 @@ __device__ __forceinline__ bool never_blends(const float (&X)[4], const float (&
   const float zmin = fminf(fminf(Z[0], Z[1]), fminf(Z[2], Z[3])), zmax = fmaxf(fmaxf(Z[0], Z[1]), fmaxf(Z[2], Z[3]));
   const float zr = zmax * rcp(zmin);
   const float fall = fmaxf(0.0f, fmaf(Gabs, 0x1p-20f, r - (G0 + lo)));   // of f, per relative depth, at most
-  const float swapped = (fabsf(G0) + fmaxf(hi, -lo)) * zr * 0x1p-20f;
-  const float bound = fmaf(fall, zr - 1.0f + 0x1p-20f, 2.0f * r + swapped);
-  bool ok = alpha_min > 0.0f && zmin > 0.0f && s >= 0.0f && s * bound <= 0.5f * alpha_min;
+  float area = INFINITY, top = 0.0f;
+#pragma unroll
+  for (int F = 0; F < 4; ++F) {
+    area = fminf(area, D[F] != 0.0f ? fabsf(D[F]) : INFINITY);   // (a face without area is never hit)
+    top = fmaxf(top, fabsf(f[F]));
+  }
+  const float thin = ext * ext * rcp(area);
+  const float order = (fabsf(G0) + fmaxf(hi, -lo)) * zr * fmaf(thin, 0x1p-23f, 0x1p-20f);
+  const float moved = (fabsf(g[0]) + fabsf(g[1]) + fabsf(g[2])) * zmax * reach * (e * e * e) * fabsf(id) * 0x1p-25f;
+  const float bound = fmaf(fall, zr - 1.0f + 0x1p-20f, 2.0f * r + fmaf(top, 0x1p-20f, order + moved));
+  bool ok = alpha_min > 0.0f && zmin > 0.0f && s >= 0.0f && s * bound <= 0.95f * alpha_min;
 #pragma unroll
   for (int F = 0; F < 4; ++F) ok = ok && (D[F] == 0.0f || fabsf(D[F]) * 64.0f >= ext * ext);
   return ok;
