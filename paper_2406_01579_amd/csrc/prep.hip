@@ -250,7 +250,7 @@ __global__ __launch_bounds__(PF_THREADS) void k_pf_scatter(void* ws, Layout L, f
     }
   }
   if (b == 0) prefilter_totals(ws, L, lds);
-  if (b >= (int)L.pf_blocks) return;   // (no blocks of tets: block 0 only writes the totals)
+  if (b >= (int)L.pf_blocks) return;   // (these only clear; without tets block 0 also writes the totals)
   uint32_t part = 0;
   for (int j = threadIdx.x; j < b; j += PF_THREADS) part += cnt[j] & ~PF_INVALID;
   uint32_t before;
@@ -315,9 +315,16 @@ __global__ __launch_bounds__(PF_THREADS) void k_pf_scatter(void* ws, Layout L, f
   }
 }
 
+// The scatter's blocks: one per block of tets, more where those would be few for
+// the tile counters that it clears (16 words a thread).
+static unsigned pf_scatter_blocks(const Layout& L) {
+  const int64_t words = 32 * (int64_t)tile_counter_row(L);
+  return (unsigned)std::max(std::max<int64_t>(L.pf_blocks, 1), std::min<int64_t>(words / (16 * PF_THREADS), 1024));
+}
+
 hipError_t launch_prefilter(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
   if (L.pf_blocks > 0) k_pf_count<<<(unsigned)L.pf_blocks, PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
-  k_pf_scatter<<<(unsigned)std::max<int64_t>(L.pf_blocks, 1), PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
+  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
   return hipGetLastError();
 }
 
@@ -339,7 +346,7 @@ hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, 
   Blob b;
   std::memcpy(b.w, img.data(), img.size());
   k_pf_count_desc<<<(unsigned)L.pf_blocks, PF_THREADS, 0, st>>>(b, (int)words, ws, L, p.prefilter_tf);
-  k_pf_scatter<<<(unsigned)L.pf_blocks, PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
+  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
   return hipGetLastError();
 }
 
@@ -1128,60 +1135,67 @@ __device__ __forceinline__ bool bucket_sort_long(uint32_t* rv, uint32_t* xk, uin
 // 19 to 21 us at 4 x 512^2, 122 to 140 at 8 x 1024^2, for 69 to 67 and 59 to 50
 // us in the two walks there (634 to 594 in the forward, the backward's pairs
 // bound at 590), 151 + 237 to 138 + 217 with the resort window of five.
+//   Past DS_GRID lists a workgroup takes several, far apart in the dispatch order:
+// a workgroup per tile, most of which only leave, cost 97 us of a 4096^2 frame
+// (262k tiles) of an object a fifth as wide, 22 so.
+constexpr unsigned DS_GRID = 32768;
 __global__ __launch_bounds__(256) void k_tile_depth_sort(void* ws, Layout L, int blend_lists) {
   __shared__ DepthSort S;
   static_assert(DS_LIST >= 2 * DS_RUN, "the merge sort's two LDS buffers");
   const uint32_t n_empty = at<const uint32_t>(ws, L.o_tile_hist)[0];
-  if (blockIdx.x >= (uint32_t)L.total_tiles - n_empty) return;
-  const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[blockIdx.x];
-  const uint32_t s0 = sl.start, n = sl.end - sl.start, t = threadIdx.x;
-  uint32_t* rk = at<uint32_t>(ws, sorted_tile_keys(L)) + s0;       // result pair: tile keys, records
-  uint32_t* rv = at<uint32_t>(ws, sorted_entry_records(L)) + s0;
-  const uint32_t* zkey = at<const uint32_t>(ws, L.o_key1a);        // depth bits per record
-  // scratch pair, then the blend lists
-  uint32_t* xk = at<uint32_t>(ws, blend_entry_index(L)) + s0;
-  uint32_t* xv = at<uint32_t>(ws, blend_entry_records(L)) + s0;
-  const uint32_t* src = rv;
-  if (n > 1u) {
-    bool done;
-    if (n <= (uint32_t)DS_LIST) {
-      done = bucket_sort_list(rv, zkey, n, S);
-      if (done) src = reinterpret_cast<const uint32_t*>(S.key);
-    } else {
-      done = bucket_sort_long(rv, xk, xv, zkey, n, S);
+  const uint32_t t = threadIdx.x, n_work = (uint32_t)L.total_tiles - n_empty;
+  for (uint32_t slot = blockIdx.x; slot < n_work; slot += gridDim.x) {
+    const TileSlot sl = at<const TileSlot>(ws, L.o_tile_order)[slot];
+    const uint32_t s0 = sl.start, n = sl.end - sl.start;
+    uint32_t* rk = at<uint32_t>(ws, sorted_tile_keys(L)) + s0;       // result pair: tile keys, records
+    uint32_t* rv = at<uint32_t>(ws, sorted_entry_records(L)) + s0;
+    const uint32_t* zkey = at<const uint32_t>(ws, L.o_key1a);        // depth bits per record
+    // scratch pair, then the blend lists
+    uint32_t* xk = at<uint32_t>(ws, blend_entry_index(L)) + s0;
+    uint32_t* xv = at<uint32_t>(ws, blend_entry_records(L)) + s0;
+    const uint32_t* src = rv;
+    if (n > 1u) {
+      bool done;
+      if (n <= (uint32_t)DS_LIST) {
+        done = bucket_sort_list(rv, zkey, n, S);
+        if (done) src = reinterpret_cast<const uint32_t*>(S.key);
+      } else {
+        done = bucket_sort_long(rv, xk, xv, zkey, n, S);
+      }
+      if (!done) merge_sort_list(rk, rv, xk, xv, zkey, n, S.key);
     }
-    if (!done) merge_sort_list(rk, rv, xk, xv, zkey, n, S.key);
-  }
-  __syncthreads();
-  uint32_t m = 0u;   // of the blend list so far
-  for (uint32_t i0 = 0; i0 < n; i0 += 256u) {
-    const uint32_t i = i0 + t, v = i < n ? src[i] : 1u;
-    if (i < n) {
-      rv[i] = v >> 1;
-      rk[i] = sl.tile;   // the list's tile keys
-    }
-    if (!blend_lists) continue;
-    const uint64_t b = __ballot((v & 1u) == 0u);
-    if ((t & 63u) == 0u) S.red[t >> 6] = (uint32_t)__popcll(b);
     __syncthreads();
-    uint32_t o = m + (uint32_t)__popcll(b & ((1ull << (t & 63u)) - 1ull));
+    uint32_t m = 0u;   // of the blend list so far
+    for (uint32_t i0 = 0; i0 < n; i0 += 256u) {
+      const uint32_t i = i0 + t, v = i < n ? src[i] : 1u;
+      if (i < n) {
+        rv[i] = v >> 1;
+        rk[i] = sl.tile;   // the list's tile keys
+      }
+      if (!blend_lists) continue;
+      const uint64_t b = __ballot((v & 1u) == 0u);
+      if ((t & 63u) == 0u) S.red[t >> 6] = (uint32_t)__popcll(b);
+      __syncthreads();
+      uint32_t o = m + (uint32_t)__popcll(b & ((1ull << (t & 63u)) - 1ull));
 #pragma unroll
-    for (uint32_t w = 0; w < 4u; ++w) {
-      o += w < t >> 6 ? S.red[w] : 0u;
-      m += S.red[w];
+      for (uint32_t w = 0; w < 4u; ++w) {
+        o += w < t >> 6 ? S.red[w] : 0u;
+        m += S.red[w];
+      }
+      if ((v & 1u) == 0u) {
+        xv[o] = v >> 1;
+        xk[o] = s0 + i;
+      }
+      __syncthreads();
     }
-    if ((v & 1u) == 0u) {
-      xv[o] = v >> 1;
-      xk[o] = s0 + i;
-    }
-    __syncthreads();
+    if (blend_lists && t == 0u) at<TileSlot>(ws, L.o_tile_order)[slot].end = s0 + m;
+    __syncthreads();   // the next list takes the LDS
   }
-  if (blend_lists && t == 0u) at<TileSlot>(ws, L.o_tile_order)[blockIdx.x].end = s0 + m;
 }
 
 hipError_t launch_tile_depth_sort(void* ws, const Layout& L, bool blend_lists, hipStream_t st) {
   if (L.total_tiles == 0) return hipSuccess;
-  k_tile_depth_sort<<<(unsigned)L.total_tiles, 256, 0, st>>>(ws, L, blend_lists ? 1 : 0);
+  k_tile_depth_sort<<<std::min(working_tiles(L), DS_GRID), 256, 0, st>>>(ws, L, blend_lists ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -688,10 +688,10 @@ template <int NWV>
 static void launch_bwd_mw(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
   const int rc = (p.flags & RENDER_RECOMPUTE_STATE) ? 1 : 0;
   if (p.chunk_bwd == 16)
-    k_composite_bwd_mw<NWV, 16><<<(unsigned)L.total_tiles, 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
+    k_composite_bwd_mw<NWV, 16><<<working_tiles(L), 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
                                                                                p.t_min, rc);
   else
-    k_composite_bwd_mw<NWV, 32><<<(unsigned)L.total_tiles, 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
+    k_composite_bwd_mw<NWV, 32><<<working_tiles(L), 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
                                                                                p.t_min, rc);
 }
 

@@ -540,7 +540,7 @@ static void launch_fwd_win_ws(void* ws, const Layout& L, const render_params& p,
 }
 template <int NWV, int WS>
 static void launch_bwd_win_ws(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
-  k_composite_bwd_win<NWV, WS><<<(unsigned)L.total_tiles, 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
+  k_composite_bwd_win<NWV, WS><<<working_tiles(L), 64 * NWV, 0, st>>>(ws, L, p.alpha_min, p.alpha_clamp,
                                                                               p.t_min, p.window);
 }
 // the smallest slot count that holds N_w entries and one arrival

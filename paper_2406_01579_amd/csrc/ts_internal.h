@@ -186,6 +186,14 @@ inline __host__ __device__ uint32_t tile_counter(const Layout& L, uint32_t tile)
   return (tile & 31u) * (uint32_t)tile_counter_row(L) + (tile >> 5);
 }
 
+// Tiles that can have entries (the first ones of the dispatch orders): each has at
+// least one, and past the capacity all lists are empty.  What a kernel launches
+// of the others only leaves again, which in a mostly empty image adds up: one
+// frame of a small object at 4096^2 471 to 385 us, forward and backward 595 to 438.
+inline unsigned working_tiles(const Layout& L) {
+  return (unsigned)(L.total_tiles < L.entry_cap ? L.total_tiles : L.entry_cap);
+}
+
 template <class T>
 __host__ __device__ inline T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
