@@ -286,7 +286,8 @@ int render_profile_read(double* ms /* [RENDER_NSTAGES] */, int64_t* counts /* [R
  * a tet with an index outside [0, V) contributes no edge.  edges: device
  * int32 [6K][2] (6K pairs always suffice); n_edges: device int32, receives
  * the count.  Workspace from render_mesh_edges_workspace_size (device,
- * caller-owned).  Asynchronous on stream.  Built once per topology.
+ * caller-owned; 110 bytes per tet).  Asynchronous on stream.  Built once per
+ * topology.
  */
 int render_mesh_edges_workspace_size(int32_t K, size_t* bytes);
 int render_mesh_edges(const int32_t* tets, int32_t K, int32_t V, int32_t* edges, int32_t* n_edges,
@@ -388,7 +389,8 @@ int render_refit_cube(const float* bounds, const float* cube_in, int32_t R, floa
  *   capacities (then only the first `capacity` items are written);
  *   vert_capacity <= edge count and tri_capacity <= 2 K always suffice.
  * Tets with an index outside [0, V) give no triangle.  Asynchronous on
- * stream; workspace from render_marching_tets_workspace_size.
+ * stream; workspace from render_marching_tets_workspace_size (4.2 bytes per
+ * edge of the capacity and 4 per tet).
  */
 int render_marching_tets_workspace_size(int32_t K, int64_t edge_capacity, size_t* bytes);
 int render_marching_tets(const float* verts, const int32_t* tets, const float* sdf, int32_t V, int32_t K,

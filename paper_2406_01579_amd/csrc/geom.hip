@@ -346,8 +346,9 @@ __device__ __forceinline__ uint32_t vs_item() {
 // to one point (a bucket of thousands) 3434 and 786 us.  Bound by k_edge_bin's
 // LDS set (101 us) and, without order, by an atomic per pair.  (Buckets past LDS
 // sorted by one block's merges instead: 13.5 ms for that point.)  What the sort
-// would still do faster is tets that all share one vertex, and few others: 60,000
-// of them 110 and 151 us, 500,000 394 and 845 us, a block's pass over a bucket.
+// would still do faster is random tets that all share one vertex: 100,000 on
+// 80,000 vertices 132 and 213 us, 500,000 on 400,000 392 and 759 us, a block's pass
+// over a bucket.
 // ---------------------------------------------------------------------------
 constexpr int EB_T = 512;             // threads
 constexpr uint32_t EB_CHUNK = 512;    // tets per chunk
@@ -1330,6 +1331,11 @@ __global__ __launch_bounds__(RT) void k_reg_losses(const float* part, int nb, do
   }
 }
 
+// Vertices that per-vertex workspaces sized by the tets make room for: a mesh has
+// some six tets per vertex.  With more, most belong to no tet or the tets share
+// few, and the calls take the ways that need no such array, as slow as they are.
+inline uint64_t mesh_vertices(int32_t K) { return (uint64_t)K + 1024; }
+
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 inline int bit_length(uint32_t x) { return x ? 32 - __builtin_clz(x) : 0; }
 
@@ -1343,7 +1349,7 @@ EdgeLayout edge_layout(int32_t K) {
   E.sort_blocks = (n + SORT_TILE - 1) / SORT_TILE;
   E.edge_blocks = (n + EDGE_TILE - 1) / EDGE_TILE;
   // binned: the vertices the per-vertex arrays have room for
-  E.verts = 4ull * (uint64_t)K + 1024;
+  E.verts = mesh_vertices(K);
   size_t o = 0;
   E.o_n = o; o += al(16);
   E.o_ka = o; o += al(4 * n);
@@ -1358,11 +1364,10 @@ EdgeLayout edge_layout(int32_t K) {
   return E;
 }
 
-// The binned build where the vertex arrays fit the workspace (sized by K; past
-// that most vertices belong to no tet) and the buckets are short on average: a
-// mesh has some six tets per vertex, and up to eight are allowed.  Random tets, a
-// million of them: at 6 per vertex 777 us against 778 us with the sort, at 11
-// 846 and 777, at 50 1590 and 608, where what counts is the buckets' own sort.
+// The binned build where the vertex arrays fit the workspace and the buckets are
+// short on average: up to eight tets per vertex.  Random tets, a million of them:
+// at 6 per vertex 777 us against 778 us with the sort, at 11 846 and 777, at 50
+// 1590 and 608, where what counts is the buckets' own sort.
 static bool mesh_edges_binned_fits(uint64_t K, uint64_t V, const EdgeLayout& E) {
   return V + 1 <= E.verts && K <= 8 * V;
 }
@@ -1504,7 +1509,7 @@ MTLayout mt_layout(int32_t K, int64_t edge_cap) {
   MTLayout M{};
   M.edge_blocks = ((uint64_t)edge_cap + EDGE_TILE - 1) / EDGE_TILE;
   M.tet_blocks = ((uint64_t)K + EDGE_TILE - 1) / EDGE_TILE;
-  M.verts = (uint64_t)edge_cap;   // vertices whose first edges the table holds
+  M.verts = std::min<uint64_t>((uint64_t)edge_cap, mesh_vertices(K));   // vertices whose first edges the table holds
   size_t o = 0;
   M.o_vid = o; o += al(4 * (size_t)edge_cap);
   M.o_first = o; o += al(4 * (size_t)M.verts);
