@@ -1067,12 +1067,13 @@ __global__ __launch_bounds__(RT) void k_mt_edge_mark(const float* sdf, int32_t V
     const uint64_t m = __ballot(cut);
     if (lane == 0u && j0 + 64u * i < ne) mark[(j0 + 64u * i) / 64u] = m;
     cnt += (uint32_t)__popcll(m);
-    if (first_edge && ok) {
+    if (first_edge) {
       // edges ascend by (a, b): the first of its lower vertex differs from the
-      // one before (an unused vertex's entry is never read)
+      // one before (an unused vertex's entry is never read; every lane takes part
+      // in the exchange, also one whose own edge is foreign or past the list)
       int before = __shfl_up(e[i].x, 1, 64);
-      if (lane == 0u) before = j > 0u ? reinterpret_cast<const int2*>(edges)[j - 1u].x : -1;
-      if (before != e[i].x) first_edge[e[i].x] = j;
+      if (lane == 0u) before = j > 0u && j < ne ? reinterpret_cast<const int2*>(edges)[j - 1u].x : -1;
+      if (ok && before != e[i].x) first_edge[e[i].x] = j;
     }
   }
   if (lane == 0u) wsum[wave] = cnt;
