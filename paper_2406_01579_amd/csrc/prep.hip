@@ -1,8 +1,9 @@
 // Per-scene and per-view preparation kernels of the gfx950 tetrahedron
 // rasterizer: descriptor upload, the alpha_max pre-filter with order-
 // preserving compaction and per-tet normal/colour (Sec. 3.2, App. A.3),
-// projection and tile counting (Sec. 3.3), the device-wide scan of tile
-// counts, tile-duplicated key emission, and tile ranges.
+// projection and binning, tile lists, placement, the dispatch orders, depth
+// order inside every tile (Sec. 3.3), the backward's gradient clear; and the
+// coarse-to-fine bounds and grids (App. B).
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -228,7 +229,7 @@ __device__ void prefilter_totals(void* ws, const Layout& L, uint32_t* lds /*[8]*
 // the equivalent 3x3 edge system), mean colour.  Each block finds the kept
 // tets before it by summing the counts of the blocks before it (all threads
 // at once); block 0 also writes the per-scene and per-view totals.
-__global__ __launch_bounds__(PF_THREADS) void k_pf_scatter(void* ws, Layout L, float tf) {
+__global__ __launch_bounds__(PF_THREADS) void k_pf_scatter(void* ws, Layout L) {
   const DevScene* sc = at<const DevScene>(ws, L.o_scene);
   const uint32_t* cnt = at<const uint32_t>(ws, L.o_pf_cnt);
   TetRec* trec = at<TetRec>(ws, L.o_trec);
@@ -324,7 +325,7 @@ static unsigned pf_scatter_blocks(const Layout& L) {
 
 hipError_t launch_prefilter(void* ws, const Layout& L, const render_params& p, hipStream_t st) {
   if (L.pf_blocks > 0) k_pf_count<<<(unsigned)L.pf_blocks, PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
-  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
+  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L);
   return hipGetLastError();
 }
 
@@ -346,7 +347,7 @@ hipError_t launch_desc_prefilter(const DevScene* hs, int ns, const DevView* hv, 
   Blob b;
   std::memcpy(b.w, img.data(), img.size());
   k_pf_count_desc<<<(unsigned)L.pf_blocks, PF_THREADS, 0, st>>>(b, (int)words, ws, L, p.prefilter_tf);
-  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L, p.prefilter_tf);
+  k_pf_scatter<<<pf_scatter_blocks(L), PF_THREADS, 0, st>>>(ws, L);
   return hipGetLastError();
 }
 

@@ -9,21 +9,6 @@
 namespace ts {
 namespace {
 
-// The records of sorted entries [base, base + n) into LDS, eight threads per
-// 128-byte record.  With rfirst, the copy's first-entry field comes from the
-// records' first entries, where the placement kernel writes them.
-__device__ __forceinline__ void load_recs(ViewRec* recs, const ViewRec* __restrict__ vrec,
-                                          const uint32_t* __restrict__ srec, uint32_t base, int n, int nthreads,
-                                          const uint32_t* __restrict__ rfirst = nullptr) {
-  for (int q = threadIdx.x; q < n * 8; q += nthreads) {
-    const int e = q >> 3, part = q & 7;
-    const uint32_t r = srec[base + e];
-    float4 t = reinterpret_cast<const float4*>(&vrec[r])[part];
-    if (rfirst && part == 7) t.w = __uint_as_float(rfirst[r]);   // entry0 is the last word of the record
-    reinterpret_cast<float4*>(&recs[e])[part] = t;
-  }
-}
-
 // What the forward's evaluation needs of a record: all but the features,
 // which go to a table of their own.
 struct alignas(16) EvalRec {
@@ -31,12 +16,6 @@ struct alignas(16) EvalRec {
   uint32_t rx, ry, span[2];
 };
 static_assert(sizeof(EvalRec) == 96 && offsetof(EvalRec, rx) == 80, "six 16-byte parts");
-
-__device__ __forceinline__ bool has_pixel(const ViewRec& R, int i, int j) {
-  int i0, i1, j0, j1;
-  unpack_rect(R, i0, i1, j0, j1);
-  return i >= i0 && i <= i1 && j >= j0 && j <= j1;
-}
 
 struct Tile8 {
   int view, tile;
@@ -69,38 +48,6 @@ __device__ __forceinline__ Tile8 tile8(const DevView* vw, const TileSlot& sl) {
   c.j = c.ty * 8 + (lane >> 3);
   c.inside = c.i < V.W && c.j < V.H;
   return c;
-}
-
-// The tile's reduced gradient of each chunk entry (gacc[e][0..TGRAD_STRIDE))
-// goes to the entry's pre-sort slot: the record's first entry plus this
-// tile's row-major index inside the record's tile rectangle; the slot is
-// flagged as reached.  With chunk_rec (the chunk's record indices) it is
-// added into its record's accumulator instead.
-// (A slot past the entry capacity belongs to an overflowed forward, whose
-// outputs are invalid anyway: it is skipped.)
-__device__ __forceinline__ void store_entry_grads(const ViewRec* recs, const float (*gacc)[TGRAD_STRIDE], int n,
-                                                  const Tile8& c, float* __restrict__ tgrad,
-                                                  uint8_t* __restrict__ eflag, int nthreads, uint64_t cap,
-                                                  const uint32_t* __restrict__ chunk_rec = nullptr) {
-  if (chunk_rec) {
-    for (int q = threadIdx.x; q < n * (TGRAD_STRIDE - 1); q += nthreads) {
-      const int e = q / (TGRAD_STRIDE - 1), k = q - e * (TGRAD_STRIDE - 1);
-      const float v = gacc[e][k];
-      if (v != 0.0f) unsafeAtomicAdd(&tgrad[(size_t)chunk_rec[e] * TGRAD_STRIDE + k], v);
-    }
-    return;
-  }
-  for (int q = threadIdx.x; q < n * TGRAD_STRIDE; q += nthreads) {
-    const int e = q / TGRAD_STRIDE, k = q - e * TGRAD_STRIDE;
-    const ViewRec& R = recs[e];
-    int i0, i1, j0, j1;
-    unpack_rect(R, i0, i1, j0, j1);
-    const int tx0 = i0 >> 3, ty0 = j0 >> 3, nx = (i1 >> 3) - tx0 + 1;
-    const size_t d = (size_t)R.entry0 + (size_t)((c.ty - ty0) * nx + (c.tx - tx0));
-    if (d >= cap) continue;
-    tgrad[d * TGRAD_STRIDE + k] = gacc[e][k];
-    if (k == 0) eflag[d] = 1;
-  }
 }
 
 // ---------------------------------------------------------------------------
