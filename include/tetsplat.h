@@ -133,9 +133,10 @@ typedef struct {
   int64_t kept;         /* tets kept by the pre-filter, summed over scenes */
   int64_t records;      /* (view, kept tet) records */
   int32_t overflow;     /* bit 0: kept capacity, bit 1: entry capacity exceeded (the forward's
-                           outputs are invalid); bit 2: the (entry, pixel) pairs the forward
-                           blended exceed the entry capacity (multi-wave 8x8 path): the outputs
-                           stand, a backward of this forward would not */
+                           outputs are invalid: after bit 1 every list is empty, the images
+                           are their backgrounds); bit 2: the (entry, pixel) pairs the forward
+                           blended exceed the entry capacity (multi-wave 8x8 and resort-window
+                           paths): the outputs stand, a backward of this forward would not */
   int32_t invalid_index;/* nonzero if some tet had a vertex index outside [0, V) */
   int64_t entry_capacity, kept_capacity;
   int64_t entries_needed; /* entry capacity the forward and its backward want (exact even on
@@ -267,9 +268,10 @@ enum {
   RENDER_STAGE_SCAN = 4,        /* the scan of the tiles' entry counts: tile lists */
   RENDER_STAGE_EMIT = 5,        /* entries placed into the tile lists; the forward's dispatch order */
   RENDER_STAGE_PAIR_GRADS = 6,  /* backward: per-(entry, pixel) gradients summed per (tile, entry) */
-  RENDER_STAGE_RANGES = 7,      /* dispatch orders (forward and backward) */
+  RENDER_STAGE_RANGES = 7,      /* not recorded any more (reads 0; the number stays): the forward's dispatch
+                                   order is part of EMIT, the backward's of ZERO_GRADS */
   RENDER_STAGE_COMPOSITE = 8,   /* forward compositing */
-  RENDER_STAGE_ZERO_GRADS = 9,  /* gradient buffer clear */
+  RENDER_STAGE_ZERO_GRADS = 9,  /* backward descriptors, gradient buffer clear, the backward's dispatch order */
   RENDER_STAGE_COMPOSITE_BWD = 10, /* reverse-order compositing backward (walk and recurrence) */
   RENDER_STAGE_VERTEX_BWD = 11, /* per-record chain to vertices */
   RENDER_NSTAGES = 12
