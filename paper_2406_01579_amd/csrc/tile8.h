@@ -1,7 +1,8 @@
 // Helpers shared by the compositing kernels that run one 8x8 pixel tile per
 // workgroup (one pixel per lane of each 64-lane wave): the tile's pixel
-// coordinates, the record-rectangle test, and the coalesced LDS staging of a
-// chunk of sorted records (8 lanes per 128-byte record).
+// coordinates, the lists of the (entry, pixel) pairs to evaluate, and the
+// coalesced LDS staging of a chunk of sorted records (8 lanes per 128-byte
+// record).
 #pragma once
 
 #include "ts_device.h"
