@@ -56,7 +56,7 @@ __device__ __forceinline__ TileCtx tile_ctx(const DevView* vw, const TileSlot* s
 
 // The records of sorted entries [base, base + n) into LDS, eight threads per
 // 128-byte record.  With rfirst, the copy's first-entry field comes from the
-// records' first entries, where the placement kernel writes them.
+// records' first entries, where the projection writes them.
 __device__ __forceinline__ void load_chunk(ViewRec* recs, const ViewRec* __restrict__ vrec,
                                            const uint32_t* __restrict__ srec, uint32_t base, int n, int nthreads,
                                            const uint32_t* __restrict__ rfirst = nullptr) {
