@@ -127,7 +127,7 @@ def program(tmp_path_factory):
              _block(src, fn + "fast_expm1_neg"), _block(src, fn + "pixel_eval"), _block(src, fn + "never_blends")]
     d = tmp_path_factory.mktemp("never_blends")
     (d / "t.cpp").write_text(PRELUDE + "\n".join(parts) + MAIN)
-    subprocess.run([cxx, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-w", "-o", str(d / "t"), str(d / "t.cpp")],
+    subprocess.run([cxx, "-O2", "-std=c++17", "-ffp-contract=off", "-w", "-o", str(d / "t"), str(d / "t.cpp")],
                    check=True)
     return str(d / "t")
 
